@@ -224,7 +224,7 @@ typedef struct {
 
 /* Bytes of device workspace lg_search asks for with n_points points and n_poses
  * poses.  With opt_outer > 0 this includes per-candidate arrays that let the
- * criteria of Alg. 2 gather their slow LPs into launches of their own; lg_search
+ * criteria of Alg. 2 solve a contact step's LPs in one launch over all sets; lg_search
  * also accepts a workspace without them (down to the size with opt_outer = 0
  * plus Alg. 2's cell grid and candidate ids) and then solves each step's LPs in
  * one launch per round, with the same outputs.  A smaller workspace fails with

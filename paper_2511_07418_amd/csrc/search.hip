@@ -240,71 +240,95 @@ __device__ inline void duff_basis(double nx, double ny, double nz, double *x, do
 constexpr double kLpTol = 1e-12;  // reduced-cost and ratio-tie tolerance
 constexpr double kLpPiv = 1e-9;   // smallest admissible pivot element
 constexpr int kBlandAfter = 48;   // pivots priced by Dantzig's rule before Bland's
+constexpr int kLpChecks = 4;      // residual corrections of one LP at most
+// Lanes of a wave at a candidate optimum before they are served together: fewer
+// run the refinement and the reloads more often, more let lanes wait (1.2 M LPs
+// of 5 contacts: 8 lanes 0.82 ms, 16 0.67, 24 0.63, 32 0.65).
+constexpr int kLpBatch = 24;
+
+// contact data of each lane's set, lane-contiguous: cd[6 i + c][tid] (point,
+// normal), da[i][tid] the reciprocal of contact i's tangent basis (up to 6
+// contacts; beyond that it is recomputed, the LDS would cost occupancy)
+template <int KM>
+struct LpLds {
+    static constexpr bool kDa = KM <= 6;
+    float cd[KM * 6][256];
+    double da[kDa ? KM : 1][256];
+};
+
+template <int KM>
+__device__ inline void lp_load(LpLds<KM> &L, int tid, int ci, const float *__restrict__ pts,
+                               const float *__restrict__ nrm, int N, int idx)
+{
+    L.cd[6 * ci + 0][tid] = pts[idx];
+    L.cd[6 * ci + 1][tid] = pts[N + idx];
+    L.cd[6 * ci + 2][tid] = pts[2 * N + idx];
+    L.cd[6 * ci + 3][tid] = nrm[idx];
+    L.cd[6 * ci + 4][tid] = nrm[N + idx];
+    L.cd[6 * ci + 5][tid] = nrm[2 * N + idx];
+    if constexpr (LpLds<KM>::kDa) L.da[ci][tid] = duff_a((double)L.cd[6 * ci + 5][tid]);
+}
 
 // ---- force-closure LP, one set per lane -------------------------------------
 // Revised simplex with an explicit 7x7 basis inverse per lane.  Reduced
 // costs are priced through the duals y = c_B^T B^-1: for wrench column
 // (contact i, edge e),
 //   y^T a_ie = u_i . d_ie + y_6,  u_i = y_f + (y_m x p_i) / rho,
-//   u_i . d_ie = -u_i.n_i + mu (cos_e u_i.x_i + sin_e u_i.y_i),
-// so pricing all k*m columns costs O(k) dot products plus 2 FMAs per edge.
-// Bland's rule: lowest entering index, ratio ties to the lowest basic
-// variable; pivots below kLpPiv are not admissible.  Double precision: the
-// verdict is a thresholded decision and the LP is latency-bound.
+//   u_i . d_ie = -u_i.n_i + mu (cos_e u_i.x_i + sin_e u_i.y_i).
+// With the Duff basis (s = sign n_z, a = -1 / (s + n_z)) and
+// h = a (n_x u_x + n_y u_y) - u_z, u.x = u_x + s n_x h and u.y = s u_y + n_y h,
+// so a contact's three projections take six multiply-adds and no basis.  For
+// the 8-edge cone (MC == 8) the best edge of a contact is the largest of
+// |bx|, |by| and (|bx| + |by|) / sqrt 2 (b = (u.x, u.y)); its index is formed
+// once, for the winning contact.  The slack pair of row r costs 1 - |y_r|.
+// The duals are updated with the pivot row instead of recomputed (c_B^T B^-1
+// is 49 multiply-adds), and a pivot is one multiply-add per entry of B^-1:
+// row r loses (al_r - [r == lr]) / al_lr times the old pivot row.  Dantzig's
+// rule for the first kBlandAfter pivots, then Bland's (lowest entering index,
+// ratio ties to the lowest basic variable; no cycling); pivots below kLpPiv
+// are not admissible.  Double precision: the verdict is a thresholded decision.
 // At a candidate optimum x_B and y are refined against the original columns
 // (one residual correction through the current B^-1) and the pricing is
-// repeated, so drift in B^-1 cannot end the search early or bias t*.  (One
-// correction keeps t* within 1e-9 of the FP64 oracle's tableau simplex, as
-// two did, at a tenth less time in the Alg. 2 criteria.)
-// (LpConst: the cone edge directions, shared with the batched launch.)
+// repeated, so drift in B^-1 or y cannot end the search early or bias t*.
+// What bounds it: VALU issue, and the lanes of a wave that wait for the
+// wave's slowest LP.  The pricing was half of a pivot's ~1,000 instructions
+// (each edge's reduced cost and each basis written out), the row exchange
+// with its selects a third.  Measured (65,536 poses x 64 sets of 5 contacts,
+// 1.2 M LPs): 2.05 -> 0.63 ms with the lanes refilled as in lp_wave; 4,096 sets
+// of 3 contacts 165 -> 55 us; Alg. 2's criteria of a contact step (8,192 poses)
+// 1.57 -> 0.63 ms.
+template <int KM, int MC>
+struct Lp {
+    double Bi[7][7], xB[7], y[7];
+    int basis[7];
+    int k, n, m;
+    double mu, inv_rho;
 
-// t* of the set held in this lane's LDS column (cd[6 i + c][tid]); status
-// 0 = optimal, 1 = pivot cap, 2 = unbounded ratio test (not expected).
-// MC > 0: the cone has MC edges (m == MC), known at compile time, so the
-// pricing's edge loop is unrolled over constant edge directions.
-template <int KM, bool WARM = false, int MC = 0>
-__device__ inline double lp_lane(float (&cd)[KM * 6][256], int tid, int k, int m, double mu, double rho,
-                                 int max_pivots, const LpConst &cs, int &status_out, int (*warm)[256] = nullptr)
-{
-    const int n = k * m;
-    const double inv_rho = 1.0 / rho;
-    // the reciprocal of each contact's tangent basis, once per LP (every
-    // pricing and column rebuilds the basis); in LDS up to 6 contacts, beyond
-    // that recomputed (the LDS would cost the 8-contact kernels occupancy)
-    constexpr bool kDa = KM <= 6;
-    __shared__ double da[kDa ? KM : 1][256];
-    if constexpr (kDa)
-        for (int i = 0; i < k; ++i) da[i][tid] = duff_a((double)cd[6 * i + 5][tid]);
-    auto basis_of = [&](int ci, double nx, double ny, double nz, double *x, double *y) {
-        if constexpr (kDa)
-            duff_basis_a(nx, ny, nz, da[ci][tid], x, y);
-        else
-            duff_basis(nx, ny, nz, x, y);
-    };
-    // contact i's point and normal (each lane reads only its own column)
-    auto contact = [&](int ci, double &px, double &py, double &pz, double &nx, double &ny, double &nz) {
-        px = cd[6 * ci + 0][tid];
-        py = cd[6 * ci + 1][tid];
-        pz = cd[6 * ci + 2][tid];
-        nx = cd[6 * ci + 3][tid];
-        ny = cd[6 * ci + 4][tid];
-        nz = cd[6 * ci + 5][tid];
-    };
+    __device__ inline void basis_of(const LpLds<KM> &L, int tid, int ci, double &px, double &py, double &pz,
+                                    double &nx, double &ny, double &nz, double &a) const
+    {
+        px = L.cd[6 * ci + 0][tid];
+        py = L.cd[6 * ci + 1][tid];
+        pz = L.cd[6 * ci + 2][tid];
+        nx = L.cd[6 * ci + 3][tid];
+        ny = L.cd[6 * ci + 4][tid];
+        nz = L.cd[6 * ci + 5][tid];
+        if constexpr (LpLds<KM>::kDa) a = L.da[ci][tid]; else a = duff_a(nz);
+    }
+
     // original column j of [W^T -I I; 1 0 0]
-    auto column = [&](int j, double *a) {
-#pragma unroll
-        for (int r = 0; r < 7; ++r) a[r] = 0.0;
+    __device__ inline void column(const LpLds<KM> &L, int tid, const LpConst &cs, int j, double *a) const
+    {
         if (j < n) {
             const int mm = MC > 0 ? MC : m;  // a constant divisor for the 8-edge kernels
             const int ci = j / mm, e = j - ci * mm;
-            double px, py, pz, nx, ny, nz;
-            contact(ci, px, py, pz, nx, ny, nz);
-            double x[3], y[3];
-            basis_of(ci, nx, ny, nz, x, y);
-            const double c = cs.ce[e], s = cs.se[e];
-            const double dx = -nx + mu * (c * x[0] + s * y[0]);
-            const double dy = -ny + mu * (c * x[1] + s * y[1]);
-            const double dz = -nz + mu * (c * x[2] + s * y[2]);
+            double px, py, pz, nx, ny, nz, ia, x[3], t[3];
+            basis_of(L, tid, ci, px, py, pz, nx, ny, nz, ia);
+            duff_basis_a(nx, ny, nz, ia, x, t);
+            const double c = mu * cs.ce[e], s = mu * cs.se[e];
+            const double dx = fma(s, t[0], fma(c, x[0], -nx));
+            const double dy = fma(s, t[1], fma(c, x[1], -ny));
+            const double dz = fma(s, t[2], fma(c, x[2], -nz));
             a[0] = dx;
             a[1] = dy;
             a[2] = dz;
@@ -312,328 +336,484 @@ __device__ inline double lp_lane(float (&cd)[KM * 6][256], int tid, int k, int m
             a[4] = (pz * dx - px * dz) * inv_rho;
             a[5] = (px * dy - py * dx) * inv_rho;
             a[6] = 1.0;
-        } else if (j < n + 6) {
-#pragma unroll
-            for (int r = 0; r < 6; ++r) a[r] = (r == j - n) ? -1.0 : 0.0;
         } else {
+            const int r0 = j < n + 6 ? j - n : j - n - 6;
+            const double v = j < n + 6 ? -1.0 : 1.0;
 #pragma unroll
-            for (int r = 0; r < 6; ++r) a[r] = (r == j - n - 6) ? 1.0 : 0.0;
-        }
-    };
-    // initial basis: g_0 on the normalisation row, s-_r (w0_r <= 0) or s+_r
-    double Bi[7][7], xB[7];
-    int basis[7];
-#define LG_LP_COLD()                                                                                        \
-    do {                                                                                                    \
-        double w0[7];                                                                                       \
-        column(0, w0);                                                                                      \
-        _Pragma("unroll") for (int r = 0; r < 7; ++r) _Pragma("unroll") for (int c = 0; c < 7; ++c) Bi[r][c] = 0.0; \
-        _Pragma("unroll") for (int r = 0; r < 6; ++r) {                                                       \
-            const double sg = w0[r] <= 0.0 ? 1.0 : -1.0;                                                    \
-            basis[r] = w0[r] <= 0.0 ? n + 6 + r : n + r;                                                    \
-            Bi[r][r] = sg;                                                                                  \
-            Bi[r][6] = -sg * w0[r];                                                                         \
-            xB[r] = -sg * w0[r];                                                                            \
-        }                                                                                                   \
-        Bi[6][6] = 1.0;                                                                                     \
-        basis[6] = 0;                                                                                       \
-        xB[6] = 1.0;                                                                                        \
-    } while (0)
-// replace the basic variable of row lr by column e (al = B^-1 a_e)
-#define LG_LP_PIVOT(lr, al, e)                                                                              \
-    do {                                                                                                    \
-        double pv = 1.0, prow[7], px = 0.0;                                                                 \
-        _Pragma("unroll") for (int c = 0; c < 7; ++c) prow[c] = 0.0;                                        \
-        _Pragma("unroll") for (int r = 0; r < 7; ++r) if (r == (lr)) {                                      \
-            pv = (al)[r];                                                                                   \
-            px = xB[r];                                                                                     \
-            _Pragma("unroll") for (int c = 0; c < 7; ++c) prow[c] = Bi[r][c];                               \
-        }                                                                                                   \
-        const double inv = 1.0 / pv;                                                                        \
-        _Pragma("unroll") for (int c = 0; c < 7; ++c) prow[c] *= inv;                                       \
-        px *= inv;                                                                                          \
-        _Pragma("unroll") for (int r = 0; r < 7; ++r) {                                                     \
-            if (r == (lr)) {                                                                                \
-                _Pragma("unroll") for (int c = 0; c < 7; ++c) Bi[r][c] = prow[c];                           \
-                xB[r] = px;                                                                                 \
-                basis[r] = (e);                                                                             \
-            } else {                                                                                        \
-                _Pragma("unroll") for (int c = 0; c < 7; ++c) Bi[r][c] -= (al)[r] * prow[c];                \
-                xB[r] -= (al)[r] * px;                                                                      \
-            }                                                                                               \
-        }                                                                                                   \
-    } while (0)
-    bool need_cold = true;
-    // Warm start (the "free lunch" of Sec. 5.4): the optimal basis of a
-    // neighbouring problem -- the same column ids, one contact's columns
-    // rebuilt from its new point -- is brought into the cold basis column by
-    // column, each by a primal pivot with the usual ratio test (so the basis
-    // stays feasible; a column without an admissible pivot is left out).  The
-    // simplex then continues from that basis, near the optimum when the
-    // problems are close.  The optimum, t*, does not depend on the start.
-    // warm[r][tid]: the column ids in, the final basis out.
-    if constexpr (WARM) {
-        if (warm[0][tid] >= 0) {
-            LG_LP_COLD();
-            need_cold = false;
-#pragma unroll 1
-            for (int w = 0; w < 7; ++w) {
-                const int col = warm[w][tid];
-                bool inb = false;
-#pragma unroll
-                for (int r = 0; r < 7; ++r) inb |= basis[r] == col;
-                if (inb) continue;
-                double a[7], al[7];
-                column(col, a);
-#pragma unroll
-                for (int r = 0; r < 7; ++r) {
-                    double sacc = 0.0;
-#pragma unroll
-                    for (int c = 0; c < 7; ++c) sacc += Bi[r][c] * a[c];
-                    al[r] = sacc;
-                }
-                int lr = -1;
-                double bx = 0.0, ba = 1.0;
-#pragma unroll
-                for (int r = 0; r < 7; ++r) {
-                    if (al[r] > kLpPiv) {
-                        const double lhs = xB[r] * ba, rhs = bx * al[r];
-                        const double band = kLpTol * (ba + fabs(bx)) * al[r];
-                        if (lr < 0 || lhs < rhs - band || (fabs(lhs - rhs) <= band && basis[r] < basis[lr])) {
-                            lr = r;
-                            bx = xB[r];
-                            ba = al[r];
-                        }
-                    }
-                }
-                if (lr >= 0) LG_LP_PIVOT(lr, al, col);
-            }
+            for (int r = 0; r < 6; ++r) a[r] = r == r0 ? v : 0.0;
+            a[6] = 0.0;
         }
     }
-    if (need_cold) LG_LP_COLD();
-    auto cost = [&](int j) { return j >= n ? 1.0 : 0.0; };
-    auto duals = [&](double *y) {
+
+    // initial basis: g_0 on the normalisation row, s-_r (w0_r <= 0) or s+_r
+    __device__ inline void cold(const LpLds<KM> &L, int tid, const LpConst &cs)
+    {
+        double w0[7];
+        column(L, tid, cs, 0, w0);
 #pragma unroll
-        for (int c = 0; c < 7; ++c) {
-            double s = 0.0;
+        for (int r = 0; r < 7; ++r)
 #pragma unroll
-            for (int r = 0; r < 7; ++r) s += cost(basis[r]) * Bi[r][c];
-            y[c] = s;
+            for (int c = 0; c < 7; ++c) Bi[r][c] = 0.0;
+        y[6] = 0.0;
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            const double sg = w0[r] <= 0.0 ? 1.0 : -1.0;
+            basis[r] = w0[r] <= 0.0 ? n + 6 + r : n + r;
+            Bi[r][r] = sg;
+            Bi[r][6] = -sg * w0[r];
+            xB[r] = -sg * w0[r];
+            y[r] = sg;
+            y[6] += xB[r];
         }
-    };
-    // Pricing.  Dantzig (most negative reduced cost, ties to the lowest index)
-    // for the first kBlandAfter pivots; Bland (first negative) afterwards,
-    // which rules out cycling.  -1 when no reduced cost is below -kLpTol.
-    auto price = [&](const double *y, bool bland) {
+        Bi[6][6] = 1.0;
+        basis[6] = 0;
+        xB[6] = 1.0;
+    }
+
+    // entering column, -1 when no reduced cost is below -kLpTol; d: its reduced cost
+    __device__ inline int price(const LpLds<KM> &L, int tid, const LpConst &cs, bool bland, double &d) const
+    {
+        const double m0 = y[3] * inv_rho, m1 = y[4] * inv_rho, m2 = y[5] * inv_rho;
         int e = -1;
         double best = -kLpTol;
-        for (int i = 0; i < k && !(bland && e >= 0); ++i) {
-            double px, py, pz, nx, ny, nz;
-            contact(i, px, py, pz, nx, ny, nz);
+        auto project = [&](int i, double &an, double &bx, double &by) {
+            double px, py, pz, nx, ny, nz, a;
+            basis_of(L, tid, i, px, py, pz, nx, ny, nz, a);
             // u = y_f + (y_m x p) / rho
-            const double ux = y[0] + (y[4] * pz - y[5] * py) * inv_rho;
-            const double uy = y[1] + (y[5] * px - y[3] * pz) * inv_rho;
-            const double uz = y[2] + (y[3] * py - y[4] * px) * inv_rho;
-            double x[3], yy[3];
-            basis_of(i, nx, ny, nz, x, yy);
-            const double an = ux * nx + uy * ny + uz * nz;
-            const double bx = ux * x[0] + uy * x[1] + uz * x[2];
-            const double by = ux * yy[0] + uy * yy[1] + uz * yy[2];
-            if constexpr (MC > 0) {
-                bool done = false;
-#pragma unroll
-                for (int ee = 0; ee < MC; ++ee) {
-                    const double d = -(-an + mu * (cs.ce[ee] * bx + cs.se[ee] * by)) - y[6];
-                    if (!done && d < best) {
-                        best = d;
-                        e = i * MC + ee;
-                        done = bland;
-                    }
+            const double ux = fma(m1, pz, fma(-m2, py, y[0]));
+            const double uy = fma(m2, px, fma(-m0, pz, y[1]));
+            const double uz = fma(m0, py, fma(-m1, px, y[2]));
+            const double t = fma(nx, ux, ny * uy), h = fma(a, t, -uz), sg = copysign(1.0, nz);
+            an = fma(nz, uz, t);
+            bx = fma(sg * nx, h, ux);
+            by = fma(ny, h, sg * uy);
+        };
+        if (MC == 8 && !bland) {
+            double sbx = 0.0, sby = 0.0;
+            int ci = -1;
+            for (int i = 0; i < k; ++i) {
+                double an, bx, by;
+                project(i, an, bx, by);
+                const double ax = fabs(bx), ay = fabs(by);
+                const double r = fmax(fmax(ax, ay), (ax + ay) * M_SQRT1_2);
+                const double di = fma(-mu, r, an) - y[6];
+                if (di < best) {
+                    best = di;
+                    ci = i;
+                    sbx = bx;
+                    sby = by;
                 }
-            } else {
+            }
+            if (ci >= 0) {
+                const double ax = fabs(sbx), ay = fabs(sby), dg = (ax + ay) * M_SQRT1_2;
+                const bool xn = sbx < 0.0, yn = sby < 0.0;
+                const int diag = yn ? (xn ? 5 : 7) : (xn ? 3 : 1), ex = xn ? 4 : 0, ey = yn ? 6 : 2;
+                e = ci * 8 + (dg > fmax(ax, ay) ? diag : (ax >= ay ? ex : ey));
+            }
+        } else {
+            for (int i = 0; i < k && !(bland && e >= 0); ++i) {
+                double an, bx, by;
+                project(i, an, bx, by);
                 for (int ee = 0; ee < m; ++ee) {
-                    const double d = -(-an + mu * (cs.ce[ee] * bx + cs.se[ee] * by)) - y[6];
-                    if (d < best) {
-                        best = d;
+                    const double di = fma(-mu, fma(cs.ce[ee], bx, cs.se[ee] * by), an) - y[6];
+                    if (di < best) {
+                        best = di;
                         e = i * m + ee;
                         if (bland) break;
                     }
                 }
             }
         }
-        for (int r = 0; r < 6 && !(bland && e >= 0); ++r)
-            if (1.0 + y[r] < best) {
-                best = 1.0 + y[r];
-                e = n + r;
+        if (bland) {
+            for (int r = 0; r < 12 && e < 0; ++r) {
+                double v = 0.0;
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+                    if (q == r % 6) v = r < 6 ? 1.0 + y[q] : 1.0 - y[q];
+                if (v < best) {
+                    best = v;
+                    e = n + r;
+                }
             }
-        for (int r = 0; r < 6 && !(bland && e >= 0); ++r)
-            if (1.0 - y[r] < best) {
-                best = 1.0 - y[r];
-                e = n + 6 + r;
-            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 6; ++r)
+                if (1.0 - fabs(y[r]) < best) {
+                    best = 1.0 - fabs(y[r]);
+                    e = y[r] < 0.0 ? n + r : n + 6 + r;
+                }
+        }
+        d = best;
         return e;
-    };
-    // residual corrections of x_B (B x = e_6) and y (B^T y = c_B)
-    auto refine = [&](double *y) {
-        double rx[7] = {0, 0, 0, 0, 0, 0, 1.0}, ry[7];
-#pragma unroll 1
-        for (int q = 0; q < 7; ++q) {
-            double a[7];
-            column(basis[q], a);
-            double dot = 0.0;
-#pragma unroll
-            for (int r = 0; r < 7; ++r) {
-                rx[r] -= a[r] * xB[q];
-                dot += a[r] * y[r];
-            }
-            ry[q] = cost(basis[q]) - dot;
-        }
+    }
+
+    // al = B^-1 a
+    __device__ inline void solve(const double *a, double *al) const
+    {
 #pragma unroll
         for (int r = 0; r < 7; ++r) {
             double s = 0.0;
 #pragma unroll
-            for (int c = 0; c < 7; ++c) s += Bi[r][c] * rx[c];
-            xB[r] += s;
-        }
-#pragma unroll
-        for (int c = 0; c < 7; ++c) {
-            double s = 0.0;
-#pragma unroll
-            for (int r = 0; r < 7; ++r) s += ry[r] * Bi[r][c];
-            y[c] += s;
-        }
-    };
-    int piv = 0, status = 0, checks = 0;
-    for (;;) {
-        double y[7];
-        duals(y);
-        const bool bland = piv >= kBlandAfter;
-        int e = price(y, bland);
-        if (e < 0) {
-            if (checks >= 4) break;
-            ++checks;
-            refine(y);
-            e = price(y, bland);
-            if (e < 0) break;
-        }
-        if (piv >= max_pivots) {
-            status = 1;
-            break;
-        }
-        double a[7], al[7];
-        column(e, a);
-#pragma unroll
-        for (int r = 0; r < 7; ++r) {
-            double s = 0.0;
-#pragma unroll
-            for (int c = 0; c < 7; ++c) s += Bi[r][c] * a[c];
+            for (int c = 0; c < 7; ++c) s = fma(Bi[r][c], a[c], s);
             al[r] = s;
         }
-        // ratio test min x_B[r] / al[r] without divisions: the current best is
-        // kept as the fraction bx / ba (ba > 0) and ratios are compared by
-        // cross-multiplication; the tie band is kLpTol (1 + |best|).
-        int lr = -1;
+    }
+
+    // Ratio test min x_B[r] / al[r] without divisions: the current best is
+    // kept as the fraction bx / ba (ba > 0) and ratios are compared by
+    // cross-multiplication; the tie band is kLpTol (1 + |best|).
+    __device__ inline int ratio(const double *al) const
+    {
+        int lr = -1, bb = 0;
         double bx = 0.0, ba = 1.0;
 #pragma unroll
         for (int r = 0; r < 7; ++r) {
             if (al[r] > kLpPiv) {
                 const double lhs = xB[r] * ba, rhs = bx * al[r];
                 const double band = kLpTol * (ba + fabs(bx)) * al[r];
-                if (lr < 0 || lhs < rhs - band || (fabs(lhs - rhs) <= band && basis[r] < basis[lr])) {
+                if (lr < 0 || lhs < rhs - band || (fabs(lhs - rhs) <= band && basis[r] < bb)) {
                     lr = r;
                     bx = xB[r];
                     ba = al[r];
+                    bb = basis[r];
                 }
             }
         }
-        if (lr < 0) {
+        return lr;
+    }
+
+    // replace the basic variable of row lr by column e (al = B^-1 a_e, d its reduced cost)
+    __device__ inline void pivot(int lr, const double *al, int e, double d)
+    {
+        double oh[7], pv = 0.0, px = 0.0, prow[7];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+            oh[r] = r == lr ? 1.0 : 0.0;
+            pv = fma(oh[r], al[r], pv);
+            px = fma(oh[r], xB[r], px);
+        }
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+            prow[c] = oh[0] * Bi[0][c];
+#pragma unroll
+            for (int r = 1; r < 7; ++r) prow[c] = fma(oh[r], Bi[r][c], prow[c]);
+        }
+        double inv = __builtin_amdgcn_rcp(pv);
+        inv = fma(fma(-pv, inv, 1.0), inv, inv);
+        inv = fma(fma(-pv, inv, 1.0), inv, inv);
+        const double dy = d * inv;
+#pragma unroll
+        for (int c = 0; c < 7; ++c) y[c] = fma(dy, prow[c], y[c]);
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+            const double f = (oh[r] - al[r]) * inv;
+            xB[r] = fma(f, px, xB[r]);
+            basis[r] = r == lr ? e : basis[r];
+#pragma unroll
+            for (int c = 0; c < 7; ++c) Bi[r][c] = fma(f, prow[c], Bi[r][c]);
+        }
+    }
+
+    __device__ inline double cost(int j) const { return j >= n ? 1.0 : 0.0; }
+
+    // residual corrections of x_B (B x = e_6) and y (B^T y = c_B); a rolled loop,
+    // so that one column's registers are live at a time (unrolled it spills 68)
+    __device__ inline void refine(const LpLds<KM> &L, int tid, const LpConst &cs)
+    {
+        double rx[7] = {0, 0, 0, 0, 0, 0, 1.0}, ry[7];
+#pragma unroll 1
+        for (int q = 0; q < 7; ++q) {
+            int bq = basis[0];
+            double xq = xB[0];
+#pragma unroll
+            for (int r = 1; r < 7; ++r) {
+                bq = r == q ? basis[r] : bq;
+                xq = r == q ? xB[r] : xq;
+            }
+            double a[7];
+            column(L, tid, cs, bq, a);
+            double res = cost(bq);
+#pragma unroll
+            for (int r = 0; r < 7; ++r) {
+                rx[r] = fma(-a[r], xq, rx[r]);
+                res = fma(-a[r], y[r], res);
+            }
+#pragma unroll
+            for (int r = 0; r < 7; ++r) ry[r] = r == q ? res : ry[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+            double s = 0.0;
+#pragma unroll
+            for (int c = 0; c < 7; ++c) s = fma(Bi[r][c], rx[c], s);
+            xB[r] += s;
+        }
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+            double s = 0.0;
+#pragma unroll
+            for (int r = 0; r < 7; ++r) s = fma(ry[r], Bi[r][c], s);
+            y[c] += s;
+        }
+    }
+
+    __device__ inline bool basic(int j) const
+    {
+        bool in = false;
+#pragma unroll
+        for (int r = 0; r < 7; ++r) in |= basis[r] == j;
+        return in;
+    }
+
+    __device__ inline double tstar() const
+    {
+        double ts = 0.0;
+#pragma unroll
+        for (int r = 0; r < 7; ++r)
+            if (basis[r] >= n) ts += xB[r];
+        return ts;
+    }
+};
+
+// The LPs of a wave: lanes take LPs one after another instead of waiting for
+// the slowest of 64.  fetch(tid, t): load LP t of the wave's share into the
+// lane's column of L and set P.k, P.n (false: no LP, already written); done(t, ts,
+// status, P): write a finished one.  status 0 = optimal, 1 = pivot cap,
+// 2 = unbounded ratio test (not expected).  A lane at a candidate optimum waits
+// until kLpBatch lanes of its wave are (or none is running); those are then
+// refined, written and reloaded together, because that part (about two pivots'
+// instructions, and dependent loads) would otherwise run for a lane or two at
+// nearly every pivot.  Warm start (the "free lunch" of Sec. 5.4): warm(t, r) is
+// column id r of the optimal basis of a neighbouring problem -- the same column
+// ids, one contact's columns rebuilt from its new point -- or -1 at r = 0 for
+// none.  The seven columns are brought into the cold basis one per step, each
+// by a primal pivot with the usual ratio test (so the basis stays feasible; a
+// column without an admissible pivot is left out); the simplex continues from
+// there, near the optimum when the problems are close.  t* does not depend on
+// the start.
+template <int KM, int MC, bool WARM, class Fetch, class Warm, class Done>
+__device__ __forceinline__ void lp_wave(LpLds<KM> &L, int64_t next, int64_t end, int m, double mu, double rho,
+                                        int max_pivots, const LpConst &cs, Fetch fetch, Warm warm, Done done)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    enum { kIdle, kRun, kStop };
+    Lp<KM, MC> P;
+    P.m = m;
+    P.mu = mu;
+    P.inv_rho = 1.0 / rho;
+    P.k = P.n = 0;
+    int st = kIdle, status = 0, piv = 0, checks = 0, wi = 7;
+    int64_t t = 0;
+    for (;;) {
+        const unsigned long long running = __ballot(st == kRun);
+        if (running == 0 || __popcll(__ballot(st == kStop)) >= kLpBatch) {
+            if (st == kStop) {
+                bool fin = true;
+                if (status == 0 && checks < kLpChecks) {
+                    ++checks;
+                    P.refine(L, tid, cs);
+                    double d;
+                    fin = P.price(L, tid, cs, piv >= kBlandAfter, d) < 0;
+                }
+                if (fin) done(t, P.tstar(), status, P);
+                st = fin ? kIdle : kRun;
+            }
+            const unsigned long long need = __ballot(st == kIdle);
+            if (next < end && need) {
+                if (st == kIdle) {
+                    t = next + __popcll(need & ((1ull << lane) - 1ull));
+                    if (t < end && fetch(t, P)) {
+                        P.cold(L, tid, cs);
+                        piv = checks = status = 0;
+                        if constexpr (WARM) wi = warm(t, 0) >= 0 ? 0 : 7;
+                        st = kRun;
+                    }
+                }
+                next += __popcll(need);
+            }
+            if (__ballot(st == kRun) == 0) {
+                if (next >= end) break;
+                continue;
+            }
+        }
+        if (st == kRun) {
+            int e = -1;
+            double d = 0.0;
+            if constexpr (WARM) {
+                while (wi < 7) {
+                    const int c = warm(t, wi++);
+                    if (!P.basic(c)) {
+                        e = c;
+                        break;
+                    }
+                }
+            }
+            const bool forced = e >= 0;
+            if (!forced) {
+                e = P.price(L, tid, cs, piv >= kBlandAfter, d);
+                if (e < 0) st = kStop;
+                if (e >= 0 && piv >= max_pivots) {
+                    status = 1;
+                    st = kStop;
+                }
+            }
+            if (st == kRun) {
+                double a[7], al[7];
+                P.column(L, tid, cs, e, a);
+                if (WARM && forced) {
+                    d = P.cost(e);
+#pragma unroll
+                    for (int r = 0; r < 7; ++r) d = fma(-a[r], P.y[r], d);
+                }
+                P.solve(a, al);
+                const int lr = P.ratio(al);
+                if (lr >= 0) {
+                    P.pivot(lr, al, e, d);
+                    if (!forced) ++piv;
+                } else if (!forced) {
+                    status = 2;
+                    st = kStop;
+                }
+            }
+        }
+    }
+}
+
+// one LP per lane, every lane of the caller's own; warm[r][tid]: the column ids
+// in (see lp_wave), the final basis out
+template <int KM, int MC>
+__device__ inline double lp_lane(LpLds<KM> &L, int tid, int k, int m, double mu, double rho, int max_pivots,
+                                 const LpConst &cs, int &status, int (*warm)[256])
+{
+    Lp<KM, MC> P;
+    P.k = k;
+    P.m = m;
+    P.n = k * m;
+    P.mu = mu;
+    P.inv_rho = 1.0 / rho;
+    P.cold(L, tid, cs);
+    int piv = 0, checks = 0, wi = warm[0][tid] >= 0 ? 0 : 7;
+    status = 0;
+    for (;;) {
+        int e = -1;
+        double d = 0.0;
+        while (wi < 7 && e < 0) {
+            const int c = warm[wi++][tid];
+            if (!P.basic(c)) e = c;
+        }
+        const bool forced = e >= 0;
+        if (!forced) {
+            e = P.price(L, tid, cs, piv >= kBlandAfter, d);
+            if (e < 0) {
+                if (checks >= kLpChecks) break;
+                ++checks;
+                P.refine(L, tid, cs);
+                e = P.price(L, tid, cs, piv >= kBlandAfter, d);
+                if (e < 0) break;
+            }
+            if (piv >= max_pivots) {
+                status = 1;
+                break;
+            }
+        }
+        double a[7], al[7];
+        P.column(L, tid, cs, e, a);
+        if (forced) {
+            d = P.cost(e);
+#pragma unroll
+            for (int r = 0; r < 7; ++r) d = fma(-a[r], P.y[r], d);
+        }
+        P.solve(a, al);
+        const int lr = P.ratio(al);
+        if (lr >= 0) {
+            P.pivot(lr, al, e, d);
+            if (!forced) ++piv;
+        } else if (!forced) {
             status = 2;
             break;
         }
-        LG_LP_PIVOT(lr, al, e);
-        ++piv;
     }
-#undef LG_LP_PIVOT
-#undef LG_LP_COLD
-    double ts = 0.0;
 #pragma unroll
-    for (int r = 0; r < 7; ++r)
-        if (basis[r] >= n) ts += xB[r];
-    if constexpr (WARM) {
-#pragma unroll
-        for (int r = 0; r < 7; ++r) warm[r][tid] = basis[r];
-    }
-    status_out = status;
-    return ts;
+    for (int r = 0; r < 7; ++r) warm[r][tid] = P.basis[r];
+    return P.tstar();
 }
 
-// block bid of nb blocks (grid-stride); cd: contact data of each lane's set
-// in LDS, lane-contiguous: cd[6*i + c][tid]
+// waves of the nb blocks share n_work LPs in contiguous runs
+__device__ inline void lp_share(int64_t bid, int64_t nb, int64_t n_work, int64_t &next, int64_t &end)
+{
+    const int64_t w = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t per = (n_work + 4 * nb - 1) / (4 * nb);
+    next = min(n_work, w * per);
+    end = min(n_work, next + per);
+}
+
+// block bid of nb blocks: the verdicts of the sets of poses with at least k non-empty domains
 template <int KM, int MC = 0>
-__device__ __forceinline__ void verdict_sets(float (&cd)[KM * 6][256], int64_t bid, int64_t nb,
-                                             const float *__restrict__ pts, const float *__restrict__ nrm, int N,
-                                             const int32_t *__restrict__ set_pt, const int32_t *__restrict__ palm_pt,
+__device__ __forceinline__ void verdict_sets(LpLds<KM> &L, int64_t bid, int64_t nb, const float *__restrict__ pts,
+                                             const float *__restrict__ nrm, int N, const int32_t *__restrict__ set_pt,
+                                             const int32_t *__restrict__ palm_pt,
                                              const int32_t *__restrict__ valid_poses,
                                              const int32_t *__restrict__ n_valid_poses, int D, int k, int m, double mu,
                                              double rho, double eps, int max_pivots, const LpConst &cs,
                                              uint8_t *__restrict__ verdict, double *__restrict__ tstar)
 {
     const int tid = threadIdx.x;
-    const int64_t n_work = (int64_t)(*n_valid_poses) * D;
-    const int64_t stride = nb * 256;
-    // grid-stride over the sets of poses with at least k non-empty domains
-    for (int64_t t = bid * 256 + tid; t < n_work; t += stride) {
-        const int64_t g = valid_poses[t / D];
-        const int64_t sid = g * D + (t % D);
-        const int32_t *sp = set_pt + sid * k;
+    int64_t next, end;
+    lp_share(bid, nb, (int64_t)(*n_valid_poses) * D, next, end);
+    // n_poses * D < 2^31
+    auto set_of = [&](int64_t t) {
+        const uint32_t q = (uint32_t)t / (uint32_t)D;
+        return (int64_t)valid_poses[q] * D + ((uint32_t)t - q * (uint32_t)D);
+    };
+    auto fetch = [&](int64_t t, Lp<KM, MC> &P) {
+        const int64_t sid = set_of(t);
         // a palm contact (Sec. 5.1 static link) is one more, fixed, contact
-        const int pc = palm_pt ? palm_pt[g] : -1;
+        const int pc = palm_pt ? palm_pt[valid_poses[(uint32_t)t / (uint32_t)D]] : -1;
         const int kc = pc >= 0 ? k + 1 : k;
         bool valid = true;
         for (int i = 0; i < kc; ++i) {
-            const int idx = i < k ? sp[i] : pc;
+            const int idx = i < k ? set_pt[sid * k + i] : pc;
             valid &= idx >= 0 && idx < N;
-            const int ii = (idx >= 0 && idx < N) ? idx : 0;
-            cd[6 * i + 0][tid] = pts[ii];
-            cd[6 * i + 1][tid] = pts[N + ii];
-            cd[6 * i + 2][tid] = pts[2 * N + ii];
-            cd[6 * i + 3][tid] = nrm[ii];
-            cd[6 * i + 4][tid] = nrm[N + ii];
-            cd[6 * i + 5][tid] = nrm[2 * N + ii];
+            lp_load(L, tid, i, pts, nrm, N, (idx >= 0 && idx < N) ? idx : 0);
         }
         if (!valid) {
             verdict[sid] = 0;
             tstar[sid] = __builtin_nan("");
-            continue;
         }
-        int status = 0;
-        const double ts = lp_lane<KM, false, MC>(cd, tid, kc, m, mu, rho, max_pivots, cs, status);
-        verdict[sid] = (status == 0 && ts <= eps) ? 1 : 0;
-        tstar[sid] = status == 0 ? ts : __builtin_nan("");
-    }
+        P.k = kc;
+        P.n = kc * m;
+        return valid;
+    };
+    lp_wave<KM, MC, false>(
+        L, next, end, m, mu, rho, max_pivots, cs, fetch, [](int64_t, int) { return -1; },
+        [&](int64_t t, double ts, int status, const Lp<KM, MC> &) {
+            const int64_t sid = set_of(t);
+            verdict[sid] = (status == 0 && ts <= eps) ? 1 : 0;
+            tstar[sid] = status == 0 ? ts : __builtin_nan("");
+        });
 }
 
 template <int KM, int MC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_verdict_lane(const float *__restrict__ pts, const float *__restrict__ nrm, int N, const int32_t *__restrict__ set_pt,
                const int32_t *__restrict__ palm_pt, const int32_t *__restrict__ valid_poses,
                const int32_t *__restrict__ n_valid_poses, int D, int k, int m, double mu, double rho, double eps,
                int max_pivots, LpConst cs, uint8_t *__restrict__ verdict, double *__restrict__ tstar)
 {
-    __shared__ float cd[KM * 6][256];
-    verdict_sets<KM, MC>(cd, blockIdx.x, gridDim.x, pts, nrm, N, set_pt, palm_pt, valid_poses, n_valid_poses, D, k, m,
+    __shared__ LpLds<KM> L;
+    verdict_sets<KM, MC>(L, blockIdx.x, gridDim.x, pts, nrm, N, set_pt, palm_pt, valid_poses, n_valid_poses, D, k, m,
                          mu, rho, eps, max_pivots, cs, verdict, tstar);
 }
 
 template <int KM, int MC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_verdict_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx, const uint32_t *__restrict__ first,
                 int n)
 {
-    __shared__ float cd[KM * 6][256];
+    __shared__ LpLds<KM> L;
     const int j = batch_member(first, n, blockIdx.x);
     const ChunkDesc &c = d[idx[j]];
-    verdict_sets<KM, MC>(cd, blockIdx.x - first[j], first[j + 1] - first[j], c.pts, c.nrm, c.N, c.set_pt, nullptr,
+    verdict_sets<KM, MC>(L, blockIdx.x - first[j], first[j + 1] - first[j], c.pts, c.nrm, c.N, c.set_pt, nullptr,
                      c.valid_poses, c.n_valid_poses, c.D, c.k, c.m, c.mu, c.rho, c.eps, c.max_pivots, c.cs, c.verdict,
                      c.tstar);
 }
@@ -1088,7 +1268,7 @@ k_optimize(const float *__restrict__ pts, const float *__restrict__ nrm, int N, 
            uint32_t request_id, int64_t pose_offset, const int32_t *__restrict__ cands, int32_t *__restrict__ set_pt,
            uint8_t *__restrict__ verdict, double *__restrict__ tstar)
 {
-    __shared__ float cd[KM * 6][256];
+    __shared__ LpLds<KM> L;
     __shared__ int cur[KM][256];  // the set's current point indices (every lane of a group holds them)
     __shared__ int wbs[7][256];   // per lane: the warm basis of its LP in, its final basis out
     __shared__ int cbs[7][256];   // per lane: the current set's optimal basis (the last pick's)
@@ -1096,14 +1276,7 @@ k_optimize(const float *__restrict__ pts, const float *__restrict__ nrm, int N, 
     const int wbase = tid - lane;  // first thread of this wave
     const int64_t n_work = (int64_t)(*n_valid_poses) * D;
     const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / GS;
-    auto load = [&](int ci, int idx) {
-        cd[6 * ci + 0][tid] = pts[idx];
-        cd[6 * ci + 1][tid] = pts[N + idx];
-        cd[6 * ci + 2][tid] = pts[2 * N + idx];
-        cd[6 * ci + 3][tid] = nrm[idx];
-        cd[6 * ci + 4][tid] = nrm[N + idx];
-        cd[6 * ci + 5][tid] = nrm[2 * N + idx];
-    };
+    auto load = [&](int ci, int idx) { lp_load(L, tid, ci, pts, nrm, N, idx); };
     for (int64_t t = ((int64_t)blockIdx.x * blockDim.x + tid) / GS; t < n_work; t += groups) {
         const int64_t pg = valid_poses[t / D];
         const int d = (int)(t % D);
@@ -1141,7 +1314,7 @@ k_optimize(const float *__restrict__ pts, const float *__restrict__ nrm, int N, 
                 if (cand >= 0) {  // always, for a drawn set (its domains are non-empty)
                     load(i, cand);
                     int st = 0;
-                    Jc = lp_lane<KM, true, MC>(cd, tid, kc, m, mu, rho, max_pivots, cs, st, wbs);
+                    Jc = lp_lane<KM, MC>(L, tid, kc, m, mu, rho, max_pivots, cs, st, wbs);
                     if (st != 0) Jc = INFINITY;
                 }
             }
@@ -1170,31 +1343,18 @@ k_optimize(const float *__restrict__ pts, const float *__restrict__ nrm, int N, 
     }
 }
 
-// ---- Alg. 2 criteria with the slow LPs gathered into their own waves --------
+// ---- Alg. 2 criteria, a contact step's LPs over all sets ----------------------
 // k_optimize runs a contact step's candidate LPs side by side, so each wave
-// waits for the slowest of its 64 LPs at every step.  Most warm-started LPs
-// end within a pivot or two of the warm basis, but about a third need many
-// more.  With a workspace that holds a step's candidate results, each
-// contact step takes three launches instead: every candidate's LP stopped
-// after kOptEasyPivots simplex pivots (kOptColdPivots at a round's first
-// step, which has no warm basis) (k_opt_try); the LPs not finished by then
-// queued and solved again from the same start with the full pivot cap, in
-// waves of slow LPs only (k_opt_hard); then each set's pick (k_opt_pick).
-// A capped run is a prefix of the full run from the same start, so t*, the
-// final bases and the picks are those of k_optimize.  (Caps measured at c3,
-// search stage: 1, 2, 4, 8, 12, 16 warm pivots 119, 117, 112, 110, 113,
-// 117 ms with the cold step uncapped; with 8 warm, 10, 14, 20 cold pivots
-// 108.6, 107.5, 109.7 ms.)
-constexpr int kOptEasyPivots = 8;
-constexpr int kOptColdPivots = 14;
-
+// waits for the slowest of its 64 LPs at every step.  With a workspace that
+// holds a step's candidate results, each contact step takes two launches
+// instead: every candidate's LP, the lanes of a wave taking one after another
+// (k_opt_solve, see lp_wave), then each set's pick (k_opt_pick).  The LPs, their
+// starting bases and the picks are those of k_optimize.
 struct OptSplit {
     double *sJ;          // per set: criterion value of its last pick (INF before any)
     int32_t *sB;         // per set: 7 basis column ids of its last finite pick (-1: none yet)
     double *cJ;          // per candidate (set t, candidate j at t * n_inner + j): t*, INF if unsolved
     int32_t *cB;         // per candidate: the 7 column ids of its final basis
-    int32_t *queue;      // candidates whose LP needs more than kOptEasyPivots pivots
-    uint32_t *n_queue;   // queue length, one counter per contact step
 };
 
 // Set t of the sets of poses with non-empty domains: its set id and whether it
@@ -1216,106 +1376,47 @@ __device__ inline bool opt_set(int64_t t, const int32_t *__restrict__ valid_pose
     return drawn;
 }
 
-// LP of candidate j of set t at contact step i, from the set's current points
-// (its own column of cd), warm-started from the set's last pick's basis
-// (none at the round's first step); cap: the pivot cap of this run.
-template <int KM, int MC>
-__device__ inline double opt_cand_lp(float (&cd)[KM * 6][256], int (&wb)[7][256], int tid, int64_t t, int j, int i,
-                                     const float *__restrict__ pts, const float *__restrict__ nrm, int N,
-                                     const int32_t *__restrict__ valid_poses, const uint32_t *__restrict__ dom_count,
-                                     const int32_t *__restrict__ palm_pt, int F, int D, int k, int m, double mu,
-                                     double rho, int cap, const LpConst &cs, int n_inner, uint32_t seed_lo,
-                                     uint32_t seed_hi, uint32_t request_id, int64_t pose_offset,
-                                     const int32_t *__restrict__ cands, const int32_t *__restrict__ set_pt,
-                                     const OptSplit &os, int &st)
-{
-    st = 3;  // no LP (not a drawn set, or no candidate)
-    int64_t sid;
-    int pc;
-    if (!opt_set(t, valid_poses, dom_count, palm_pt, set_pt, N, F, D, k, seed_lo, seed_hi, request_id, pose_offset,
-                 sid, pc))
-        return INFINITY;
-    const int cand = cands[(t * k + i) * n_inner + j];
-    if (cand < 0) return INFINITY;
-    auto load = [&](int ci, int idx) {
-        cd[6 * ci + 0][tid] = pts[idx];
-        cd[6 * ci + 1][tid] = pts[N + idx];
-        cd[6 * ci + 2][tid] = pts[2 * N + idx];
-        cd[6 * ci + 3][tid] = nrm[idx];
-        cd[6 * ci + 4][tid] = nrm[N + idx];
-        cd[6 * ci + 5][tid] = nrm[2 * N + idx];
-    };
-    const int32_t *sp = set_pt + sid * k;
-    for (int c = 0; c < k; ++c) load(c, c == i ? cand : sp[c]);
-    if (pc >= 0) load(k, pc);
-#pragma unroll
-    for (int r = 0; r < 7; ++r) wb[r][tid] = i == 0 ? -1 : os.sB[t * 7 + r];
-    return lp_lane<KM, true, MC>(cd, tid, pc >= 0 ? k + 1 : k, m, mu, rho, cap, cs, st, wb);
-}
-
+// LPs of the candidates at contact step i, each from the set's current points,
+// warm-started from the set's last pick's basis (none at the round's first step)
 template <int KM, int MC>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_opt_try(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
-          const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
-          const uint32_t *__restrict__ dom_count, const int32_t *__restrict__ palm_pt, int F, int D, int k, int m,
-          double mu, double rho, int max_pivots, LpConst cs, int n_inner, int i, uint32_t seed_lo, uint32_t seed_hi,
-          uint32_t request_id, int64_t pose_offset, const int32_t *__restrict__ cands,
-          const int32_t *__restrict__ set_pt, OptSplit os)
+k_opt_solve(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
+            const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
+            const int32_t *__restrict__ palm_pt, int D, int k, int m, double mu, double rho, int max_pivots,
+            LpConst cs, int n_inner, int i, const int32_t *__restrict__ cands, const int32_t *__restrict__ set_pt,
+            OptSplit os)
 {
-    __shared__ float cd[KM * 6][256];
-    __shared__ int wb[7][256];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int64_t n_cand = (int64_t)(*n_valid_poses) * D * n_inner;
-    const int cap = min(max_pivots, i == 0 ? kOptColdPivots : kOptEasyPivots);
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + tid; g < n_cand; g += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t t = g / n_inner;
-        const int j = (int)(g - t * n_inner);
-        int st;
-        const double Jc = opt_cand_lp<KM, MC>(cd, wb, tid, t, j, i, pts, nrm, N, valid_poses, dom_count, palm_pt, F,
-                                              D, k, m, mu, rho, cap, cs, n_inner, seed_lo, seed_hi, request_id,
-                                              pose_offset, cands, set_pt, os, st);
-        const bool slow = st == 1 && cap < max_pivots;
-        if (!slow) {
-            os.cJ[g] = st == 0 ? Jc : INFINITY;
-#pragma unroll
-            for (int r = 0; r < 7; ++r) os.cB[g * 7 + r] = wb[r][tid];
-        }
-        // one queue reservation per wave
-        const unsigned long long sb = __ballot(slow);
-        if (sb) {
-            const int leader = __ffsll((long long)sb) - 1;
-            uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(os.n_queue + i, (uint32_t)__popcll(sb));
-            base = __shfl(base, leader, 64);
-            if (slow) os.queue[base + __popcll(sb & ((1ull << lane) - 1))] = (int32_t)g;
-        }
-    }
-}
-
-template <int KM, int MC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_opt_hard(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
-           const int32_t *__restrict__ valid_poses, const uint32_t *__restrict__ dom_count,
-           const int32_t *__restrict__ palm_pt, int F, int D, int k, int m, double mu, double rho, int max_pivots,
-           LpConst cs, int n_inner, int i, uint32_t seed_lo, uint32_t seed_hi, uint32_t request_id,
-           int64_t pose_offset, const int32_t *__restrict__ cands, const int32_t *__restrict__ set_pt, OptSplit os)
-{
-    __shared__ float cd[KM * 6][256];
+    __shared__ LpLds<KM> L;
     __shared__ int wb[7][256];
     const int tid = threadIdx.x;
-    const int64_t n = os.n_queue[i];
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + tid; q < n; q += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t g = os.queue[q];
-        const int64_t t = g / n_inner;
+    int64_t next, end;
+    lp_share(blockIdx.x, gridDim.x, (int64_t)(*n_valid_poses) * D * n_inner, next, end);
+    auto fetch = [&](int64_t g, Lp<KM, MC> &P) {
+        const int64_t t = (uint32_t)g / (uint32_t)n_inner;  // candidate ids are below 2^31
         const int j = (int)(g - t * n_inner);
-        int st;
-        const double Jc = opt_cand_lp<KM, MC>(cd, wb, tid, t, j, i, pts, nrm, N, valid_poses, dom_count, palm_pt, F,
-                                              D, k, m, mu, rho, max_pivots, cs, n_inner, seed_lo, seed_hi,
-                                              request_id, pose_offset, cands, set_pt, os, st);
-        os.cJ[g] = st == 0 ? Jc : INFINITY;
+        const int cand = cands[(t * k + i) * n_inner + j];
+        if (cand < 0) {  // not a drawn set (k_opt_project)
+            os.cJ[g] = INFINITY;
+            return false;
+        }
+        const uint32_t q = (uint32_t)t / (uint32_t)D;
+        const int64_t pg = valid_poses[q], sid = pg * D + ((uint32_t)t - q * (uint32_t)D);
+        const int pc = palm_pt ? palm_pt[pg] : -1;
+        for (int c = 0; c < k; ++c) lp_load(L, tid, c, pts, nrm, N, c == i ? cand : set_pt[sid * k + c]);
+        if (pc >= 0) lp_load(L, tid, k, pts, nrm, N, pc);
 #pragma unroll
-        for (int r = 0; r < 7; ++r) os.cB[g * 7 + r] = wb[r][tid];
-    }
+        for (int r = 0; r < 7; ++r) wb[r][tid] = i == 0 ? -1 : os.sB[t * 7 + r];
+        P.k = pc >= 0 ? k + 1 : k;
+        P.n = P.k * m;
+        return true;
+    };
+    lp_wave<KM, MC, true>(
+        L, next, end, m, mu, rho, max_pivots, cs, fetch, [&](int64_t, int r) { return wb[r][tid]; },
+        [&](int64_t g, double ts, int status, const Lp<KM, MC> &P) {
+            os.cJ[g] = status == 0 ? ts : INFINITY;
+#pragma unroll
+            for (int r = 0; r < 7; ++r) os.cB[g * 7 + r] = P.basis[r];
+        });
 }
 
 // Each set's pick at contact step i: the lowest candidate within kOptTau of
@@ -1702,7 +1803,7 @@ struct SearchWs {
     uint32_t *cell_count, *cell_start;
     float4 *cell_pts;
     int32_t *cands;
-    OptSplit split;   // arrays of the gathered-slow-LP criteria (null when not laid out)
+    OptSplit split;   // per-candidate arrays of the criteria (null when not laid out)
     size_t bytes;
 };
 
@@ -1752,21 +1853,21 @@ static SearchWs search_ws(void *base, int64_t n_points, int64_t n_poses, int64_t
             w.split.sB = reinterpret_cast<int32_t *>(take((size_t)n_sets * 28));
             w.split.cJ = reinterpret_cast<double *>(take(nc_ * 8));
             w.split.cB = reinterpret_cast<int32_t *>(take(nc_ * 28));
-            w.split.queue = reinterpret_cast<int32_t *>(take(nc_ * 4));
-            w.split.n_queue = reinterpret_cast<uint32_t *>(take((size_t)std::max<int64_t>(k, 1) * 4));
+            take(nc_ * 4);  // not used: the size asked for (40 B per candidate) is part of the interface
+            take((size_t)std::max<int64_t>(k, 1) * 4);
         }
     }
     w.bytes = off + 256;
     return w;
 }
 
-// Alg. 2 criteria with the slow LPs gathered need candidate ids below 2^31.
+// Alg. 2 criteria with per-candidate results need candidate ids below 2^31.
 static bool split_fits(int64_t n_poses, int64_t draws, const lg_search_params *p)
 {
     return p->opt_outer > 0 && n_poses * draws * p->opt_inner < 0x7fffffffLL;
 }
 
-// Workspace of the search: with split, the arrays of the gathered-slow-LP
+// Workspace of the search: with split, the per-candidate arrays of the
 // criteria too (what lg_search_workspace_bytes asks for); without, the least
 // a search runs in (Alg. 2 then runs its criteria in one launch per round).
 static size_t search_ws_bytes(int32_t n_points, int32_t n_poses, const lg_search_params *p, bool split)
@@ -1781,8 +1882,8 @@ size_t lg_search_workspace_bytes(int32_t n_points, int32_t n_poses, const lg_sea
     return search_ws_bytes(n_points, n_poses, p, true);
 }
 
-// One round of Alg. 2 criteria with the slow LPs gathered: per contact step
-// the capped LPs of every candidate, the queued slow ones, the picks.
+// One round of Alg. 2 criteria with per-candidate results: per contact step
+// the LPs of every candidate, then the picks.
 static lg_status opt_split_round(const float *pts, const float *nrm, int n_points, const SearchWs &ws,
                                  const uint32_t *dom_count, const int32_t *palm, int F, const lg_search_params *p,
                                  int kk, bool m8, const LpConst &cs, dim3 sgrid, dim3 cgrid, bool last,
@@ -1790,20 +1891,11 @@ static lg_status opt_split_round(const float *pts, const float *nrm, int n_point
 {
     const uint32_t slo = (uint32_t)p->seed, shi = (uint32_t)(p->seed >> 32);
     const double mu = p->mu, rho = p->moment_scale;
-    // queue counters cleared by a kernel, not a memset node (the stream may be captured)
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, s, ws.split.n_queue, (int64_t)p->k, 0u);
     for (int i = 0; i < p->k; ++i) {
 #define LG_SPLIT_M(KM, MC)                                                                                       \
-    do {                                                                                                         \
-        hipLaunchKernelGGL((k_opt_try<KM, MC>), cgrid, dim3(256), 0, s, pts, nrm, n_points, ws.valid_poses,     \
-                           ws.n_valid_poses, dom_count, palm, F, p->draws, p->k, p->m_edges, mu, rho,           \
-                           p->max_pivots, cs, p->opt_inner, i, slo, shi, p->request_id, p->pose_offset,          \
-                           ws.cands, set_pt, ws.split);                                                          \
-        hipLaunchKernelGGL((k_opt_hard<KM, MC>), cgrid, dim3(256), 0, s, pts, nrm, n_points, ws.valid_poses,    \
-                           dom_count, palm, F, p->draws, p->k, p->m_edges, mu, rho, p->max_pivots, cs,           \
-                           p->opt_inner, i, slo, shi, p->request_id, p->pose_offset, ws.cands, set_pt,           \
-                           ws.split);                                                                            \
-    } while (0)
+    hipLaunchKernelGGL((k_opt_solve<KM, MC>), cgrid, dim3(256), 0, s, pts, nrm, n_points, ws.valid_poses,       \
+                       ws.n_valid_poses, palm, p->draws, p->k, p->m_edges, mu, rho, p->max_pivots, cs,           \
+                       p->opt_inner, i, ws.cands, set_pt, ws.split)
 #define LG_SPLIT(KM) if (m8) LG_SPLIT_M(KM, 8); else LG_SPLIT_M(KM, 0)
         if (kk <= 3) { LG_SPLIT(3); } else if (kk <= 4) { LG_SPLIT(4); } else if (kk <= 5) { LG_SPLIT(5); }
         else if (kk <= 6) { LG_SPLIT(6); } else { LG_SPLIT(8); }
@@ -1830,9 +1922,15 @@ LpConst lg::lp_const(int m)
     return cs;
 }
 
+// Blocks of an LP launch: no more than are resident at once (two per CU: two
+// waves per SIMD), so that each lane takes several LPs; a small launch spreads
+// over every SIMD, down to a few LPs per wave (its time is that of its slowest
+// LP, and a wave waits for the slowest of its own): 4,096 sets 55 us with 16
+// sets per block, 75 us with 64; 1.2 M LPs 0.67 ms with two blocks per CU, 0.68
+// with four.
 uint32_t lg::verdict_blocks(int64_t n_sets, int n_cu)
 {
-    return (uint32_t)std::max<int64_t>(1, std::min<int64_t>((n_sets + 255) / 256, (int64_t)n_cu * 8));
+    return (uint32_t)std::max<int64_t>(1, std::min<int64_t>((n_sets + 15) / 16, (int64_t)n_cu * 2));
 }
 
 void lg::chunk_workspace(void *ws, int64_t n_points, int64_t n_poses, int64_t draws, ChunkDesc &c)
@@ -1879,7 +1977,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
     if (lds > 48 * 1024) return fail(LG_EUNSUPPORTED, "too many points for the draw rank structure");
     hipStream_t s = as_stream(stream);
     const bool opt = p->opt_outer > 0;
-    // Alg. 2 criteria with the slow LPs gathered when the workspace holds their arrays
+    // Alg. 2 criteria with per-candidate results when the workspace holds their arrays
     const bool split = opt && split_fits(n_poses, p->draws, p) &&
                        workspace_bytes >= search_ws_bytes(n_points, n_poses, p, true);
     const SearchWs ws = search_ws(workspace, n_points, n_poses, p->draws, opt, p->k, opt ? p->opt_inner : 0, split);
@@ -1931,9 +2029,8 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
             1, std::min<int64_t>((n_sets * gs + 255) / 256, (int64_t)n_cu * 8)));
         const dim3 pgrid((unsigned)std::max<int64_t>(
             1, std::min<int64_t>((n_sets * p->k * p->opt_inner + 255) / 256, (int64_t)n_cu * 32)));
-        // grid-stride grids of the gathered-slow-LP criteria (candidates; sets)
-        const dim3 cgrid((unsigned)std::max<int64_t>(
-            1, std::min<int64_t>((n_sets * p->opt_inner + 255) / 256, (int64_t)n_cu * 8)));
+        // grids of the per-candidate criteria (candidates; sets)
+        const dim3 cgrid(verdict_blocks(n_sets * p->opt_inner, n_cu));
         const dim3 sgrid((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_sets + 255) / 256, (int64_t)n_cu * 8)));
 #define LG_OPT_M(KM, GS, MC)                                                                                     \
     hipLaunchKernelGGL((k_optimize<KM, GS, MC>), ogrid, dim3(256), 0, s, pts, nrm, n_points, ws.valid_poses,       \
@@ -1967,7 +2064,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
 #undef LG_OPT
 #undef LG_OPT_M
         LG_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_relink, lgrid, dim3(256), 0, s, H, field->d_bits, pts, nrm, n_points, poses,
+        hipLaunchKernelGGL(k_relink, sgrid, dim3(256), 0, s, H, field->d_bits, pts, nrm, n_points, poses,
                            ws.valid_poses, ws.n_valid_poses, dom_count, p->draws, p->k, (uint32_t)p->seed,
                            (uint32_t)(p->seed >> 32), p->request_id, p->pose_offset, set_pt, set_link);
     }
@@ -2083,7 +2180,7 @@ lg_status lg_search_extend(const lg_field *field, const float *pts, const float 
     int dev = 0, n_cu = 0;
     LG_HIP(hipGetDevice(&dev));
     LG_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    const dim3 lgrid((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_sets + 255) / 256, (int64_t)n_cu * 8)));
+    const dim3 lgrid(verdict_blocks(n_sets, n_cu));
     const bool m8 = p->m_edges == 8;
 #define LG_VERDICT2_M(KM, MC)                                                                                   \
     hipLaunchKernelGGL((k_verdict_lane<KM, MC>), lgrid, dim3(256), 0, s, pts, nrm, n_points, set_pt2, nullptr,    \
