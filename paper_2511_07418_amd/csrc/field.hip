@@ -85,6 +85,7 @@ void free_field(lg_field *f)
     (void)hipFree(f->d_bits);
     (void)hipFree(f->d_merged);
     (void)hipFree(f->d_wit);
+    (void)hipFree(f->d_cull);
     (void)hipSetDevice(cur);
     delete f;
 }
@@ -291,6 +292,9 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
     if (e == hipSuccess) e = hipMalloc(&f->d_merged, merged_bytes);
     if (e == hipSuccess) e = hipMemset(f->d_bits, 0, bits_bytes);
     if (e == hipSuccess) e = hipMemset(f->d_merged, 0, merged_bytes);
+    H.cull_row = (G + 31) / 32;
+    const size_t cull_bytes = (size_t)(kCullLevels + 1) * F * G * G * H.cull_row * 4;
+    if (e == hipSuccess) e = hipMalloc(&f->d_cull, cull_bytes);
     size_t wit_bytes = 0;
     if (e == hipSuccess && p->keep_witness) {
         wit_bytes = (size_t)J * G3 * B * 4;
@@ -307,7 +311,7 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
         free_field(f);
         return st;
     }
-    f->device_bytes = n_all * 4 + (J + PC) * 4 + bits_bytes + merged_bytes + wit_bytes;
+    f->device_bytes = n_all * 4 + (J + PC) * 4 + bits_bytes + merged_bytes + wit_bytes + cull_bytes;
     float *base = f->d_params;
     H.origin = base;
     base += n_origin;
@@ -329,6 +333,7 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
     base += n_pc;
     H.bin_lut = reinterpret_cast<const uint32_t *>(base);
     H.axis_samples = f->d_axis_samples;
+    H.cull = f->d_cull;
     H.n_palm_surf = PS;
     H.n_palm_caps = PC;
     *out = f;
@@ -428,6 +433,47 @@ __global__ void k_field_merge(DevHand H, const uint32_t *__restrict__ bits, uint
     }
 }
 
+// Occupied voxels of the merged tables, one bit per voxel: thread per 32 voxels of a row.
+__global__ void k_occupancy(DevHand H, const uint32_t *__restrict__ merged, uint32_t *__restrict__ occ)
+{
+    const int G = H.G, row = H.cull_row;
+    const int64_t G3 = (int64_t)G * G * G, n = (int64_t)G * G * row;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int f = blockIdx.y, w = (int)(i % row);
+    const uint32_t iy = (uint32_t)(i / row % G), iz = (uint32_t)(i / row / G);
+    uint32_t bits = 0;
+    for (uint32_t b = 0; b < 32u && 32u * w + b < (uint32_t)G; ++b) {
+        const uint32_t v = brick_word(32u * w + b, iy, iz, (uint32_t)(G / 4));
+        uint32_t any = 0;
+        for (int q = 0; q < H.W; ++q) any |= merged[((int64_t)f * H.W + q) * G3 + v];
+        bits |= (any != 0u ? 1u : 0u) << b;
+    }
+    occ[f * n + i] = bits;
+}
+
+// src dilated by d <= 4 voxels along each axis (box dilations compose, so each
+// level comes from the one before): OR of (2d + 1)^2 rows, then along the row.
+__global__ void k_dilate(int F, int G, int row, int d, const uint32_t *__restrict__ src, uint32_t *__restrict__ dst)
+{
+    const int64_t n = (int64_t)G * G * row;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int f = blockIdx.y, w = (int)(i % row), iy = (int)(i / row % G), iz = (int)(i / row / G);
+    const uint32_t *s = src + f * n;
+    uint32_t a = 0, lo = 0, hi = 0;  // the word, its lower and its upper neighbour
+    for (int z = max(0, iz - d); z <= min(G - 1, iz + d); ++z)
+        for (int y = max(0, iy - d); y <= min(G - 1, iy + d); ++y) {
+            const uint32_t *r = s + ((int64_t)z * G + y) * row;
+            a |= r[w];
+            if (w > 0) lo |= r[w - 1];
+            if (w + 1 < row) hi |= r[w + 1];
+        }
+    uint32_t o = a;
+    for (int k = 1; k <= d; ++k) o |= (a << k) | (lo >> (32 - k)) | (a >> k) | (hi << (32 - k));
+    dst[f * n + i] = o;
+}
+
 __global__ void k_popcount(const uint32_t *__restrict__ w, int64_t n, unsigned long long *__restrict__ out)
 {
     unsigned long long c = 0;
@@ -443,6 +489,18 @@ static lg_status merge_and_count(lg_field *f, hipStream_t st)
     const int64_t G3W = (int64_t)H.G * H.G * H.G * H.W;
     dim3 grid((unsigned)std::min<int64_t>((G3W + 255) / 256, 4096), H.F);
     hipLaunchKernelGGL(k_field_merge, grid, dim3(256), 0, st, H, f->d_bits, f->d_merged);
+    LG_HIP(hipGetLastError());
+    // the voxels' occupancy and its dilations, for the query's culling
+    const int64_t n_row = (int64_t)H.G * H.G * H.cull_row;
+    const dim3 cgrid((unsigned)((n_row + 255) / 256), H.F);
+    uint32_t *src = f->d_cull + (int64_t)kCullLevels * H.F * n_row;
+    hipLaunchKernelGGL(k_occupancy, cgrid, dim3(256), 0, st, H, f->d_merged, src);
+    for (int l = 0; l < kCullLevels; ++l) {
+        uint32_t *dst = f->d_cull + (int64_t)l * H.F * n_row;
+        hipLaunchKernelGGL(k_dilate, cgrid, dim3(256), 0, st, H.F, H.G, H.cull_row,
+                           cull_reach(l) - (l ? cull_reach(l - 1) : 0), src, dst);
+        src = dst;
+    }
     LG_HIP(hipGetLastError());
     unsigned long long *d_cnt = nullptr;
     LG_HIP(hipMalloc(&d_cnt, sizeof(unsigned long long)));

@@ -22,6 +22,7 @@ constexpr int kMaxBins = 64;
 constexpr uint32_t kPurposeJoint = 1u;
 constexpr uint32_t kPurposeDraw = 3u;
 constexpr int32_t kNoWitness = 0x7fffffff;
+constexpr int kCullLevels = 8;  // dilations of a finger's occupied voxels (cull_reach)
 constexpr int kLutRes = 28;  // cube-map cells per face edge of the bin table (18.4 KiB in LDS)
 
 // Device-side description of a hand and its field window (kernel argument).
@@ -44,6 +45,9 @@ struct DevHand {
     int n_palm_surf, n_palm_caps; // static link (palm): contact vectors and capsules, base frame
     const float *palm_surf;       // [n_palm_surf][6]
     const float *palm_caps;       // [n_palm_caps][7]
+    const uint32_t *cull;         // [kCullLevels][F][G][G][cull_row] bits: voxels within cull_reach(level) of an
+                                  // occupied one of the finger's window (per axis), one bit per x
+    int cull_row;                 // words of a row: ceil(G / 32)
     int finger_first[kMaxFingers];
     int finger_dof[kMaxFingers];
     // Lattice form of the windows (lat != 0): every finger's window has the
@@ -79,6 +83,7 @@ struct lg_field {
     uint32_t *d_bits = nullptr;    // per-link tables [J][G^3][W]
     uint32_t *d_merged = nullptr;  // per-finger OR of its links [F][G^3][W]
     int32_t *d_wit = nullptr;      // [J][G^3][B], kNoWitness = none
+    uint32_t *d_cull = nullptr;    // DevHand::cull, after it the undilated occupancy
 };
 
 namespace lg {
@@ -281,6 +286,13 @@ __device__ inline uint32_t brick_word_u24(uint32_t ix, uint32_t iy, uint32_t iz,
 {
     const uint32_t blk = mad_u24(mad_u24(iz >> 2, GB, iy >> 2), GB, ix >> 2);
     return (blk << 6) | ((iz & 3u) << 4) | ((iy & 3u) << 2) | (ix & 3u);
+}
+
+// Voxels a level of DevHand::cull is dilated by: a point set within cull_reach
+// voxels of a voxel (per axis) meets no table entry where the level's bit is 0.
+__host__ __device__ inline int cull_reach(int level)
+{
+    return level < 4 ? level + 1 : level == 4 ? 6 : level == 5 ? 8 : level == 6 ? 12 : 16;
 }
 
 // Voxel of object point p in finger f's window under pose P (-1 outside):

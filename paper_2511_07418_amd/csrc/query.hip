@@ -19,8 +19,14 @@
 // With chunk bounds (a bounding sphere per 64 consecutive points, a one-level
 // bounding-volume hierarchy over the object; tight when the points are in
 // Morton order), a (chunk, finger) pair whose sphere misses the finger's
-// window is skipped: its 64 domain bits are zero without a lookup, and a
-// chunk that misses every window is not loaded at all.
+// window, or every occupied voxel of it, is skipped: its 64 domain bits are
+// zero without a lookup, and a chunk that no finger keeps is not loaded at all.
+//
+// What bounds it: VALU issue (65,536 poses x 65,536 points, 22 joints: 5.6 G wave
+// instructions in 8.9 ms; 8.0 G in 12.0 ms before the culling by voxels, the bin
+// index in float arithmetic, the in-brick word by three multiply-adds and the
+// scalar chunk bookkeeping).  About 110 instructions per kept chunk: 9 for the
+// direction, 45 for its bin, 30 for the cell and word, 9 per kept finger.
 #include <math.h>
 
 #include <algorithm>
@@ -33,6 +39,7 @@ namespace lg {
 
 constexpr int kQueryThreads = 256;
 constexpr int kQueryWaves = kQueryThreads / 64;
+constexpr int kQueryMaxThreads = 1024;
 constexpr float kCullMargin = 1e-3f;  // voxels added to a chunk's radius (float rounding is ~1e-4)
 
 // the LLVM writelane intrinsic: lane `lane` (uniform) of v replaced by the uniform x
@@ -40,6 +47,17 @@ extern "C" __device__ int lg_writelane(int x, int lane, int v) __asm("llvm.amdgc
 __device__ inline uint32_t write_lane(uint32_t v, uint32_t x, int lane)
 {
     return (uint32_t)lg_writelane((int)x, lane, (int)v);
+}
+
+// Chunks a wave takes at a time: 32 (full 256-byte stores) when that gives each
+// wave of the block two or more units, else fewer, so that no wave is idle (2,048
+// points are one unit of 32: three of four waves had no work).
+__host__ __device__ inline int query_unit(int N, int waves)
+{
+    const int nchunks = (N + 63) >> 6;
+    int uc = 32;
+    while (uc > 4 && nchunks < 2 * uc * waves) uc >>= 1;
+    return uc;
 }
 
 // Bounding sphere (centre of the box, largest distance) of each chunk of 64
@@ -66,49 +84,69 @@ k_chunk_bounds(const float *__restrict__ pts, int N, float4 *__restrict__ bounds
     if (lane == 0) bounds[chunk] = make_float4(cx, cy, cz, fmaf(r, 1e-5f, r + 1e-7f));
 }
 
-// skip[f] bit j: chunk blk * 32 + j cannot reach finger f's window (all 0
-// without bounds); returns the chunks that reach no window.  Lane l tests
-// chunk l % 32 against finger f0 + l / 32, two fingers per ballot: the distance
-// from the sphere's centre (voxel coordinates of map aff[LAT ? 0 : f]) to the
-// finger's window box [lo, lo + G]^3 against its radius; lo = G for a
-// finger's own (biased) map, lat_o[f] in lattice coordinates.
+// Largest stretch of an affine map (an upper bound of its 2-norm, equal to it
+// for a scaled rotation): a sphere of radius r maps into one of r * map_stretch.
+__device__ inline float map_stretch(const Affine &a)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        float t = 0.f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            t += fabsf(fmaf(a.m[4 * r], a.m[4 * c], fmaf(a.m[4 * r + 1], a.m[4 * c + 1], a.m[4 * r + 2] * a.m[4 * c + 2])));
+        s = fmaxf(s, t);
+    }
+    return sqrtf(s);
+}
+
+// keep[f] bit j: chunk c0 + j (j < 8, below c_end) may hold a domain point of
+// finger f; returns the union.  Without bounds every chunk may.  Lane l tests
+// chunk c0 + l % 8 against finger l / 8: the distance from the sphere's centre
+// (voxel coordinates of map aff[LAT ? 0 : f]) to the finger's window box
+// [lo, lo + G]^3 against its radius (win[f] = lo and the map's stretch; lo = G for
+// a finger's own, biased, map, lat_o[f] in lattice coordinates), then the window's occupied voxels: with the
+// centre moved into the window, every voxel a point of the chunk can fall in is
+// within ceil(radius) of the centre's per axis, so the bit of a dilation that
+// reaches as far decides.  Of the (chunk, finger) pairs whose sphere meets the
+// window, 40-70 % meet no occupied voxel (65,536 points, 22 joints: 58 % of all
+// pairs meet a window, 23 % an occupied voxel, 10 % hold a domain point).
 template <int FM, bool LAT>
-__device__ inline uint32_t block_skip(const float4 *__restrict__ bounds, const Affine *aff, const DevHand &H,
-                                      int blk, int nchunks, int lane, uint32_t (&skip)[FM])
+__device__ inline uint32_t group_keep(const float4 *__restrict__ bounds, const Affine *aff, const float4 *win,
+                                      const DevHand &H, int c0, int c_end, int lane, uint32_t (&keep)[FM])
 {
     const int F = H.F, G = H.G;
-#pragma unroll
-    for (int f = 0; f < FM; ++f) skip[f] = 0u;
-    if (!bounds) return 0u;
-#pragma unroll
-    for (int f0 = 0; f0 < FM; f0 += 2) {
-        if (f0 >= F) break;
-        const int f = min(f0 + (lane >> 5), F - 1);
-        const int ch = blk * 32 + (lane & 31);
-        bool out = true;
-        if (ch < nchunks) {
-            const float4 sb = bounds[ch];
-            const Affine &a = aff[LAT ? 0 : f];
-            const float ux = fmaf(a.m[0], sb.x, fmaf(a.m[1], sb.y, fmaf(a.m[2], sb.z, a.m[3])));
-            const float uy = fmaf(a.m[4], sb.x, fmaf(a.m[5], sb.y, fmaf(a.m[6], sb.z, a.m[7])));
-            const float uz = fmaf(a.m[8], sb.x, fmaf(a.m[9], sb.y, fmaf(a.m[10], sb.z, a.m[11])));
-            const float lx = LAT ? (float)H.lat_o[f][0] : (float)G, ly = LAT ? (float)H.lat_o[f][1] : (float)G,
-                        lz = LAT ? (float)H.lat_o[f][2] : (float)G;
-            const float dx = fmaxf(fmaxf(lx - ux, ux - (lx + G)), 0.f);
-            const float dy = fmaxf(fmaxf(ly - uy, uy - (ly + G)), 0.f);
-            const float dz = fmaxf(fmaxf(lz - uz, uz - (lz + G)), 0.f);
-            const float rv = fmaf(sb.w, H.inv_h, kCullMargin);
-            out = fmaf(dx, dx, fmaf(dy, dy, dz * dz)) > rv * rv;
+    const int f = lane >> 3, ch = c0 + (lane & 7);
+    bool in = f < F && ch < c_end;
+    if (bounds && in) {
+        const float4 sb = bounds[ch];
+        const Affine &a = aff[LAT ? 0 : f];
+        const float4 o = win[f];
+        // window coordinates
+        const float ux = fmaf(a.m[0], sb.x, fmaf(a.m[1], sb.y, fmaf(a.m[2], sb.z, a.m[3]))) - o.x;
+        const float uy = fmaf(a.m[4], sb.x, fmaf(a.m[5], sb.y, fmaf(a.m[6], sb.z, a.m[7]))) - o.y;
+        const float uz = fmaf(a.m[8], sb.x, fmaf(a.m[9], sb.y, fmaf(a.m[10], sb.z, a.m[11]))) - o.z;
+        const float dx = fmaxf(fmaxf(-ux, ux - G), 0.f);
+        const float dy = fmaxf(fmaxf(-uy, uy - G), 0.f);
+        const float dz = fmaxf(fmaxf(-uz, uz - G), 0.f);
+        const float rv = fmaf(sb.w, o.w, kCullMargin);
+        in = !(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) > rv * rv);
+        if (in && rv <= (float)cull_reach(kCullLevels - 1)) {
+            // the first level that reaches rv
+            const int l = rv <= 4.f ? max((int)ceilf(rv), 1) - 1 : rv <= 6.f ? 4 : rv <= 8.f ? 5 : rv <= 12.f ? 6 : 7;
+            const int ix = min(max((int)ux, 0), G - 1), iy = min(max((int)uy, 0), G - 1), iz = min(max((int)uz, 0), G - 1);
+            const uint32_t w = H.cull[(uint32_t)((((l * F + f) * G + iz) * G + iy) * H.cull_row + (ix >> 5))];
+            in = (w >> (ix & 31)) & 1u;
         }
-        const unsigned long long m = __ballot(out);
-        skip[f0] = (uint32_t)m;
-        if (f0 + 1 < FM) skip[f0 + 1] = (uint32_t)(m >> 32);
     }
-    uint32_t all = ~0u;
+    const unsigned long long m = __ballot(in);
+    uint32_t any = 0u;
 #pragma unroll
-    for (int f = 0; f < FM; ++f)
-        if (f < F) all &= skip[f];
-    return all;
+    for (int q = 0; q < FM; ++q) {
+        keep[q] = (uint32_t)(m >> (8 * q)) & 0xffu;  // fingers past F were not tested: 0
+        any |= keep[q];
+    }
+    return any;
 }
 
 // argmax_b <d, c_b> (ties to the lowest b, as nearest_bin) through the
@@ -122,16 +160,14 @@ __device__ inline int nearest_bin_lut4(const uint32_t *lut, const float4 *c4, in
     // face and face coordinates by the cube-map instructions (the table is
     // built in their convention): ma = 2 x the major component, so
     // (sc / |major| + 1) R / 2 = sc R / |ma| + R / 2
-    const int face = (int)__builtin_amdgcn_cubeid(dx, dy, dz);
     const float sc = __builtin_amdgcn_cubesc(dx, dy, dz), tc = __builtin_amdgcn_cubetc(dx, dy, dz);
     const float sf = (float)kLutRes * __builtin_amdgcn_rcpf(fabsf(__builtin_amdgcn_cubema(dx, dy, dz)));
-    const int is = min(max((int)fmaf(sc, sf, 0.5f * kLutRes), 0), kLutRes - 1);
-    const int it = min(max((int)fmaf(tc, sf, 0.5f * kLutRes), 0), kLutRes - 1);
-    // byte offset of the entry; the row by a 24-bit multiply (full rate; the
-    // compiler would otherwise pick the quarter-rate 32-bit multiply)
-    uint32_t row;
-    asm("v_mul_u32_u24 %0, %1, %2" : "=v"(row) : "n"(4 * kLutRes), "v"((uint32_t)(face * kLutRes + it)));
-    const uint32_t boff = row + ((uint32_t)is << 2);
+    // the entry's index in float arithmetic (whole numbers below 2^13, exact):
+    // cells clamped to the face, a NaN to cell 0
+    const float is = __builtin_amdgcn_fmed3f(floorf(fmaf(sc, sf, 0.5f * kLutRes)), 0.0f, (float)(kLutRes - 1));
+    const float it = __builtin_amdgcn_fmed3f(floorf(fmaf(tc, sf, 0.5f * kLutRes)), 0.0f, (float)(kLutRes - 1));
+    const float id = fmaf(__builtin_amdgcn_cubeid(dx, dy, dz), (float)(kLutRes * kLutRes), fmaf(it, (float)kLutRes, is));
+    const uint32_t boff = (uint32_t)id << 2;
     const uint32_t e = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(lut) + boff);
     float best = -3.0e38f;
     int bi = 0;
@@ -168,28 +204,32 @@ struct QueryLds {
     float4 cb4[kMaxBins];
     uint32_t lut[6 * kLutRes * kLutRes];
     Affine aff[LAT ? 1 : FM];
-    uint32_t cnt[FM][kQueryWaves];
+    float4 win[FM];  // see group_keep
 };
 
-// the domains of pose g (one block)
+// the domains of pose g (one block of any number of waves up to 16)
 template <int W, int FM, bool LAT>
 __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &H, const uint32_t *__restrict__ merged,
                                            const float *__restrict__ pts, const float *__restrict__ nrm, int N,
                                            const float *__restrict__ poses, const float4 *__restrict__ bounds,
-                                           uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count, int g)
+                                           uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count, int uc,
+                                           int g)
 {
     float4 *cb4 = L.cb4;
     uint32_t *lut = L.lut;
     Affine *aff = L.aff;
-    auto &cnt = L.cnt;
     const float *pose = poses + 12 * (int64_t)g;
-    for (int i = threadIdx.x; i < H.B; i += kQueryThreads)
+    for (int i = threadIdx.x; i < H.B; i += blockDim.x)
         cb4[i] = make_float4(H.bin_c[3 * i], H.bin_c[3 * i + 1], H.bin_c[3 * i + 2], 0.0f);
-    for (int i = threadIdx.x; i < 6 * kLutRes * kLutRes; i += kQueryThreads) lut[i] = H.bin_lut[i];
-    if (LAT) {
-        if (threadIdx.x == 0) aff[0] = lattice_affine(H, pose);
-    } else if (threadIdx.x < H.F) {
-        aff[threadIdx.x] = finger_affine(H, pose, threadIdx.x);
+    for (int i = threadIdx.x; i < 6 * kLutRes * kLutRes; i += blockDim.x) lut[i] = H.bin_lut[i];
+    if (threadIdx.x < (LAT ? 1 : H.F)) {
+        aff[threadIdx.x] = LAT ? lattice_affine(H, pose) : finger_affine(H, pose, threadIdx.x);
+    }
+    if (threadIdx.x < H.F) {
+        const int f = threadIdx.x;
+        const float sc = map_stretch(LAT ? lattice_affine(H, pose) : finger_affine(H, pose, f));
+        L.win[f] = LAT ? make_float4((float)H.lat_o[f][0], (float)H.lat_o[f][1], (float)H.lat_o[f][2], sc)
+                       : make_float4((float)H.G, (float)H.G, (float)H.G, sc);
     }
     __syncthreads();
     // the wave index is uniform: in a scalar register, the block and chunk
@@ -214,21 +254,21 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
     uint32_t c[FM];
 #pragma unroll
     for (int f = 0; f < FM; ++f) c[f] = 0;
-    // Waves take blocks of 32 consecutive chunks (2,048 points, a compact
-    // patch of the Morton-ordered object) in turn.  The 64 ballot words of a
-    // block stay in registers, lane 2j / 2j+1 holding chunk j's halves, and
-    // leave as one coalesced 256-byte store per finger.
-    const int nblk = (nchunks + 31) >> 5;
-    for (int blk = wave; blk < nblk; blk += kQueryWaves) {
+    // Waves take units of uc consecutive chunks (a compact patch of the
+    // Morton-ordered object) in turn.  The ballot words of a unit stay in
+    // registers, lane 2j / 2j+1 holding chunk j's halves, and leave as one
+    // coalesced store per finger.
+    const int waves = blockDim.x >> 6, nunit = (nchunks + uc - 1) / uc;
+    for (int unit = wave; unit < nunit; unit += waves) {
         uint32_t acc[FM];
 #pragma unroll
         for (int f = 0; f < FM; ++f) acc[f] = 0;
-        const int c_end = min(nchunks, (blk + 1) * 32);
-        uint32_t skip[FM];
-        const uint32_t skip_all = block_skip<FM, LAT>(bounds, aff, H, blk, nchunks, lane, skip);
-        for (int chunk = blk * 32; chunk < c_end; ++chunk) {
-            const uint32_t cbit = 1u << (chunk - blk * 32);
-            if (skip_all & cbit) continue;  // no window in reach: its ballot words stay 0
+        const int u0 = unit * uc, c_end = min(nchunks, u0 + uc);
+        for (int c0 = u0; c0 < c_end; c0 += 8) {
+          uint32_t keep[FM];
+          for (uint32_t todo = group_keep<FM, LAT>(bounds, aff, L.win, H, c0, c_end, lane, keep); todo; todo &= todo - 1u) {
+            const uint32_t cbit = todo & (0u - todo);
+            const int chunk = c0 + __builtin_ctz(todo);
             // re-read the maps from LDS every chunk instead of pinning their
             // registers for the whole sweep
             asm volatile("" ::: "memory");
@@ -248,7 +288,7 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
             float qx, qy, qz;
             query_dir(P, nx, ny, nz, qx, qy, qz);
             const int b = nearest_bin_lut4(lut, cb4, B, qx, qy, qz);
-            const uint32_t plane = W == 2 ? __umul24((uint32_t)(b >> 5), G3) : 0u;
+            const uint32_t plane = W == 2 ? __umul24((uint32_t)(b >> 5), 4u * G3) : 0u;  // byte offset
             uint32_t word[FM];  // 0 outside the window
             uint32_t voff = 0, ip = 0;
             if (LAT) {
@@ -258,14 +298,21 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
                 Iy = min(max(Iy, 0), 1023);
                 Iz = min(max(Iz, 0), 1023);
                 ip = (uint32_t)Ix | (uint32_t)Iy << 10 | (uint32_t)Iz << 20;
-                voff = (brick_word_u24((uint32_t)Ix, (uint32_t)Iy, (uint32_t)Iz, GB) + plane) << 2;
+                // 4 * (brick word + plane): each coordinate's in-brick part goes with
+                // stride 1, 4, 16, its brick part (v & ~3, times a constant) on top
+                voff = (uint32_t)Ix << 2;
+                voff = mad_u24((uint32_t)Ix & 1020u, 60u, voff) + plane;
+                voff += (uint32_t)Iy << 4;
+                voff = mad_u24((uint32_t)Iy & 1020u, 64u * GB - 16u, voff);
+                voff += (uint32_t)Iz << 6;
+                voff = mad_u24((uint32_t)Iz & 1020u, 64u * GB * GB - 64u, voff);
                 asm volatile("" : "+v"(voff));  // one add per finger below, not a re-associated pair
             }
             // all finger gathers are issued before any is consumed
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
                 word[f] = 0u;
-                if (f < F && !(skip[f] & cbit)) {
+                if (keep[f] & cbit) {  // 0 for fingers past F
                     uint32_t off;
                     bool in;
                     if (LAT) {
@@ -279,25 +326,25 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
                         const float uz = fmaf(a.m[8], px, fmaf(a.m[9], py, fmaf(a.m[10], pz, a.m[11])));
                         const int Ix = (int)ux, Iy = (int)uy, Iz = (int)uz;
                         in = ((int)valid & (int)(min(Ix, min(Iy, Iz)) >= G) & (int)(max(Ix, max(Iy, Iz)) < 2 * G)) != 0;
-                        off = (brick_word_u24((uint32_t)Ix, (uint32_t)Iy, (uint32_t)Iz, GB) + plane) << 2;
+                        off = (brick_word_u24((uint32_t)Ix, (uint32_t)Iy, (uint32_t)Iz, GB) << 2) + plane;
                     }
                     if (in) word[f] = *reinterpret_cast<const uint32_t *>(mbase + (off + koff[f]));
                 }
             }
-            const int j2 = 2 * (chunk - blk * 32);
+            const int j2 = 2 * (chunk - u0);
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
-                if (f >= F) break;
-                if (skip[f] & cbit) continue;  // the ballot would be 0
-                const bool hit = ((word[f] >> (b & 31)) & 1u) != 0u;
+                if (!(keep[f] & cbit)) continue;  // the ballot would be 0
+                const bool hit = (int)(word[f] << (~b & 31)) < 0;  // bit b % 32
                 const unsigned long long m = __ballot(hit);
                 // the chunk's two ballot halves into lanes j2, j2 + 1 (j2 is uniform)
                 acc[f] = write_lane(acc[f], (uint32_t)m, j2);
                 acc[f] = write_lane(acc[f], (uint32_t)(m >> 32), j2 + 1);
             }
+          }
         }
-        const int wi = blk * 64 + lane;
-        if (wi < NW) {
+        const int wi = u0 * 2 + lane;
+        if (lane < 2 * uc && wi < NW) {
 #pragma unroll
             for (int f = 0; f < FM; ++f)
                 if (f < F) dom_bits[((int64_t)g * F + f) * NW + wi] = acc[f];
@@ -309,27 +356,29 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
 #pragma unroll
     for (int f = 0; f < FM; ++f)
         for (int off = 32; off > 0; off >>= 1) c[f] += __shfl_xor(c[f], off, 64);
+    __syncthreads();  // every wave is done with the bin table: its LDS holds the counts [wave][FM]
+    uint32_t *cnt = L.lut;
     if (lane == 0) {
 #pragma unroll
         for (int f = 0; f < FM; ++f)
-            if (f < F) cnt[f][wave] = c[f];
+            if (f < F) cnt[wave * FM + f] = c[f];
     }
     __syncthreads();
     if (threadIdx.x < F) {
         uint32_t s = 0;
-        for (int w = 0; w < kQueryWaves; ++w) s += cnt[threadIdx.x][w];
+        for (int w = 0; w < waves; ++w) s += cnt[w * FM + threadIdx.x];
         dom_count[(int64_t)g * F + threadIdx.x] = s;
     }
 }
 
 template <int W, int FM, bool LAT>
-__global__ void __launch_bounds__(kQueryThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ void __launch_bounds__(kQueryMaxThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_query(DevHand H, const uint32_t *__restrict__ merged, const float *__restrict__ pts,
         const float *__restrict__ nrm, int N, const float *__restrict__ poses, const float4 *__restrict__ bounds,
-        uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count)
+        uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count, int uc)
 {
     __shared__ QueryLds<FM, LAT> L;
-    query_pose<W, FM, LAT>(L, H, merged, pts, nrm, N, poses, bounds, dom_bits, dom_count, blockIdx.x);
+    query_pose<W, FM, LAT>(L, H, merged, pts, nrm, N, poses, bounds, dom_bits, dom_count, uc, blockIdx.x);
 }
 
 // The same over the poses of several chunks (one block per pose).
@@ -342,7 +391,7 @@ k_query_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx,
     const int j = batch_member(first, n, blockIdx.x);
     const ChunkDesc &c = d[idx[j]];
     query_pose<W, FM, LAT>(L, c.H, c.merged, c.pts, c.nrm, c.N, c.poses, c.bounds, c.dom_bits, c.dom_count,
-                           (int)(blockIdx.x - first[j]));
+                           query_unit(c.N, kQueryWaves), (int)(blockIdx.x - first[j]));
 }
 
 // Cone query (Sec. 4.3's theta_hit test): a query (x, -R n) hits finger f if
@@ -354,15 +403,19 @@ template <int W, int FM>
 __global__ void __launch_bounds__(kQueryThreads)
 k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__restrict__ pts,
              const float *__restrict__ nrm, int N, const float *__restrict__ poses, const float4 *__restrict__ bounds,
-             float cos_hit, uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count)
+             float cos_hit, uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count, int uc)
 {
     __shared__ float cb[3 * kMaxBins];
     __shared__ Affine aff[FM];
+    __shared__ float4 win[FM];
     __shared__ uint32_t cnt[FM][kQueryWaves];
     const int g = blockIdx.x;
     const float *pose = poses + 12 * (int64_t)g;
     for (int i = threadIdx.x; i < 3 * H.B; i += blockDim.x) cb[i] = H.bin_c[i];
-    if (threadIdx.x < H.F) aff[threadIdx.x] = finger_affine(H, pose, threadIdx.x);
+    if (threadIdx.x < H.F) {
+        aff[threadIdx.x] = finger_affine(H, pose, threadIdx.x);
+        win[threadIdx.x] = make_float4((float)H.G, (float)H.G, (float)H.G, map_stretch(aff[threadIdx.x]));
+    }
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int F = H.F, G = H.G, B = H.B;
@@ -375,17 +428,17 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
     uint32_t c[FM];
 #pragma unroll
     for (int f = 0; f < FM; ++f) c[f] = 0;
-    const int nblk = (nchunks + 31) >> 5;
-    for (int blk = wave; blk < nblk; blk += kQueryWaves) {
+    const int nunit = (nchunks + uc - 1) / uc;
+    for (int unit = wave; unit < nunit; unit += kQueryWaves) {
         uint32_t acc[FM];
 #pragma unroll
         for (int f = 0; f < FM; ++f) acc[f] = 0;
-        const int c_end = min(nchunks, (blk + 1) * 32);
-        uint32_t skip[FM];
-        const uint32_t skip_all = block_skip<FM, false>(bounds, aff, H, blk, nchunks, lane, skip);
-        for (int chunk = blk * 32; chunk < c_end; ++chunk) {
-            const uint32_t cbit = 1u << (chunk - blk * 32);
-            if (skip_all & cbit) continue;  // no window in reach: its ballot words stay 0
+        const int u0 = unit * uc, c_end = min(nchunks, u0 + uc);
+        for (int c0 = u0; c0 < c_end; c0 += 8) {
+          uint32_t keep[FM];
+          for (uint32_t todo = group_keep<FM, false>(bounds, aff, win, H, c0, c_end, lane, keep); todo; todo &= todo - 1u) {
+            const uint32_t cbit = todo & (0u - todo);
+            const int chunk = c0 + __builtin_ctz(todo);
             asm volatile("" ::: "memory");
             const int i = chunk * 64 + lane;
             const bool valid = i < N;
@@ -415,7 +468,7 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
                 ent[f] = 0ull;
-                if (f < F && !(skip[f] & cbit)) {
+                if (keep[f] & cbit) {  // 0 for fingers past F
                     // biased window coordinates (see window_voxel): inside iff all in [G, 2G)
                     const Affine &a = aff[f];
                     const float ux = fmaf(a.m[0], px, fmaf(a.m[1], py, fmaf(a.m[2], pz, a.m[3])));
@@ -431,7 +484,7 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
                     }
                 }
             }
-            const int j2 = 2 * (chunk - blk * 32);
+            const int j2 = 2 * (chunk - u0);
             // the point's cone as a bin mask over the band's bins that some
             // finger's entry holds (the per-finger test is then one AND)
             unsigned long long cone = 0ull;
@@ -448,16 +501,16 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
             }
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
-                if (f >= F) break;
-                if (skip[f] & cbit) continue;  // the ballot would be 0
+                if (!(keep[f] & cbit)) continue;  // the ballot would be 0
                 const bool hit = (ent[f] & cone) != 0ull;
                 const unsigned long long bm = __ballot(hit);
                 acc[f] = write_lane(acc[f], (uint32_t)bm, j2);
                 acc[f] = write_lane(acc[f], (uint32_t)(bm >> 32), j2 + 1);
             }
+          }
         }
-        const int wi = blk * 64 + lane;
-        if (wi < NW) {
+        const int wi = u0 * 2 + lane;
+        if (lane < 2 * uc && wi < NW) {
 #pragma unroll
             for (int f = 0; f < FM; ++f)
                 if (f < F) dom_bits[((int64_t)g * F + f) * NW + wi] = acc[f];
@@ -485,6 +538,8 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
 
 using namespace lg;
 
+static int query_threads(int n_poses) { return n_poses <= 256 ? 1024 : n_poses <= 512 ? 512 : kQueryThreads; }
+
 static lg_status query_domains(const lg_field *field, const float *pts, const float *nrm, int32_t n_points,
                                const float *poses, int32_t n_poses, const float4 *bounds, uint32_t *dom_bits,
                                uint32_t *dom_count, void *stream)
@@ -498,9 +553,12 @@ static lg_status query_domains(const lg_field *field, const float *pts, const fl
         return fail(LG_EUNSUPPORTED, "n_points above 357,913,941 (32-bit byte offsets into the point rows)");
     hipStream_t s = as_stream(stream);
     const DevHand &H = field->dh;
+    // A pose is one block.  Few poses leave the chip short of waves, so they
+    // get larger blocks (up to 16 waves).
+    const int tb = query_threads(n_poses), uc = query_unit(n_points, tb / 64);
 #define LG_QUERY(W, FM, LAT)                                                                                 \
-    hipLaunchKernelGGL((k_query<W, FM, LAT>), dim3(n_poses), dim3(kQueryThreads), 0, s, H, field->d_merged, pts, \
-                       nrm, n_points, poses, bounds, dom_bits, dom_count)
+    hipLaunchKernelGGL((k_query<W, FM, LAT>), dim3(n_poses), dim3(tb), 0, s, H, field->d_merged, pts,        \
+                       nrm, n_points, poses, bounds, dom_bits, dom_count, uc)
 #define LG_QUERY_F(W, LAT)                                                                                   \
     if (H.F <= 3) LG_QUERY(W, 3, LAT); else if (H.F <= 4) LG_QUERY(W, 4, LAT);                               \
     else if (H.F <= 5) LG_QUERY(W, 5, LAT); else LG_QUERY(W, 8, LAT)
@@ -615,7 +673,8 @@ extern "C" lg_status lg_query_domains_cone(const lg_field *field, const float *p
     const DevHand &H = field->dh;
 #define LG_QCONE(W, FM)                                                                                        \
     hipLaunchKernelGGL((k_query_cone<W, FM>), dim3(n_poses), dim3(kQueryThreads), 0, s, H, field->d_merged, pts, \
-                       nrm, n_points, poses, reinterpret_cast<const float4 *>(bounds), cos_hit, dom_bits, dom_count)
+                       nrm, n_points, poses, reinterpret_cast<const float4 *>(bounds), cos_hit, dom_bits, dom_count,     \
+                       query_unit(n_points, kQueryWaves))
     if (H.W == 1) {
         if (H.F <= 3) LG_QCONE(1, 3); else if (H.F <= 4) LG_QCONE(1, 4); else if (H.F <= 5) LG_QCONE(1, 5); else LG_QCONE(1, 8);
     } else {
