@@ -24,12 +24,13 @@
 //    the waves (LDS) and the workgroups (64-bit atomicMax of ordered value
 //    bits above the inverted point index); bias and ReLU are applied to the
 //    pooled maximum.
-//  * the head and every backward product are small GEMMs (rows = objects)
-//    run by k_gemm, one wave per 32x32 output tile;
-//  * the encoder backward is sparse: the max-pool routes each channel's
-//    gradient to one point, so only B x 256 point rows are revisited (FP32).
-
-#include <type_traits>
+//  * the head's layers and their input gradients are chains of small products
+//    (rows = objects): a workgroup of 8 waves takes 32 objects through a whole
+//    chain (k_head, k_head_bwd), a wave per 32 columns, activations in LDS;
+//  * every weight gradient, the biases, the loss and the encoder's backward are
+//    independent once the chain is done and run in one launch (k_grads).  The
+//    encoder's is sparse: the max-pool routes each channel's gradient to one
+//    point, so only B x 256 point rows are revisited (FP32).
 
 #include "lg_internal.h"
 
@@ -51,25 +52,37 @@ constexpr int64_t kWa = kB2 + kH2, kBa = kWa + kH2 * kHH;
 constexpr int64_t kWb = kBa + kHH, kBb = kWb + kHH * kHH;
 constexpr int64_t kWc = kBb + kHH, kBc = kWc + kHH * kOut;
 constexpr int64_t kNParams = kBc + kOut;
-// BF16 weight copies, transposed to [out][in_pad] so that an MFMA B operand
-// (8 consecutive k of one output column) is one 16-byte load
-constexpr int64_t kT1 = 0, kT2 = kT1 + kH1 * kInPad, kTa = kT2 + kH2 * kH1;
-constexpr int64_t kTb = kTa + kHH * kH2, kTc = kTb + kHH * kHH, kNT = kTc + kOut * kHH;
+// BF16 weight copies.  Encoder layers: transposed to [out][in_pad], so that an MFMA
+// operand (8 consecutive inputs of one output) is one 16-byte load.  Head layers:
+// in operand order, twice, so that a wave's load of an operand is 1 KiB in one
+// piece (rows of the transposed copy are 32 pieces; a block's weight reads then
+// took 12 us instead of 4): for the products with W, tiles of 32 outputs, k = inputs
+// (kTa, kTb, kTc); for those with W^T, tiles of 32 inputs, k = outputs (kUa, kUb,
+// kUc).  [tile][k / 16][lane][8]; outputs are padded to 160 in the last layer.
+constexpr int kOutPad = (kOut + 31) / 32 * 32;
+constexpr int64_t kT1 = 0, kT2 = kT1 + kH1 * kInPad, kTa = kT2 + kH2 * kH1, kTb = kTa + kHH * kH2;
+constexpr int64_t kTc = kTb + kHH * kHH, kUa = kTc + kHH * kOutPad, kUb = kUa + kHH * kH2;
+constexpr int64_t kUc = kUb + kHH * kHH, kNT = kUc + kHH * kOutPad;
 
 struct LayerDesc {
-    int in, out, in_pad;
-    int64_t w, b, t;
+    int in, out, in_pad;  // in_pad: encoder layers only
+    int64_t w, b, t, u;
     float init_gain;
 };
 __host__ __device__ inline LayerDesc layer(int l)
 {
     switch (l) {
-    case 0: return {kIn, kH1, kInPad, kW1, kB1, kT1, 1.0f};
-    case 1: return {kH1, kH2, kH1, kW2, kB2, kT2, 1.0f};
-    case 2: return {kH2, kHH, kH2, kWa, kBa, kTa, 1.0f};
-    case 3: return {kHH, kHH, kHH, kWb, kBb, kTb, 1.0f};
-    default: return {kHH, kOut, kHH, kWc, kBc, kTc, 0.1f};
+    case 0: return {kIn, kH1, kInPad, kW1, kB1, kT1, 0, 1.0f};
+    case 1: return {kH1, kH2, kH1, kW2, kB2, kT2, 0, 1.0f};
+    case 2: return {kH2, kHH, 0, kWa, kBa, kTa, kUa, 1.0f};
+    case 3: return {kHH, kHH, 0, kWb, kBb, kTb, kUb, 1.0f};
+    default: return {kHH, kOut, 0, kWc, kBc, kTc, kUc, 0.1f};
     }
+}
+// place of element (k, c) of an operand array: column (or row) c of the tiles, kpad values of k
+__host__ __device__ inline int64_t operand_at(int k, int c, int kpad)
+{
+    return (((int64_t)(c >> 5) * (kpad / 16) + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (c & 31)) * 8 + (k & 7);
 }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -114,23 +127,33 @@ __global__ void k_init(float *__restrict__ P, uint32_t s_lo, uint32_t s_hi)
     }
 }
 
-__global__ void k_refresh_bf16(const float *__restrict__ P, uint16_t *__restrict__ T)
+// the BF16 copies of parameter i (value w); biases have none
+__device__ inline void store_bf16(uint16_t *__restrict__ T, int64_t i, float w)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= kNT) return;
     for (int l = 0; l < 5; ++l) {
         const LayerDesc L = layer(l);
-        const int64_t n = (int64_t)L.out * L.in_pad;
-        if (idx >= L.t && idx < L.t + n) {
-            const int o = (int)((idx - L.t) / L.in_pad), i = (int)((idx - L.t) % L.in_pad);
-            T[idx] = i < L.in ? bf16_bits(P[L.w + (int64_t)i * L.out + o]) : (uint16_t)0;
-            return;
+        if (i < L.w || i >= L.b) continue;
+        const int r = (int)(i - L.w) / L.out, o = (int)(i - L.w) - r * L.out;
+        const uint16_t h = bf16_bits(w);
+        if (l < 2) {
+            T[L.t + (int64_t)o * L.in_pad + r] = h;
+        } else {
+            T[L.t + operand_at(r, o, kHH)] = h;
+            T[L.u + operand_at(o, r, l == 4 ? kOutPad : kHH)] = h;
         }
     }
 }
 
+// every copy from the parameters (the padding stays as it was filled: 0)
+__global__ void k_refresh_bf16(const float *__restrict__ P, uint16_t *__restrict__ T)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kNParams) store_bf16(T, i, P[i]);
+}
+
+// One step of Adam; the BF16 copies of a weight are written with it.
 __global__ void k_adam(float *__restrict__ P, const float *__restrict__ G, float *__restrict__ Mo,
-                       float *__restrict__ Vo, float lr_t, float b1, float b2, float eps)
+                       float *__restrict__ Vo, uint16_t *__restrict__ T, float lr_t, float b1, float b2, float eps)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kNParams) return;
@@ -139,7 +162,9 @@ __global__ void k_adam(float *__restrict__ P, const float *__restrict__ G, float
     const float v = b2 * Vo[i] + (1.0f - b2) * g * g;
     Mo[i] = m;
     Vo[i] = v;
-    P[i] -= lr_t * m / (sqrtf(v) + eps);
+    const float w = P[i] - lr_t * m / (sqrtf(v) + eps);
+    P[i] = w;
+    store_bf16(T, i, w);
 }
 
 __global__ void k_fill_u64(unsigned long long *__restrict__ p, int64_t n)
@@ -152,7 +177,8 @@ __global__ void k_fill_u64(unsigned long long *__restrict__ p, int64_t n)
 constexpr int kEncWaves = 8;
 constexpr int kEncThreads = 64 * kEncWaves;
 constexpr int kEncPair = 64;                         // points a wave takes per step: two 32-row blocks
-constexpr int kEncChunk = kEncPair * kEncWaves * 4;  // points per workgroup (4 steps per wave)
+constexpr int kEncStep = kEncPair * kEncWaves;       // points a workgroup takes per step
+constexpr int kEncMaxSteps = 4;
 constexpr int kLd = kH1 + 8;                                   // padded LDS row of W2^T (BF16 elements)
 static_assert(kEncThreads >= kH2, "the pooled-key merge takes one thread per channel");
 static_assert(kEncWaves * kH2 * 8 <= kH2 * kLd * 2, "the pooled-key merge reuses the W2 buffer");
@@ -216,7 +242,7 @@ __device__ inline void fold_rows(f32x16_t a, int row0, int end, int half, float 
     }
 }
 
-// grid (ceil(Np / kEncChunk), B), kEncThreads threads.  Each wave runs its
+// grid (ceil(Np / (kEncStep * steps)), B), kEncThreads threads.  Each wave runs its
 // own 64-point steps with no barrier: layer 1 is computed transposed
 // (channels x points), so a lane ends up holding 4-channel groups of one
 // point; one lane-half swap per dword turns them into the layer-2 A operand
@@ -224,7 +250,7 @@ __device__ inline void fold_rows(f32x16_t a, int row0, int end, int half, float 
 // Registers, not LDS, set the occupancy: the H1 of two row blocks, two
 // accumulators and the running pairs take 174 VGPRs, two waves per SIMD.
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))) void
-k_encode(const float *__restrict__ x, int Np, const uint16_t *__restrict__ T, const float *__restrict__ P,
+k_encode(const float *__restrict__ x, int Np, int steps, const uint16_t *__restrict__ T, const float *__restrict__ P,
          unsigned long long *__restrict__ keys)
 {
     __shared__ __attribute__((aligned(16))) uint16_t sW2[kH2 * kLd];
@@ -246,7 +272,7 @@ k_encode(const float *__restrict__ x, int Np, const uint16_t *__restrict__ T, co
         best[c] = -INFINITY;
         bidx[c] = 0;
     }
-    const int c0 = blockIdx.x * kEncChunk, c1 = min(Np, c0 + kEncChunk);
+    const int c0 = blockIdx.x * kEncStep * steps, c1 = min(Np, c0 + kEncStep * steps);
     for (int p0 = c0 + wave * kEncPair; p0 < c1; p0 += kEncWaves * kEncPair) {
         u16x8_t h[2][kH1 / 16];
 #pragma unroll
@@ -331,117 +357,160 @@ k_encode(const float *__restrict__ x, int Np, const uint16_t *__restrict__ T, co
     }
 }
 
-// feat = relu(max pre-activation + b2); arg = its point, or 0 where the
-// channel is cut to zero (every point then ties at 0 and the lowest wins).
-// Each key is reset to 0 once read, ready for the next pass.
-__global__ void k_pool_finish(unsigned long long *__restrict__ keys, int n, const float *__restrict__ P,
-                              float *__restrict__ feat, int32_t *__restrict__ arg)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const unsigned long long k = keys[i];
-    keys[i] = 0ull;
-    float f = 0.0f;
-    int32_t a = 0;
-    if (k) {
-        const float t = ord_val((uint32_t)(k >> 32)) + P[kB2 + i % kH2];
-        if (t > 0.0f) {
-            f = t;
-            a = (int32_t)(0xFFFFFFFFu - (uint32_t)k);
-        }
-    }
-    feat[i] = f;
-    arg[i] = a;
-}
+// ---- head ---------------------------------------------------------------------
+constexpr int kHeadWaves = kHH / 32;
+constexpr int kHeadThreads = 64 * kHeadWaves;
+constexpr int kActLd = kHH + 8;  // padded LDS row of 32 objects' BF16 activations
 
-// ---- small GEMMs -------------------------------------------------------------
-// C[m][n] = epi(sum_k A(m,k) B(k,n)), operands rounded to BF16, FP32 accumulate.
-// A(m,k) = A[m*a_ms + k*a_ks] (FP32); B(k,n) = B[k*b_ks + n*b_ns] (FP32 or BF16 bits).
-enum { kEpiNone = 0, kEpiBias = 1, kEpiBiasRelu = 2, kEpiMask = 3 };
-constexpr int kGemmSteps = 8;  // k-steps of 16 per trip of the main loop
-
-// KC: k is contiguous in both operands (a_ks = b_ks = 1, K % 16 = 0, rows
-// 16-byte aligned; B is BF16): 8 consecutive k are two float4 loads of A
-// and one 16-byte load of B.  The main loop issues the loads of kGemmSteps
-// k-steps before their MFMAs, so that they are in flight together.
-template <typename TB, int EPI, bool KC>
-__global__ __launch_bounds__(64) void k_gemm(int Mr, int Nc, int K, const float *__restrict__ A, int64_t a_ms,
-                                             int64_t a_ks, const TB *__restrict__ Bm, int64_t b_ks, int64_t b_ns,
-                                             const float *__restrict__ bias, const float *__restrict__ mask,
-                                             int64_t mask_ld, float *__restrict__ C, int64_t ldc)
+// Pooling and the three layers for 32 objects (block) of B.  feat = relu(max
+// pre-activation + b2); arg = its point, or 0 where the channel is cut to zero
+// (every point then ties at 0 and the lowest wins).  Each key is reset to 0 once
+// read, ready for the next pass.  A wave computes 32 columns of a layer from the
+// block's activations in LDS; its 16 weight operands of a layer are all loaded
+// before the layer below is done.  What bounds it: latency (a chain of three
+// products of 16 steps in one block per 32 objects): 13 us for 512 objects,
+// where pooling and three launches took 5 + 17 us and three copies.  out2, feat2, arg2: the caller's copies, or null.
+__global__ __launch_bounds__(kHeadThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+k_head(unsigned long long *__restrict__ keys, int B, const float *__restrict__ P, const uint16_t *__restrict__ T,
+       float *__restrict__ feat, int32_t *__restrict__ arg, float *__restrict__ ua, float *__restrict__ ub,
+       float *__restrict__ out, float *__restrict__ feat2, int32_t *__restrict__ arg2, float *__restrict__ out2)
 {
-    const int lane = threadIdx.x, r = lane & 31, half = lane >> 5;
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    const int m = m0 + r, n = n0 + r;
-    f32x16_t acc = {};
-    // rows m >= Mr and columns n >= Nc repeat the last one (KC) or read zeros
-    // and are not stored
-    const float *ar = A + (int64_t)min(m, Mr - 1) * a_ms + 8 * half;
-    const TB *br = Bm + (int64_t)min(n, Nc - 1) * b_ns + 8 * half;
-    // operands of one k-step (the 8 consecutive k of this lane's half)
-    struct Ops {
-        float4 a0, a1;
-        u16x8_t av, bv;
-    };
-    auto load = [&](int k0, Ops &o) {
-        if constexpr (KC) {
-            o.a0 = *(const float4 *)(ar + k0);
-            o.a1 = *(const float4 *)(ar + k0 + 4);
-            o.bv = *(const u16x8_t *)(br + k0);
-        } else {
+    __shared__ __attribute__((aligned(16))) uint16_t act[2][32 * kActLd];
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), m0 = blockIdx.x * 32, n = 32 * wave + r;
+    u16x8_t w[kHH / 16];
+    auto weights = [&](int64_t t, int tile) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int k = k0 + 8 * half + j;
-                o.av[j] = (m < Mr && k < K) ? bf16_bits(A[m * a_ms + k * a_ks]) : (uint16_t)0;
-                o.bv[j] = (n < Nc && k < K) ? bf16_bits(Bm[k * b_ks + n * b_ns]) : (uint16_t)0;
+        for (int k = 0; k < kHH / 16; ++k) w[k] = *(const u16x8_t *)&T[t + ((tile * (kHH / 16) + k) * 64 + lane) * 8];
+    };
+    auto product = [&](const uint16_t *A) {
+        f32x16_t acc = {};
+#pragma unroll
+        for (int k = 0; k < kHH / 16; ++k) acc = mfma(*(const u16x8_t *)&A[r * kActLd + 16 * k + 8 * half], w[k], acc);
+        return acc;
+    };
+    weights(kTa, wave);
+    // thread: one channel of every other object; all its keys are loaded before the first is used
+    const int c = tid % kH2, r0 = tid / kH2;
+    constexpr int kRows = 32 * kH2 / kHeadThreads, kRowStep = kHeadThreads / kH2;
+    unsigned long long key[kRows];
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+        const int row = m0 + r0 + kRowStep * q;
+        key[q] = row < B ? keys[(int64_t)row * kH2 + c] : 0ull;
+    }
+    const float b2 = P[kB2 + c];
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+        const int row = r0 + kRowStep * q;
+        float f = 0.0f;
+        if (m0 + row < B) {
+            const int64_t id = (int64_t)(m0 + row) * kH2 + c;
+            keys[id] = 0ull;
+            int32_t a = 0;
+            if (key[q]) {
+                const float t = ord_val((uint32_t)(key[q] >> 32)) + b2;
+                if (t > 0.0f) {
+                    f = t;
+                    a = (int32_t)(0xFFFFFFFFu - (uint32_t)key[q]);
+                }
+            }
+            feat[id] = f;
+            arg[id] = a;
+            if (feat2) feat2[id] = f;
+            if (arg2) arg2[id] = a;
+        }
+        act[0][row * kActLd + c] = bf16_bits(f);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+        f32x16_t acc = product(act[l]);
+        weights(l == 0 ? kTb : kTc, l == 0 ? wave : min(wave, kOutPad / 32 - 1));  // the next layer's
+        const float bias = P[(l == 0 ? kBa : kBb) + n];
+        float *u = l == 0 ? ua : ub;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int row = c_row(i, lane);
+            const float v = fmaxf(acc[i] + bias, 0.0f);
+            if (m0 + row < B) u[(int64_t)(m0 + row) * kHH + n] = v;
+            act[1 - l][row * kActLd + n] = bf16_bits(v);
+        }
+        __syncthreads();
+    }
+    if (32 * wave < kOut) {
+        const f32x16_t acc = product(act[0]);
+        if (n < kOut) {
+            const float bias = P[kBc + n];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int row = m0 + c_row(i, lane);
+                if (row >= B) continue;
+                out[(int64_t)row * kOut + n] = acc[i] + bias;
+                if (out2) out2[(int64_t)row * kOut + n] = acc[i] + bias;
             }
         }
-    };
-    auto use = [&](Ops &o) {
-        if constexpr (KC) {
-            o.av[0] = bf16_bits(o.a0.x);
-            o.av[1] = bf16_bits(o.a0.y);
-            o.av[2] = bf16_bits(o.a0.z);
-            o.av[3] = bf16_bits(o.a0.w);
-            o.av[4] = bf16_bits(o.a1.x);
-            o.av[5] = bf16_bits(o.a1.y);
-            o.av[6] = bf16_bits(o.a1.z);
-            o.av[7] = bf16_bits(o.a1.w);
-        }
-        acc = mfma(o.av, o.bv, acc);
-    };
-    int k0 = 0;
-    for (; k0 + 16 * kGemmSteps <= K; k0 += 16 * kGemmSteps) {  // all loads of a trip go out first
-        Ops o[kGemmSteps];
-#pragma unroll
-        for (int t = 0; t < kGemmSteps; ++t) load(k0 + 16 * t, o[t]);
-#pragma unroll
-        for (int t = 0; t < kGemmSteps; ++t) use(o[t]);
-    }
-    for (; k0 < K; k0 += 16) {
-        Ops o;
-        load(k0, o);
-        use(o);
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int mm = m0 + c_row(i, lane);
-        if (mm >= Mr || n >= Nc) continue;
-        float v = acc[i];
-        if (EPI == kEpiBias) v += bias[n];
-        if (EPI == kEpiBiasRelu) v = fmaxf(v + bias[n], 0.0f);
-        if (EPI == kEpiMask) v = mask[mm * mask_ld + n] > 0.0f ? v : 0.0f;
-        C[mm * ldc + n] = v;
     }
 }
 
-__global__ void k_colsum(const float *__restrict__ X, int rows, int cols, int64_t ld, float *__restrict__ out)
+// Input gradients of the head for 32 objects (block): dub = (dO Wc^T) [ub > 0],
+// dua = (dub Wb^T) [ua > 0], dfeat = dua Wa^T.  Each is computed transposed
+// (rows = inputs, columns = objects); a wave takes 32 inputs.  As separate
+// products with the copies for W, 2-byte loads a row apart took 27-40 us each at
+// 32 objects; the chain takes 13 us.
+__global__ __launch_bounds__(kHeadThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+k_head_bwd(int B, const uint16_t *__restrict__ T, const float *__restrict__ dO, const float *__restrict__ ua,
+           const float *__restrict__ ub, float *__restrict__ dub, float *__restrict__ dua, float *__restrict__ dfeat)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float s = 0.0f;
-    for (int r = 0; r < rows; ++r) s += X[r * ld + c];
-    out[c] = s;
+    __shared__ __attribute__((aligned(16))) uint16_t act[2][32 * kActLd];
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), m0 = blockIdx.x * 32, i0 = 32 * wave;
+    constexpr int kSteps = kHH / 16;
+    const int row = m0 + r;  // this lane's object in the products' columns
+    // a layer's weight operands, all loaded before the layer below is done
+    u16x8_t w[kSteps];
+    auto weights = [&](int64_t u, int steps) {
+#pragma unroll
+        for (int k = 0; k < kSteps; ++k)
+            if (k < steps) w[k] = *(const u16x8_t *)&T[u + ((wave * steps + k) * 64 + lane) * 8];
+    };
+    weights(kUc, kOutPad / 16);
+    for (int i = tid; i < 32 * kOutPad; i += kHeadThreads) {
+        const int q = i / kOutPad, j = i % kOutPad;
+        act[0][q * kActLd + j] = m0 + q < B && j < kOut ? bf16_bits(dO[(int64_t)(m0 + q) * kOut + j]) : (uint16_t)0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const uint16_t *A = act[l & 1];
+        f32x16_t acc = {};
+#pragma unroll
+        for (int k = 0; k < (l == 0 ? kOutPad / 16 : kSteps); ++k) {
+            acc = mfma(w[k], *(const u16x8_t *)&A[r * kActLd + 16 * k + 8 * half], acc);
+        }
+        if (l < 2) weights(l == 0 ? kUb : kUa, kSteps);
+        const float *mask = l == 0 ? ub : ua;
+        float *d = l == 0 ? dub : l == 1 ? dua : dfeat;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int in = i0 + 8 * g + 4 * half;  // four consecutive inputs of this lane's object
+            float4 v = make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+            if (row < B) {
+                if (l < 2) {
+                    const float4 m = *(const float4 *)&mask[(int64_t)row * kHH + in];
+                    v = make_float4(m.x > 0.0f ? v.x : 0.0f, m.y > 0.0f ? v.y : 0.0f, m.z > 0.0f ? v.z : 0.0f,
+                                    m.w > 0.0f ? v.w : 0.0f);
+                }
+                *(float4 *)&d[(int64_t)row * kHH + in] = v;
+            }
+            uint16_t *q = &act[1 - (l & 1)][r * kActLd + in];
+            q[0] = bf16_bits(v.x);
+            q[1] = bf16_bits(v.y);
+            q[2] = bf16_bits(v.z);
+            q[3] = bf16_bits(v.w);
+        }
+        __syncthreads();
+    }
 }
 
 // ---- mixture NLL -------------------------------------------------------------
@@ -460,173 +529,261 @@ __device__ inline void log_softmax8(const float *o, float lp[kM])
 
 __device__ inline float clamp_ls(float v) { return fminf(fmaxf(v, kLsMin), kLsMax); }
 
-// thread per target: NLL and responsibilities
-__global__ void k_nll(const float *__restrict__ out, const float *__restrict__ tg, const int32_t *__restrict__ off,
-                      int B, int T, float *__restrict__ nll, float *__restrict__ resp)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    int lo = 0, hi = B;  // the object: the last b with off[b] <= t
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (off[mid] <= t) lo = mid;
-        else hi = mid;
-    }
-    const float *o = out + (int64_t)lo * kOut;
-    const float *y = tg + (int64_t)t * kY;
-    float lp[kM], comp[kM];
-    log_softmax8(o, lp);
-    const float half_log_2pi = 0.91893853320467274f;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int m = 0; m < kM; ++m) {
-        float c = lp[m];
-        for (int d = 0; d < kY; ++d) {
-            const float ls = clamp_ls(o[kM + kM * kY + m * kY + d]);
-            const float z = (y[d] - o[kM + m * kY + d]) * expf(-ls);
-            c += -0.5f * z * z - ls - half_log_2pi;
-        }
-        comp[m] = c;
-        mx = fmaxf(mx, c);
-    }
-    float s = 0.0f;
-#pragma unroll
-    for (int m = 0; m < kM; ++m) s += expf(comp[m] - mx);
-    nll[t] = -(mx + logf(s));
-#pragma unroll
-    for (int m = 0; m < kM; ++m) resp[(int64_t)t * kM + m] = expf(comp[m] - mx) / s;
-}
+constexpr int kNllTile = 64;  // targets of an object held in LDS at a time
+constexpr int kNllThreads = 256;
 
-// thread per (object, output): gradient of the batch-mean NLL, targets in order
-__global__ void k_dout(const float *__restrict__ out, const float *__restrict__ tg, const int32_t *__restrict__ off,
-                       const float *__restrict__ resp, int B, float inv_T, float *__restrict__ dO)
+// Workgroup per object: NLL and responsibilities of its targets, and from them
+// the gradient of the batch-mean NLL at its outputs (thread per output, targets
+// in order).  The first and last objects also score any targets before and
+// after the offsets' range (their NLL counts in the loss).  A thread per target
+// and then one per (object, output) over global memory took 8 + 27 us at 32
+// objects of 64 targets.
+__global__ __launch_bounds__(kNllThreads) void k_nll(const float *__restrict__ out, const float *__restrict__ tg,
+                                                     const int32_t *__restrict__ off, int B, int T, float inv_T,
+                                                     float *__restrict__ nll, float *__restrict__ dO)
 {
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= B * kOut) return;
-    const int b = id / kOut, j = id % kOut;
-    const float *o = out + (int64_t)b * kOut;
-    const int t0 = off[b], t1 = off[b + 1];
-    float g = 0.0f;
-    if (j < kM) {
+    __shared__ float o[kOut], inv_s[kM * kY], lps[kM], comp[kNllTile][kM], resp[kNllTile][kM], y[kNllTile][kY];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    if (tid < kOut) o[tid] = out[(int64_t)b * kOut + tid];
+    __syncthreads();
+    if (tid < kM * kY) inv_s[tid] = expf(-clamp_ls(o[kM + kM * kY + tid]));
+    if (tid == 0) {
         float lp[kM];
         log_softmax8(o, lp);
-        const float pi = expf(lp[j]);
-        for (int t = t0; t < t1; ++t) g += pi - resp[(int64_t)t * kM + j];
-    } else if (j < kM + kM * kY) {
-        const int m = (j - kM) / kY, d = (j - kM) % kY;
-        const float ls = clamp_ls(o[kM + kM * kY + m * kY + d]);
-        const float inv_s = expf(-ls), mu = o[j];
-        for (int t = t0; t < t1; ++t) {
-            const float z = (tg[(int64_t)t * kY + d] - mu) * inv_s;
-            g -= resp[(int64_t)t * kM + m] * z * inv_s;
+#pragma unroll
+        for (int m = 0; m < kM; ++m) lps[m] = lp[m];
+    }
+    __syncthreads();
+    const int t0 = max(off[b], 0), t1 = min(off[b + 1], T);
+    const int s0 = b == 0 ? 0 : t0, s1 = b == B - 1 ? T : t1;
+    const float half_log_2pi = 0.91893853320467274f;
+    const int j = tid, m = j < kM ? j : ((j - kM) % (kM * kY)) / kY, d = j < kM ? 0 : (j - kM) % kY;
+    const float raw = j < kOut ? o[j] : 0.0f, mu = j < kM || j >= kOut ? 0.0f : o[kM + m * kY + d];
+    const float pi = j < kM ? expf(lps[m]) : 0.0f;
+    float g = 0.0f;
+    for (int base = s0; base < s1; base += kNllTile) {
+        const int nt = min(kNllTile, s1 - base);
+        for (int i = tid; i < nt * kY; i += kNllThreads) (&y[0][0])[i] = tg[(int64_t)base * kY + i];
+        __syncthreads();
+        for (int i = tid; i < nt * kM; i += kNllThreads) {
+            const int t = i / kM, mm = i % kM;
+            float c = lps[mm];
+            for (int q = 0; q < kY; ++q) {
+                const float ls = clamp_ls(o[kM + kM * kY + mm * kY + q]);
+                const float z = (y[t][q] - o[kM + mm * kY + q]) * inv_s[mm * kY + q];
+                c += -0.5f * z * z - ls - half_log_2pi;
+            }
+            comp[t][mm] = c;
         }
-    } else {
-        const int m = (j - kM - kM * kY) / kY, d = (j - kM - kM * kY) % kY;
-        const float raw = o[j];
-        if (raw > kLsMin && raw < kLsMax) {
-            const float inv_s = expf(-raw), mu = o[kM + m * kY + d];
-            for (int t = t0; t < t1; ++t) {
-                const float z = (tg[(int64_t)t * kY + d] - mu) * inv_s;
-                g += resp[(int64_t)t * kM + m] * (1.0f - z * z);
+        __syncthreads();
+        for (int t = tid; t < nt; t += kNllThreads) {
+            float mx = -INFINITY, s = 0.0f;
+#pragma unroll
+            for (int mm = 0; mm < kM; ++mm) mx = fmaxf(mx, comp[t][mm]);
+#pragma unroll
+            for (int mm = 0; mm < kM; ++mm) s += expf(comp[t][mm] - mx);
+            nll[base + t] = -(mx + logf(s));
+#pragma unroll
+            for (int mm = 0; mm < kM; ++mm) resp[t][mm] = expf(comp[t][mm] - mx) / s;
+        }
+        __syncthreads();
+        if (j < kOut) {
+            const int e0 = max(t0 - base, 0), e1 = min(nt, t1 - base);
+            if (j < kM) {
+                for (int t = e0; t < e1; ++t) g += pi - resp[t][m];
+            } else if (j < kM + kM * kY) {
+                const float is = inv_s[j - kM];
+                for (int t = e0; t < e1; ++t) g -= resp[t][m] * ((y[t][d] - mu) * is) * is;
+            } else if (raw > kLsMin && raw < kLsMax) {
+                const float is = inv_s[j - kM - kM * kY];
+                for (int t = e0; t < e1; ++t) {
+                    const float z = (y[t][d] - mu) * is;
+                    g += resp[t][m] * (1.0f - z * z);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (j < kOut) dO[(int64_t)b * kOut + j] = g * inv_T;
+}
+
+// ---- weight gradients -----------------------------------------------------------
+constexpr int kGradThreads = 256;
+constexpr int kGradTile = 64;  // objects of one channel held in LDS at a time
+// tiles of 32 x 32 of the three head weights (rows = inputs): Wc, Wb, Wa
+constexpr int kTilesC = (kHH / 32) * ((kOut + 31) / 32), kTilesH = (kHH / 32) * (kHH / 32);
+constexpr int kGradTileBlocks = (kTilesC + 2 * kTilesH + 3) / 4;            // a wave per tile
+constexpr int kGradBiasBlocks = (kOut + 2 * kHH + kGradThreads - 1) / kGradThreads;
+constexpr int kGradEncBlocks = kH2 / 2;                                     // two channels per block
+constexpr int kGradBlocks = kGradTileBlocks + kGradBiasBlocks + 1 + kGradEncBlocks;
+
+struct GradArgs {
+    const float *x, *feat, *ua, *ub, *dO, *dub, *dua, *dfeat, *nll, *P;
+    const uint16_t *T;
+    const int32_t *arg;
+    float *G, *G2, *loss, *loss2, *part;  // G2, loss2: the caller's copies, or null
+    int B, Np, n_targets;
+};
+
+// Everything that depends only on the chain's activations and gradients, by
+// block: the head's weight gradients A^T D (K = objects) as MFMA tiles; the bias
+// gradients (sums over the objects in order); the loss (fixed-order sum of the
+// per-target NLL); and the encoder's backward, per (channel c, hidden k): h1 of
+// the channel's argmax points is recomputed from their inputs (six multiply-adds
+// each, instead of a [B][256][128] array written by one kernel and read by two),
+// dW2[k][c] and db2[c] summed over the objects in order, and this channel's part
+// of dW1 and db1, [128][7][256], summed over the channels by k_w1.  What bounds
+// it: latency (a hundred-odd short blocks): 14 us at 32 objects, 130 us as ten
+// launches.
+__global__ __launch_bounds__(kGradThreads) void k_grads(GradArgs a)
+{
+    __shared__ float sh[kGradTile * 2][2 * kIn + 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    int blk = blockIdx.x;
+    auto put = [&](int64_t i, float v) {
+        a.G[i] = v;
+        if (a.G2) a.G2[i] = v;
+    };
+    if (blk < kGradTileBlocks) {
+        int tile = blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
+        if (tile >= kTilesC + 2 * kTilesH) return;
+        const float *A, *D;
+        int nc = kHH;
+        int64_t w;
+        if (tile < kTilesC) {
+            A = a.ub;
+            D = a.dO;
+            nc = kOut;
+            w = kWc;
+        } else if ((tile -= kTilesC) < kTilesH) {
+            A = a.ua;
+            D = a.dub;
+            w = kWb;
+        } else {
+            tile -= kTilesH;
+            A = a.feat;
+            D = a.dua;
+            w = kWa;
+        }
+        const int m0 = 32 * (tile % (kHH / 32)), n0 = 32 * (tile / (kHH / 32));
+        const int r = lane & 31, half = lane >> 5, m = m0 + r, n = n0 + r;
+        f32x16_t acc = {};
+        for (int k0 = 0; k0 < a.B; k0 += 16) {
+            u16x8_t av, bv;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int k = k0 + 8 * half + q;
+                av[q] = k < a.B ? bf16_bits(A[(int64_t)k * kHH + m]) : (uint16_t)0;
+                bv[q] = k < a.B && n < nc ? bf16_bits(D[(int64_t)k * nc + n]) : (uint16_t)0;
+            }
+            acc = mfma(av, bv, acc);
+        }
+        if (n < nc)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) put(w + (int64_t)(m0 + c_row(i, lane)) * nc + n, acc[i]);
+        return;
+    }
+    blk -= kGradTileBlocks;
+    if (blk < kGradBiasBlocks) {
+        int i = blk * kGradThreads + tid;
+        const float *D = a.dO;
+        int nc = kOut;
+        int64_t b = kBc;
+        if (i >= kOut) {
+            i -= kOut;
+            nc = kHH;
+            D = i < kHH ? a.dub : a.dua;
+            b = i < kHH ? kBb : kBa;
+            if (i >= kHH) i -= kHH;
+            if (i >= kHH) return;
+        }
+        float s = 0.0f;
+#pragma unroll 8
+        for (int k = 0; k < a.B; ++k) s += D[(int64_t)k * nc + i];
+        put(b + i, s);
+        return;
+    }
+    blk -= kGradBiasBlocks;
+    if (blk == 0) {
+        float *s = &sh[0][0];
+        float v = 0.0f;
+        for (int t = tid; t < a.n_targets; t += kGradThreads) v += a.nll[t];
+        s[tid] = v;
+        __syncthreads();
+        for (int w = kGradThreads / 2; w > 0; w >>= 1) {
+            if (tid < w) s[tid] += s[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) {
+            a.loss[0] = s[0] / (float)a.n_targets;
+            if (a.loss2) a.loss2[0] = s[0] / (float)a.n_targets;
+        }
+        return;
+    }
+    // encoder: threads 0-127 channel c0, 128-255 channel c0 + 1; k = hidden unit
+    const int c0 = 2 * (blk - 1), half = tid >> 7, c = c0 + half, k = tid & (kH1 - 1);
+    float w1[kIn];
+#pragma unroll
+    for (int i = 0; i < kIn; ++i) w1[i] = bf16_val(a.T[kT1 + k * kInPad + i]);
+    const float b1 = a.P[kB1 + k], w2 = bf16_val(a.T[kT2 + (int64_t)c * kH1 + k]);
+    float s = 0.0f, sb = 0.0f, p[kIn + 1] = {0, 0, 0, 0, 0, 0, 0};
+    for (int b0 = 0; b0 < a.B; b0 += kGradTile) {
+        const int nb = min(kGradTile, a.B - b0);
+        __syncthreads();
+        // per (object, channel): the point as read and as BF16, and the channel's gradient
+        for (int i = tid; i < 2 * nb; i += kGradThreads) {
+            const int b = b0 + (i >> 1), cc = c0 + (i & 1);
+            const int64_t id = (int64_t)b * kH2 + cc;
+            const float *xp = a.x + ((int64_t)b * a.Np + a.arg[id]) * kIn;
+            const u16x8_t xr = input_row(xp);
+#pragma unroll
+            for (int q = 0; q < kIn; ++q) {
+                sh[i][q] = bf16_val(xr[q]);
+                sh[i][kIn + q] = q < 3 ? xp[q] * kInvSP : xp[q];
+            }
+            sh[i][2 * kIn] = a.feat[id] > 0.0f ? a.dfeat[id] : 0.0f;
+        }
+        __syncthreads();
+        for (int b = 0; b < nb; ++b) {
+            const float *v = sh[2 * b + half];
+            float z = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kIn; ++i) z = fmaf(v[i], w1[i], z);
+            const float h = bf16_val(bf16_bits(fmaxf(z + b1, 0.0f))), g = v[2 * kIn];
+            s = fmaf(h, g, s);
+            sb += g;
+            const float d = h <= 0.0f ? 0.0f : w2 * g;
+            if (d != 0.0f) {  // also keeps an infinite input of a cut unit out of the sum
+#pragma unroll
+                for (int i = 0; i < kIn; ++i) p[i] = fmaf(v[kIn + i], d, p[i]);
+                p[kIn] += d;
             }
         }
     }
-    dO[id] = g * inv_T;
-}
-
-// one workgroup of 256: fixed-order sum of the per-target NLL
-__global__ __launch_bounds__(256) void k_loss_sum(const float *__restrict__ nll, int T, float *__restrict__ loss)
-{
-    __shared__ float s[256];
-    float a = 0.0f;
-    for (int t = threadIdx.x; t < T; t += 256) a += nll[t];
-    s[threadIdx.x] = a;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss[0] = s[0] / (float)T;
-}
-
-// ---- encoder backward (sparse through the max-pool) ---------------------------
-// thread per (object, channel): the channel's gradient and the H1 row of its argmax point
-__global__ void k_enc_bwd_sel(const float *__restrict__ x, int Np, const uint16_t *__restrict__ T,
-                              const float *__restrict__ P, const float *__restrict__ feat,
-                              const int32_t *__restrict__ arg, const float *__restrict__ dfeat, int B,
-                              float *__restrict__ h1sel, float *__restrict__ gsel)
-{
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= B * kH2) return;
-    const int b = id / kH2;
-    gsel[id] = feat[id] > 0.0f ? dfeat[id] : 0.0f;
-    const u16x8_t xa = input_row(x + ((int64_t)b * Np + arg[id]) * kIn);
-    float xin[kIn];
+    put(kW2 + (int64_t)k * kH2 + c, s);
+    if (k == 0) put(kB2 + c, sb);
 #pragma unroll
-    for (int i = 0; i < kIn; ++i) xin[i] = bf16_val(xa[i]);
-    for (int k = 0; k < kH1; ++k) {
-        float z = 0.0f;
-#pragma unroll
-        for (int i = 0; i < kIn; ++i) z = fmaf(xin[i], bf16_val(T[kT1 + k * kInPad + i]), z);
-        h1sel[(int64_t)id * kH1 + k] = bf16_val(bf16_bits(fmaxf(z + P[kB1 + k], 0.0f)));
-    }
+    for (int i = 0; i <= kIn; ++i) a.part[((int64_t)k * (kIn + 1) + i) * kH2 + c] = p[i];
 }
 
-// thread per (channel c, hidden k): dW2[k][c], and db2[c] on k == 0
-__global__ void k_enc_bwd_w2(const float *__restrict__ h1sel, const float *__restrict__ gsel, int B,
-                             float *__restrict__ G)
+// dW1[0..5][k] and db1[k]: workgroup per hidden unit k, a thread per channel's part
+__global__ __launch_bounds__(kH2) void k_w1(const float *__restrict__ part, float *__restrict__ G,
+                                            float *__restrict__ G2)
 {
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= kH2 * kH1) return;
-    const int c = id / kH1, k = id % kH1;
-    float s = 0.0f, sb = 0.0f;
-    for (int b = 0; b < B; ++b) {
-        const float g = gsel[b * kH2 + c];
-        s = fmaf(h1sel[((int64_t)b * kH2 + c) * kH1 + k], g, s);
-        sb += g;
-    }
-    G[kW2 + (int64_t)k * kH2 + c] = s;
-    if (k == 0) G[kB2 + c] = sb;
-}
-
-// workgroup per hidden unit k: dW1[0..5][k] and db1[k] over all (object, channel)
-__global__ __launch_bounds__(256) void k_enc_bwd_w1(const float *__restrict__ x, int Np,
-                                                    const uint16_t *__restrict__ T,
-                                                    const float *__restrict__ h1sel,
-                                                    const float *__restrict__ gsel,
-                                                    const int32_t *__restrict__ arg, int B,
-                                                    float *__restrict__ G)
-{
-    __shared__ float s[kIn + 1][256];
+    __shared__ float s[kIn + 1][kH2 / 64];
     const int k = blockIdx.x, tid = threadIdx.x;
-    float a[kIn + 1] = {0, 0, 0, 0, 0, 0, 0};
-    for (int id = tid; id < B * kH2; id += 256) {
-        if (h1sel[(int64_t)id * kH1 + k] <= 0.0f) continue;
-        const int b = id / kH2, c = id % kH2;
-        const float d = bf16_val(T[kT2 + (int64_t)c * kH1 + k]) * gsel[id];
-        if (d == 0.0f) continue;
-        const float *xp = x + ((int64_t)b * Np + arg[id]) * kIn;
-        a[0] = fmaf(xp[0] * kInvSP, d, a[0]);
-        a[1] = fmaf(xp[1] * kInvSP, d, a[1]);
-        a[2] = fmaf(xp[2] * kInvSP, d, a[2]);
-        a[3] = fmaf(xp[3], d, a[3]);
-        a[4] = fmaf(xp[4], d, a[4]);
-        a[5] = fmaf(xp[5], d, a[5]);
-        a[6] += d;
-    }
 #pragma unroll
-    for (int i = 0; i <= kIn; ++i) s[i][tid] = a[i];
+    for (int i = 0; i <= kIn; ++i) {
+        float v = part[((int64_t)k * (kIn + 1) + i) * kH2 + tid];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if ((tid & 63) == 0) s[i][tid >> 6] = v;
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) {
-#pragma unroll
-            for (int i = 0; i <= kIn; ++i) s[i][tid] += s[i][tid + w];
-        }
-        __syncthreads();
-    }
     if (tid <= kIn) {
-        if (tid < kIn) G[kW1 + (int64_t)tid * kH1 + k] = s[tid][0];
-        else G[kB1 + k] = s[kIn][0];
+        const float v = (s[tid][0] + s[tid][1]) + (s[tid][2] + s[tid][3]);
+        const int64_t at = tid < kIn ? kW1 + (int64_t)tid * kH1 + k : kB1 + k;
+        G[at] = v;
+        if (G2) G2[at] = v;
     }
 }
 
@@ -729,32 +886,18 @@ struct lg_prop {
     float *P, *G, *Mo, *Vo;       // [kNParams]
     uint16_t *T;                  // [kNT]
     unsigned long long *keys;     // [maxB][256], all 0 between forward passes
-    bool keys_dirty = false;      // a forward pass stopped between k_encode and k_pool_finish
+    bool keys_dirty = false;      // a forward pass stopped between k_encode and k_head
     float *feat, *ua, *ub, *out;  // [maxB][256] x3, [maxB][152]
     float *dO, *dub, *dua, *dfeat;
     int32_t *arg;                 // [maxB][256]
-    float *nll, *resp;            // [maxT], [maxT][8]
-    float *h1sel, *gsel;          // [maxB][256][128], [maxB][256]
+    float *nll;                   // [maxT]
+    float *part;                  // [128][7][256], see k_grads
     float *loss;                  // [1]
 };
 
 namespace {
 
 hipStream_t st(void *s) { return reinterpret_cast<hipStream_t>(s); }
-
-template <typename TB, int EPI>
-void gemm(hipStream_t s, int Mr, int Nc, int K, const float *A, int64_t a_ms, int64_t a_ks, const TB *Bm,
-          int64_t b_ks, int64_t b_ns, const float *bias, const float *mask, int64_t mask_ld, float *C, int64_t ldc)
-{
-    const bool kc = std::is_same<TB, uint16_t>::value && a_ks == 1 && b_ks == 1 && K % 16 == 0 && a_ms % 4 == 0 &&
-                    b_ns % 8 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)Bm & 15) == 0;
-    if (kc)
-        hipLaunchKernelGGL((k_gemm<TB, EPI, true>), dim3(blocks(Nc, 32), blocks(Mr, 32)), dim3(64), 0, s, Mr, Nc, K,
-                           A, a_ms, a_ks, Bm, b_ks, b_ns, bias, mask, mask_ld, C, ldc);
-    else
-        hipLaunchKernelGGL((k_gemm<TB, EPI, false>), dim3(blocks(Nc, 32), blocks(Mr, 32)), dim3(64), 0, s, Mr, Nc,
-                           K, A, a_ms, a_ks, Bm, b_ks, b_ns, bias, mask, mask_ld, C, ldc);
-}
 
 lg_status check_batch(const lg_prop *p, const float *x, int B, int Np)
 {
@@ -765,57 +908,42 @@ lg_status check_batch(const lg_prop *p, const float *x, int B, int Np)
     return LG_OK;
 }
 
-lg_status forward(lg_prop *p, const float *x, int B, int Np, hipStream_t s)
+// out2, feat2, arg2: the caller's copies of the outputs, or null
+lg_status forward(lg_prop *p, const float *x, int B, int Np, hipStream_t s, float *out2 = nullptr,
+                  float *feat2 = nullptr, int32_t *arg2 = nullptr)
 {
-    // k_pool_finish leaves the keys it read at 0, so the next pass needs no fill
+    // k_head leaves the keys it read at 0, so the next pass needs no fill
     if (p->keys_dirty)
         hipLaunchKernelGGL(k_fill_u64, dim3(blocks((int64_t)p->max_batch * kH2, 256)), dim3(256), 0, s, p->keys,
                            (int64_t)p->max_batch * kH2);
     p->keys_dirty = true;
-    hipLaunchKernelGGL(k_encode, dim3(blocks(Np, kEncChunk), B), dim3(kEncThreads), 0, s, x, Np, p->T, p->P,
-                       p->keys);
-    hipLaunchKernelGGL(k_pool_finish, dim3(blocks((int64_t)B * kH2, 256)), dim3(256), 0, s, p->keys, B * kH2, p->P,
-                       p->feat, p->arg);
+    // Steps per wave: as many as keep two workgroups (the LDS of W2 allows two)
+    // on each of 256 CUs; fewer objects take shorter workgroups, each of which
+    // stages W2 again (32 objects of 2,048 points: 4 steps 34 us, 1 step 14 us).
+    int steps = kEncMaxSteps;
+    while (steps > 1 && (int64_t)B * blocks(Np, kEncStep * steps) < 512) steps >>= 1;
+    hipLaunchKernelGGL(k_encode, dim3(blocks(Np, kEncStep * steps), B), dim3(kEncThreads), 0, s, x, Np, steps, p->T,
+                       p->P, p->keys);
+    hipLaunchKernelGGL(k_head, dim3(blocks(B, 32)), dim3(kHeadThreads), 0, s, p->keys, B, p->P, p->T, p->feat, p->arg,
+                       p->ua, p->ub, p->out, feat2, arg2, out2);
     if (hipPeekAtLastError() == hipSuccess) p->keys_dirty = false;
-    gemm<uint16_t, kEpiBiasRelu>(s, B, kHH, kH2, p->feat, kH2, 1, p->T + kTa, 1, kH2, p->P + kBa, nullptr, 0, p->ua,
-                                 kHH);
-    gemm<uint16_t, kEpiBiasRelu>(s, B, kHH, kHH, p->ua, kHH, 1, p->T + kTb, 1, kHH, p->P + kBb, nullptr, 0, p->ub,
-                                 kHH);
-    gemm<uint16_t, kEpiBias>(s, B, kOut, kHH, p->ub, kHH, 1, p->T + kTc, 1, kHH, p->P + kBc, nullptr, 0, p->out,
-                             kOut);
     LG_HIP(hipGetLastError());
     return LG_OK;
 }
 
-lg_status backward(lg_prop *p, const float *x, int B, int Np, const float *tg, const int32_t *off, int T,
-                   hipStream_t s)
+// loss2, grad2: the caller's copies, or null
+lg_status backward(lg_prop *p, const float *x, int B, int Np, const float *tg, const int32_t *off, int T, float *loss2,
+                   float *grad2, hipStream_t s)
 {
     lg_status e = forward(p, x, B, Np, s);
     if (e != LG_OK) return e;
-    hipLaunchKernelGGL(k_nll, dim3(blocks(T, 256)), dim3(256), 0, s, p->out, tg, off, B, T, p->nll, p->resp);
-    hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(256), 0, s, p->nll, T, p->loss);
-    hipLaunchKernelGGL(k_dout, dim3(blocks((int64_t)B * kOut, 256)), dim3(256), 0, s, p->out, tg, off, p->resp, B,
-                       1.0f / (float)T, p->dO);
-    float *G = p->G;
-    // output layer
-    gemm<float, kEpiNone>(s, kHH, kOut, B, p->ub, 1, kHH, p->dO, kOut, 1, nullptr, nullptr, 0, G + kWc, kOut);
-    hipLaunchKernelGGL(k_colsum, dim3(blocks(kOut, 256)), dim3(256), 0, s, p->dO, B, kOut, (int64_t)kOut, G + kBc);
-    gemm<uint16_t, kEpiMask>(s, B, kHH, kOut, p->dO, kOut, 1, p->T + kTc, kHH, 1, nullptr, p->ub, kHH, p->dub, kHH);
-    // second head layer
-    gemm<float, kEpiNone>(s, kHH, kHH, B, p->ua, 1, kHH, p->dub, kHH, 1, nullptr, nullptr, 0, G + kWb, kHH);
-    hipLaunchKernelGGL(k_colsum, dim3(blocks(kHH, 256)), dim3(256), 0, s, p->dub, B, kHH, (int64_t)kHH, G + kBb);
-    gemm<uint16_t, kEpiMask>(s, B, kHH, kHH, p->dub, kHH, 1, p->T + kTb, kHH, 1, nullptr, p->ua, kHH, p->dua, kHH);
-    // first head layer
-    gemm<float, kEpiNone>(s, kH2, kHH, B, p->feat, 1, kH2, p->dua, kHH, 1, nullptr, nullptr, 0, G + kWa, kHH);
-    hipLaunchKernelGGL(k_colsum, dim3(blocks(kHH, 256)), dim3(256), 0, s, p->dua, B, kHH, (int64_t)kHH, G + kBa);
-    gemm<uint16_t, kEpiNone>(s, B, kH2, kHH, p->dua, kHH, 1, p->T + kTa, kH2, 1, nullptr, nullptr, 0, p->dfeat,
-                             kH2);
-    // encoder through the max-pool
-    hipLaunchKernelGGL(k_enc_bwd_sel, dim3(blocks((int64_t)B * kH2, 256)), dim3(256), 0, s, x, Np, p->T, p->P,
-                       p->feat, p->arg, p->dfeat, B, p->h1sel, p->gsel);
-    hipLaunchKernelGGL(k_enc_bwd_w2, dim3(blocks((int64_t)kH2 * kH1, 256)), dim3(256), 0, s, p->h1sel, p->gsel, B,
-                       G);
-    hipLaunchKernelGGL(k_enc_bwd_w1, dim3(kH1), dim3(256), 0, s, x, Np, p->T, p->h1sel, p->gsel, p->arg, B, G);
+    hipLaunchKernelGGL(k_nll, dim3(B), dim3(kNllThreads), 0, s, p->out, tg, off, B, T, 1.0f / (float)T, p->nll, p->dO);
+    hipLaunchKernelGGL(k_head_bwd, dim3(blocks(B, 32)), dim3(kHeadThreads), 0, s, B, p->T, p->dO, p->ua, p->ub, p->dub,
+                       p->dua, p->dfeat);
+    const GradArgs a{x,     p->feat, p->ua, p->ub, p->dO, p->dub, p->dua,  p->dfeat, p->nll,  p->P, p->T,
+                     p->arg, p->G,   grad2, p->loss, loss2, p->part, B, Np, T};
+    hipLaunchKernelGGL(k_grads, dim3(kGradBlocks), dim3(kGradThreads), 0, s, a);
+    hipLaunchKernelGGL(k_w1, dim3(kH1), dim3(kH2), 0, s, p->part, p->G, grad2);
     LG_HIP(hipGetLastError());
     return LG_OK;
 }
@@ -850,8 +978,8 @@ lg_status lg_prop_create(const lg_prop_params *params, void *stream, lg_prop **o
     const size_t oF = take((size_t)B * kH2 * 4), oUa = take((size_t)B * kHH * 4), oUb = take((size_t)B * kHH * 4);
     const size_t oO = take((size_t)B * kOut * 4), oDO = take((size_t)B * kOut * 4);
     const size_t oDub = take((size_t)B * kHH * 4), oDua = take((size_t)B * kHH * 4), oDf = take((size_t)B * kH2 * 4);
-    const size_t oA = take((size_t)B * kH2 * 4), oN = take((size_t)T * 4), oR = take((size_t)T * kM * 4);
-    const size_t oH = take((size_t)B * kH2 * kH1 * 4), oGs = take((size_t)B * kH2 * 4), oL = take(4);
+    const size_t oA = take((size_t)B * kH2 * 4), oN = take((size_t)T * 4);
+    const size_t oPt = take((size_t)kH1 * (kIn + 1) * kH2 * 4), oL = take(4);
     hipError_t e = hipMalloc(&p->slab, off);
     if (e != hipSuccess) {
         delete p;
@@ -874,14 +1002,15 @@ lg_status lg_prop_create(const lg_prop_params *params, void *stream, lg_prop **o
     p->dfeat = (float *)(base + oDf);
     p->arg = (int32_t *)(base + oA);
     p->nll = (float *)(base + oN);
-    p->resp = (float *)(base + oR);
-    p->h1sel = (float *)(base + oH);
-    p->gsel = (float *)(base + oGs);
+    p->part = (float *)(base + oPt);
     p->loss = (float *)(base + oL);
     hipStream_t s = st(stream);
     hipLaunchKernelGGL(k_init, dim3(blocks(kNParams, 256)), dim3(256), 0, s, p->P,
                        (uint32_t)params->seed, (uint32_t)(params->seed >> 32));
-    hipLaunchKernelGGL(k_refresh_bf16, dim3(blocks(kNT, 256)), dim3(256), 0, s, p->P, p->T);
+    static_assert(kNT % 4 == 0, "the copies are filled 8 bytes at a time");
+    hipLaunchKernelGGL(k_fill_u64, dim3(blocks(kNT / 4, 256)), dim3(256), 0, s,
+                       reinterpret_cast<unsigned long long *>(p->T), kNT / 4);
+    hipLaunchKernelGGL(k_refresh_bf16, dim3(blocks(kNParams, 256)), dim3(256), 0, s, p->P, p->T);
     hipLaunchKernelGGL(k_fill_u64, dim3(blocks((int64_t)B * kH2, 256)), dim3(256), 0, s, p->keys, (int64_t)B * kH2);
     e = hipMemsetAsync(p->Mo, 0, kNParams * 4, s);
     if (e == hipSuccess) e = hipMemsetAsync(p->Vo, 0, kNParams * 4, s);
@@ -921,7 +1050,7 @@ lg_status lg_prop_set_params(lg_prop *p, const float *host_in)
     LG_HIP(hipMemcpy(p->P, host_in, kNParams * 4, hipMemcpyHostToDevice));
     LG_HIP(hipMemset(p->Mo, 0, kNParams * 4));
     LG_HIP(hipMemset(p->Vo, 0, kNParams * 4));
-    hipLaunchKernelGGL(k_refresh_bf16, dim3(blocks(kNT, 256)), dim3(256), 0, 0, p->P, p->T);
+    hipLaunchKernelGGL(k_refresh_bf16, dim3(blocks(kNParams, 256)), dim3(256), 0, 0, p->P, p->T);
     LG_HIP(hipGetLastError());
     LG_HIP(hipDeviceSynchronize());
     p->step = 0;
@@ -934,12 +1063,7 @@ lg_status lg_prop_forward(lg_prop *p, const float *x, int32_t B, int32_t Np, flo
     lg_status e = check_batch(p, x, B, Np);
     if (e != LG_OK) return e;
     hipStream_t s = st(stream);
-    e = forward(p, x, B, Np, s);
-    if (e != LG_OK) return e;
-    if (out) LG_HIP(hipMemcpyAsync(out, p->out, (size_t)B * kOut * 4, hipMemcpyDeviceToDevice, s));
-    if (feat) LG_HIP(hipMemcpyAsync(feat, p->feat, (size_t)B * kH2 * 4, hipMemcpyDeviceToDevice, s));
-    if (arg) LG_HIP(hipMemcpyAsync(arg, p->arg, (size_t)B * kH2 * 4, hipMemcpyDeviceToDevice, s));
-    return LG_OK;
+    return forward(p, x, B, Np, s, out, feat, arg);
 }
 
 lg_status lg_prop_backward(lg_prop *p, const float *x, int32_t B, int32_t Np, const float *targets,
@@ -950,11 +1074,7 @@ lg_status lg_prop_backward(lg_prop *p, const float *x, int32_t B, int32_t Np, co
     if (!targets || !offsets) return fail(LG_EINVAL, "null targets or offsets");
     if (T < 1 || T > p->max_targets) return fail(LG_EINVAL, "target count outside [1, max_targets]");
     hipStream_t s = st(stream);
-    e = backward(p, x, B, Np, targets, offsets, T, s);
-    if (e != LG_OK) return e;
-    if (loss) LG_HIP(hipMemcpyAsync(loss, p->loss, 4, hipMemcpyDeviceToDevice, s));
-    if (grad) LG_HIP(hipMemcpyAsync(grad, p->G, kNParams * 4, hipMemcpyDeviceToDevice, s));
-    return LG_OK;
+    return backward(p, x, B, Np, targets, offsets, T, loss, grad, s);
 }
 
 lg_status lg_prop_adam(lg_prop *p, float lr, float beta1, float beta2, float eps, void *stream)
@@ -966,9 +1086,8 @@ lg_status lg_prop_adam(lg_prop *p, float lr, float beta1, float beta2, float eps
     p->step += 1;
     const double bc1 = 1.0 - pow((double)beta1, (double)p->step), bc2 = 1.0 - pow((double)beta2, (double)p->step);
     const float lr_t = (float)(lr * sqrt(bc2) / bc1);
-    hipLaunchKernelGGL(k_adam, dim3(blocks(kNParams, 256)), dim3(256), 0, s, p->P, p->G, p->Mo, p->Vo, lr_t, beta1,
-                       beta2, eps);
-    hipLaunchKernelGGL(k_refresh_bf16, dim3(blocks(kNT, 256)), dim3(256), 0, s, p->P, p->T);
+    hipLaunchKernelGGL(k_adam, dim3(blocks(kNParams, 256)), dim3(256), 0, s, p->P, p->G, p->Mo, p->Vo, p->T, lr_t,
+                       beta1, beta2, eps);
     LG_HIP(hipGetLastError());
     return LG_OK;
 }
