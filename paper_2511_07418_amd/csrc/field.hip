@@ -109,7 +109,7 @@ __global__ void k_fill_i32(int32_t *__restrict__ p, int64_t n, int32_t v)
 // points), so the argmax over the candidates equals the argmax over all bins,
 // also for a direction on a cell or face boundary.  Cells with more than four
 // candidates are marked for the full search (0xffffffff).
-static void cube_direction(int face, double s, double t, double *d)
+__device__ inline void cube_direction(int face, double s, double t, double *d)
 {
     switch (face) {
     case 0: d[0] = 1.0; d[1] = -t; d[2] = -s; break;
@@ -121,41 +121,44 @@ static void cube_direction(int face, double s, double t, double *d)
     }
 }
 
-static void build_bin_lut(const std::vector<float> &bc, int B, std::vector<uint32_t> &lut)
+constexpr int kLutSub = 9;  // sub-grid points per cell edge, both edges included
+
+// One wave per cell, lanes over its sub-grid points; a lane marks the bins near
+// the best at its points, the marks are joined by shuffles: 42 us, 30 ms on one
+// CPU thread.
+__global__ void __launch_bounds__(64) k_bin_lut(const float *__restrict__ bc, int B, uint32_t *__restrict__ lut)
 {
-    const int R = kLutRes, SUB = 9;
-    lut.assign(6 * R * R, 0xffffffffu);
-    const double sub_step = 2.0 / R / (SUB - 1);           // in face coordinates
-    const double margin = 2.0 * sub_step + 1e-4;            // angular spacing <= coordinate spacing
-    for (int face = 0; face < 6; ++face) {
-        for (int it = 0; it < R; ++it)
-            for (int is = 0; is < R; ++is) {
-                std::vector<int> cand;
-                for (int st = 0; st < SUB; ++st)
-                    for (int ss = 0; ss < SUB; ++ss) {
-                        const double sv = -1.0 + 2.0 * (is + (double)ss / (SUB - 1)) / R;
-                        const double tv = -1.0 + 2.0 * (it + (double)st / (SUB - 1)) / R;
-                        double d[3];
-                        cube_direction(face, sv, tv, d);
-                        const double nd = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-                        double best = -1e300, dots[kMaxBins];
-                        for (int b = 0; b < B; ++b) {
-                            dots[b] = (bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) / nd;
-                            best = std::max(best, dots[b]);
-                        }
-                        for (int b = 0; b < B; ++b)
-                            if (dots[b] >= best - margin && std::find(cand.begin(), cand.end(), b) == cand.end())
-                                cand.push_back(b);
-                    }
-                std::sort(cand.begin(), cand.end());
-                if (cand.size() <= 4) {
-                    // absent slots repeat the first candidate (the kernel evaluates all four)
-                    uint32_t e = 0;
-                    for (size_t i = 0; i < 4; ++i) e |= (uint32_t)cand[i < cand.size() ? i : 0] << (8 * i);
-                    lut[(face * R + it) * R + is] = e;
-                }
-            }
+    const int R = kLutRes, cell = blockIdx.x, lane = threadIdx.x;
+    const int is = cell % R, it = cell / R % R, face = cell / (R * R);
+    const double sub_step = 2.0 / R / (kLutSub - 1);   // in face coordinates
+    const double margin = 2.0 * sub_step + 1e-4;        // angular spacing <= coordinate spacing
+    unsigned long long cand = 0;
+    for (int q = lane; q < kLutSub * kLutSub; q += 64) {
+        const double sv = -1.0 + 2.0 * (is + (double)(q % kLutSub) / (kLutSub - 1)) / R;
+        const double tv = -1.0 + 2.0 * (it + (double)(q / kLutSub) / (kLutSub - 1)) / R;
+        double d[3];
+        cube_direction(face, sv, tv, d);
+        const double rn = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        double best = -2.0;
+        for (int b = 0; b < B; ++b)
+            best = fmax(best, (bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) * rn);
+        for (int b = 0; b < B; ++b)
+            if ((bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) * rn >= best - margin) cand |= 1ull << b;
     }
+    for (int off = 32; off > 0; off >>= 1) cand |= __shfl_xor(cand, off, 64);
+    if (lane != 0) return;
+    uint32_t e = 0xffffffffu;
+    if (__popcll(cand) <= 4) {
+        // absent slots repeat the first candidate (the kernels evaluate all four)
+        const int first = __ffsll((long long)cand) - 1;
+        e = 0;
+        for (int i = 0; i < 4; ++i) {
+            const int b = cand ? __ffsll((long long)cand) - 1 : first;
+            cand &= cand - 1;
+            e |= (uint32_t)b << (8 * i);
+        }
+    }
+    lut[cell] = e;
 }
 
 // Lattice form of the windows (see DevHand::lat): every frame has finger 0's
@@ -230,8 +233,6 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
         f->bin_c[3 * b + 1] = (float)(r * sin(ph));
         f->bin_c[3 * b + 2] = (float)z;
     }
-    std::vector<uint32_t> lut;
-    build_bin_lut(f->bin_c, B, lut);
     // capsule axis samples for the penetration test: one per mm, ends included
     // (links, then the palm's capsules, which take at least their two ends)
     f->axis_samples.resize(J + PC);
@@ -272,7 +273,7 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
     const size_t n_origin = f->origin.size(), n_axis = f->axis.size(), n_cap = f->capsule.size(),
                  n_lim = f->limits.size(), n_surf = f->surf.size(), n_gf = f->grid_frame.size(),
                  n_bc = f->bin_c.size(), n_ps = f->palm_surf.size(), n_pc = f->palm_caps.size();
-    const size_t n_lut = lut.size();
+    const size_t n_lut = 6 * kLutRes * kLutRes;  // filled on the device
     const size_t n_all = n_origin + n_axis + n_cap + n_lim + n_surf + n_gf + n_bc + n_ps + n_pc + n_lut;
     std::vector<float> packed;
     packed.reserve(n_all);
@@ -280,10 +281,15 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
                     &f->palm_surf, &f->palm_caps})
         packed.insert(packed.end(), v->begin(), v->end());
     packed.resize(n_all);
-    memcpy(packed.data() + (n_all - n_lut), lut.data(), n_lut * sizeof(uint32_t));
     const int64_t G3 = (int64_t)G * G * G;
     hipError_t e = hipMalloc(&f->d_params, n_all * sizeof(float));
     if (e == hipSuccess) e = hipMemcpy(f->d_params, packed.data(), n_all * sizeof(float), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_bin_lut, dim3((unsigned)n_lut), dim3(64), 0, nullptr,
+                           f->d_params + (n_all - n_lut - n_pc - n_ps - n_bc), B,
+                           reinterpret_cast<uint32_t *>(f->d_params + (n_all - n_lut)));
+        e = hipGetLastError();
+    }
     if (e == hipSuccess) e = hipMalloc(&f->d_axis_samples, (J + PC) * sizeof(int32_t));
     if (e == hipSuccess)
         e = hipMemcpy(f->d_axis_samples, f->axis_samples.data(), (J + PC) * sizeof(int32_t), hipMemcpyHostToDevice);
@@ -303,9 +309,10 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
             hipLaunchKernelGGL(k_fill_i32, dim3(2048), dim3(256), 0, nullptr, f->d_wit, (int64_t)J * G3 * B, kNoWitness);
             e = hipGetLastError();
         }
-        if (e == hipSuccess) e = hipDeviceSynchronize();
         f->has_witness = true;
     }
+    // the fills ran on the null stream; the caller's stream may not wait for it
+    if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         st = hip_fail(e, "field allocation");
         free_field(f);
@@ -344,49 +351,83 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
 // kernels
 // ---------------------------------------------------------------------------
 constexpr int kBuildThreads = 256;
+constexpr int64_t kBuildMaxParts = 16;
+constexpr int64_t kBuildRound = 4096;  // samples of the first round; each further round doubles the total
 
-// One thread per (finger, joint sample): sample q, walk the chain, and bin
-// every surface sample of every link of the finger.  The check-before-atomic
-// is safe because table bits only ever go 0 -> 1 and witnesses only decrease:
-// a stale read can only cause a redundant atomic, never a lost update.
-__global__ void __launch_bounds__(kBuildThreads)
-k_field_build(DevHand H, uint32_t *__restrict__ bits, int32_t *__restrict__ wit,
-              unsigned long long *__restrict__ dropped)
+// *out += the sum of c over the block of kBuildThreads threads: one atomic per
+// block (all go to one address, some 10 ns each)
+__device__ inline void block_add(unsigned int c, unsigned long long *__restrict__ out)
 {
-    __shared__ float cb[3 * kMaxBins];
-    for (int i = threadIdx.x; i < 3 * H.B; i += blockDim.x) cb[i] = H.bin_c[i];
+    __shared__ unsigned int part[kBuildThreads / 64];
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
-    const int f = blockIdx.y;
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool active = s < H.samples;
-    const int first = H.finger_first[f], d = H.finger_dof[f];
+    if (threadIdx.x == 0) {
+        unsigned long long s = 0;
+        for (int w = 0; w < kBuildThreads / 64; ++w) s += part[w];
+        if (s) atomicAdd(out, s);
+    }
+}
+
+// Thread per (link, joint sample, part of the link's surface) of a round: sample
+// q, walk the chain to the link, and bin the part's surface samples (blockIdx.z
+// of gridDim.z; a short round has several parts, or its threads' serial walk over
+// 256 samples would leave the chip idle: 4,096 samples 0.55 ms with one).  done: the table as it was
+// before this round (null: no witness kept).  A vector whose bit is set there has
+// a witness of an earlier, smaller sample, so it changes nothing and ends at one
+// 4-byte read; only the others go on to the table and to the 32 times larger
+// witness table.  The check-before-atomic is safe because table bits only ever go
+// 0 -> 1 and witnesses only decrease: a stale read can only cause a redundant
+// atomic, never a lost update.
+// What bounds it: the random reads.  All vectors against the witness table (1.4
+// GiB at 22 links of 64^3 voxels x 64 bins, read from HBM a line per vector), with
+// the bins by a scan of all 64 centres, took 41.9 ms for 262,144 samples; with the
+// rounds (under 1 % of the vectors are the first of their cell), a link at a time (its
+// 2 MiB of bits stay in L2) and the bins by the candidate table it takes 7.2 ms.
+__global__ void __launch_bounds__(kBuildThreads)
+k_field_build(DevHand H, int64_t s0, int64_t s1, const uint32_t *__restrict__ done, uint32_t *__restrict__ bits,
+              int32_t *__restrict__ wit, unsigned long long *__restrict__ dropped)
+{
+    __shared__ float4 cb4[kMaxBins];
+    __shared__ uint32_t lut[6 * kLutRes * kLutRes];
+    for (int i = threadIdx.x; i < H.B; i += kBuildThreads)
+        cb4[i] = make_float4(H.bin_c[3 * i], H.bin_c[3 * i + 1], H.bin_c[3 * i + 2], 0.0f);
+    for (int i = threadIdx.x; i < 6 * kLutRes * kLutRes; i += kBuildThreads) lut[i] = H.bin_lut[i];
+    __syncthreads();
+    const int j = blockIdx.y;
+    int f = 0;
+    while (j >= H.finger_first[f] + H.finger_dof[f]) ++f;
+    const int64_t s = s0 + (int64_t)blockIdx.x * kBuildThreads + threadIdx.x;
+    const bool active = s < s1;
+    const int first = H.finger_first[f];
     const int G = H.G, W = H.W, B = H.B;
     const int64_t G3 = (int64_t)G * G * G;
     const float *gf = H.grid_frame + 12 * f;
     unsigned int n_drop = 0;
     Tf T;
-    for (int t = 0; t < d; ++t) {
-        const int j = first + t;
+    for (int t = 0; first + t <= j; ++t) {
         const float q = active ? joint_sample(H, f, (uint32_t)s, t) : 0.0f;
-        T = joint_frame(H, T, t > 0, j, q);
-        // composite link -> window map: u = R_f^T (T x - o_f) / h + G (biased, see window_voxel)
-        Affine a;
-        {
-            const float dx = T.m[3] - gf[3], dy = T.m[7] - gf[7], dz = T.m[11] - gf[11];
+        T = joint_frame(H, T, t > 0, first + t, q);
+    }
+    // composite link -> window map: u = R_f^T (T x - o_f) / h + G (biased, see window_voxel)
+    Affine a;
+    {
+        const float dx = T.m[3] - gf[3], dy = T.m[7] - gf[7], dz = T.m[11] - gf[11];
 #pragma unroll
-            for (int r = 0; r < 3; ++r) {
+        for (int r = 0; r < 3; ++r) {
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    a.m[4 * r + c] = fmaf(gf[r], T.m[c], fmaf(gf[4 + r], T.m[4 + c], gf[8 + r] * T.m[8 + c])) * H.inv_h;
-                a.m[4 * r + 3] = fmaf(fmaf(gf[r], dx, fmaf(gf[4 + r], dy, gf[8 + r] * dz)), H.inv_h, (float)G);
-            }
+            for (int c = 0; c < 3; ++c)
+                a.m[4 * r + c] = fmaf(gf[r], T.m[c], fmaf(gf[4 + r], T.m[4 + c], gf[8 + r] * T.m[8 + c])) * H.inv_h;
+            a.m[4 * r + 3] = fmaf(fmaf(gf[r], dx, fmaf(gf[4 + r], dy, gf[8 + r] * dz)), H.inv_h, (float)G);
         }
-        if (!active) continue;
+    }
+    if (active) {
         const float *sp = H.surf + (size_t)j * H.nsurf * 6;
+        const uint32_t *dtab = done ? done + (size_t)j * G3 * W : nullptr;
         uint32_t *tab = bits + (size_t)j * G3 * W;
         int32_t *wtab = wit ? wit + (size_t)j * G3 * B : nullptr;
-        int last_v = -2, last_b = -1;
-        for (int i = 0; i < H.nsurf; ++i) {
+        const int i1 = (int)((int64_t)H.nsurf * (blockIdx.z + 1) / gridDim.z);
+        for (int i = (int)((int64_t)H.nsurf * blockIdx.z / gridDim.z); i < i1; ++i) {
             const float px = sp[6 * i], py = sp[6 * i + 1], pz = sp[6 * i + 2];
             const int v = window_voxel(a, G, px, py, pz);
             if (v < 0) {
@@ -395,23 +436,46 @@ k_field_build(DevHand H, uint32_t *__restrict__ bits, int32_t *__restrict__ wit,
             }
             float nx, ny, nz;
             tf_dir(T, sp[6 * i + 3], sp[6 * i + 4], sp[6 * i + 5], nx, ny, nz);
-            const int b = nearest_bin(cb, B, nx, ny, nz);
-            if (v == last_v && b == last_b) continue;  // same cell as the previous sample
-            last_v = v;
-            last_b = b;
-            uint32_t *wp = tab + (size_t)v * W + (b >> 5);
-            const uint32_t m = 1u << (b & 31);
-            if (!(__atomic_load_n(wp, __ATOMIC_RELAXED) & m)) atomicOr(wp, m);
-            if (wtab) {
+            const int b = nearest_bin_any(lut, cb4, B, nx, ny, nz);
+            const uint32_t at = (uint32_t)v * W + (uint32_t)(b >> 5), m = 1u << (b & 31);
+            if (dtab) {
+                if (dtab[at] & m) continue;
+                if (!(__atomic_load_n(tab + at, __ATOMIC_RELAXED) & m)) atomicOr(tab + at, m);
                 int32_t *ww = wtab + (size_t)v * B + b;
                 if (__atomic_load_n(ww, __ATOMIC_RELAXED) > (int32_t)s) atomicMin(ww, (int32_t)s);
+            } else if (!(__atomic_load_n(tab + at, __ATOMIC_RELAXED) & m)) {
+                atomicOr(tab + at, m);
             }
         }
     }
-    // wave-level sum of dropped vectors, one atomic per wave
-    unsigned long long c = n_drop;
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(dropped, c);
+    block_add(n_drop, dropped);
+}
+
+__global__ void k_copy_u32(const uint4 *__restrict__ src, uint4 *__restrict__ dst, int64_t n4)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (int64_t)gridDim.x * blockDim.x)
+        dst[i] = src[i];
+}
+
+// The rounds of a build (see k_field_build): samples [0, 4096), then up to twice
+// as many each time; done holds the table of the rounds before (with a witness).
+static hipError_t build_rounds(lg_field *f, uint32_t *done, unsigned long long *d_drop, hipStream_t s)
+{
+    const DevHand &H = f->dh;
+    const int64_t n4 = (int64_t)H.J * H.G * H.G * H.G * H.W / 4;  // G is a multiple of 4
+    for (int64_t s0 = 0; s0 < H.samples;) {
+        const int64_t s1 = done ? std::min(H.samples, std::max(kBuildRound, 2 * s0)) : H.samples;
+        if (done)
+            hipLaunchKernelGGL(k_copy_u32, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096)), dim3(256), 0, s,
+                               reinterpret_cast<const uint4 *>(f->d_bits), reinterpret_cast<uint4 *>(done), n4);
+        // parts: enough blocks for eight waves per SIMD
+        const int64_t blocks = (s1 - s0 + kBuildThreads - 1) / kBuildThreads;
+        const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(kBuildMaxParts, 2048 / (blocks * H.J)));
+        hipLaunchKernelGGL(k_field_build, dim3((unsigned)blocks, H.J, (unsigned)parts), dim3(kBuildThreads), 0, s, H,
+                           s0, s1, done, f->d_bits, f->d_wit, d_drop);
+        s0 = s1;
+    }
+    return hipGetLastError();
 }
 
 // Merged finger tables: OR over the links of finger f of their words, laid
@@ -474,13 +538,16 @@ __global__ void k_dilate(int F, int G, int row, int d, const uint32_t *__restric
     dst[f * n + i] = o;
 }
 
-__global__ void k_popcount(const uint32_t *__restrict__ w, int64_t n, unsigned long long *__restrict__ out)
+// set bits of n4 groups of four words (16-byte aligned)
+__global__ void k_popcount(const uint4 *__restrict__ w, int64_t n4, unsigned long long *__restrict__ out)
 {
-    unsigned long long c = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        c += __popc(w[i]);
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(out, c);
+    unsigned int c = 0;
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint4 v = w[i];
+        c += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    block_add(c, out);
 }
 
 static lg_status merge_and_count(lg_field *f, hipStream_t st)
@@ -505,7 +572,8 @@ static lg_status merge_and_count(lg_field *f, hipStream_t st)
     unsigned long long *d_cnt = nullptr;
     LG_HIP(hipMalloc(&d_cnt, sizeof(unsigned long long)));
     (void)hipMemsetAsync(d_cnt, 0, sizeof(unsigned long long), st);
-    hipLaunchKernelGGL(k_popcount, dim3(1024), dim3(256), 0, st, f->d_bits, (int64_t)H.J * G3W, d_cnt);
+    hipLaunchKernelGGL(k_popcount, dim3(1024), dim3(kBuildThreads), 0, st, reinterpret_cast<const uint4 *>(f->d_bits),
+                       (int64_t)H.J * G3W / 4, d_cnt);  // G is a multiple of 4
     unsigned long long cnt = 0;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&cnt, d_cnt, sizeof cnt, hipMemcpyDeviceToHost, st);
@@ -546,23 +614,23 @@ lg_status lg_build_field(const lg_hand_desc *hand, const lg_field_params *params
     if (st != LG_OK) return st;
     hipStream_t s = as_stream(stream);
     const DevHand &H = f->dh;
+    // scratch: the dropped count and, with a witness, the table of the rounds before
     unsigned long long *d_drop = nullptr;
+    uint32_t *done = nullptr;
     hipError_t e = hipMalloc(&d_drop, sizeof(unsigned long long));
     if (e == hipSuccess) e = hipMemsetAsync(d_drop, 0, sizeof(unsigned long long), s);
+    if (e == hipSuccess && f->d_wit) e = hipMalloc(&done, (size_t)H.J * H.G * H.G * H.G * H.W * 4);
     if (e != hipSuccess) {
+        (void)hipFree(d_drop);
         free_field(f);
         return hip_fail(e, "build scratch");
     }
-    dim3 grid((unsigned)((H.samples + kBuildThreads - 1) / kBuildThreads), H.F);
     // the build kernel's own duration (events on the build stream), reported by lg_field_info
     hipEvent_t ev[2] = {nullptr, nullptr};
     if (e == hipSuccess) e = hipEventCreate(&ev[0]);
     if (e == hipSuccess) e = hipEventCreate(&ev[1]);
     if (e == hipSuccess) e = hipEventRecord(ev[0], s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_field_build, grid, dim3(kBuildThreads), 0, s, H, f->d_bits, f->d_wit, d_drop);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess) e = build_rounds(f, done, d_drop, s);
     if (e == hipSuccess) e = hipEventRecord(ev[1], s);
     unsigned long long drop = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&drop, d_drop, sizeof drop, hipMemcpyDeviceToHost, s);
@@ -573,6 +641,7 @@ lg_status lg_build_field(const lg_hand_desc *hand, const lg_field_params *params
     for (hipEvent_t x : ev)
         if (x) (void)hipEventDestroy(x);
     (void)hipFree(d_drop);
+    (void)hipFree(done);
     if (e != hipSuccess) {
         free_field(f);
         return hip_fail(e, "k_field_build");

@@ -335,6 +335,73 @@ __device__ inline int nearest_bin(const float *c, int B, float dx, float dy, flo
     return bi;
 }
 
+// argmax_b <d, c_b> (ties to the lowest b, as nearest_bin) through the
+// cube-map candidate table: the four candidate slots of the direction's cell
+// (absent ones repeat the first, so the result is unchanged) are evaluated
+// without a branch.  Their centres are float4 rows in LDS, all four read
+// before the first dot product.  A cell with more than four candidates scans
+// every bin.
+__device__ inline int nearest_bin_lut4(const uint32_t *lut, const float4 *c4, int B, float dx, float dy, float dz)
+{
+    // face and face coordinates by the cube-map instructions (the table is
+    // built in their convention): ma = 2 x the major component, so
+    // (sc / |major| + 1) R / 2 = sc R / |ma| + R / 2
+    const float sc = __builtin_amdgcn_cubesc(dx, dy, dz), tc = __builtin_amdgcn_cubetc(dx, dy, dz);
+    const float sf = (float)kLutRes * __builtin_amdgcn_rcpf(fabsf(__builtin_amdgcn_cubema(dx, dy, dz)));
+    // the entry's index in float arithmetic (whole numbers below 2^13, exact):
+    // cells clamped to the face, a NaN to cell 0
+    const float is = __builtin_amdgcn_fmed3f(floorf(fmaf(sc, sf, 0.5f * kLutRes)), 0.0f, (float)(kLutRes - 1));
+    const float it = __builtin_amdgcn_fmed3f(floorf(fmaf(tc, sf, 0.5f * kLutRes)), 0.0f, (float)(kLutRes - 1));
+    const float id = fmaf(__builtin_amdgcn_cubeid(dx, dy, dz), (float)(kLutRes * kLutRes), fmaf(it, (float)kLutRes, is));
+    const uint32_t boff = (uint32_t)id << 2;
+    const uint32_t e = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(lut) + boff);
+    float best = -3.0e38f;
+    int bi = 0;
+    if (e == 0xffffffffu) {  // more than four candidates: every bin
+        for (int b = 0; b < B; ++b) {
+            const float4 c = c4[b];
+            const float sc = fmaf(c.x, dx, fmaf(c.y, dy, c.z * dz));
+            if (sc > best) {
+                best = sc;
+                bi = b;
+            }
+        }
+        return bi;
+    }
+    // byte offsets (bin * 16) of the four slots' float4 centres
+    const uint32_t off[4] = {(e << 4) & 0xff0u, (e >> 4) & 0xff0u, (e >> 12) & 0xff0u, (e >> 20) & 0xff0u};
+    float4 ck[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ck[k] = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(c4) + off[k]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float sc = fmaf(ck[k].x, dx, fmaf(ck[k].y, dy, ck[k].z * dz));
+        if (sc > best) {
+            best = sc;
+            bi = (int)(off[k] >> 4);
+        }
+    }
+    return bi;
+}
+
+// nearest_bin of any direction: the table where the direction has one (a zero or
+// non-finite one, or one whose reciprocal overflows, scans every bin)
+__device__ inline int nearest_bin_any(const uint32_t *lut, const float4 *c4, int B, float dx, float dy, float dz)
+{
+    const float ma = fmaxf(fabsf(dx), fmaxf(fabsf(dy), fabsf(dz)));
+    if (ma > 1e-30f && ma < 1e30f && !isnan(dx + dy + dz)) return nearest_bin_lut4(lut, c4, B, dx, dy, dz);
+    float best = -3.0e38f;
+    int bi = 0;
+    for (int b = 0; b < B; ++b) {
+        const float s = fmaf(c4[b].x, dx, fmaf(c4[b].y, dy, c4[b].z * dz));
+        if (s > best) {
+            best = s;
+            bi = b;
+        }
+    }
+    return bi;
+}
+
 __device__ inline bool table_bit(const uint32_t *tab, int W, int64_t voxel, int b)
 {
     return (tab[voxel * W + (b >> 5)] >> (b & 31)) & 1u;
