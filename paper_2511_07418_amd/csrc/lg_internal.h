@@ -191,13 +191,32 @@ __device__ inline void tf_dir(const Tf &T, float px, float py, float pz, float &
     z = fmaf(T.m[8], px, fmaf(T.m[9], py, T.m[10] * pz));
 }
 
+// A B for a B without translation (A's stays)
+__device__ inline Tf tf_rotate(const Tf &A, const Tf &B)
+{
+    Tf C;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            C.m[4 * i + j] = fmaf(A.m[4 * i], B.m[j], fmaf(A.m[4 * i + 1], B.m[4 + j], A.m[4 * i + 2] * B.m[8 + j]));
+        C.m[4 * i + 3] = A.m[4 * i + 3];
+    }
+    return C;
+}
+
+// Frame of a joint of origin o and axis ax given its parent frame P and joint value q.
+__device__ inline Tf joint_frame_at(const float *o, const float *ax, const Tf &P, bool has_parent, float q)
+{
+    Tf O = tf_load(o);
+    Tf base = has_parent ? tf_mul(P, O) : O;
+    return tf_rotate(base, tf_axis_angle(ax[0], ax[1], ax[2], q));
+}
+
 // Frame of joint j given its parent frame P and joint value q.
 __device__ inline Tf joint_frame(const DevHand &H, const Tf &P, bool has_parent, int j, float q)
 {
-    Tf O = tf_load(H.origin + 12 * j);
-    Tf base = has_parent ? tf_mul(P, O) : O;
-    Tf R = tf_axis_angle(H.axis[3 * j], H.axis[3 * j + 1], H.axis[3 * j + 2], q);
-    return tf_mul(base, R);
+    return joint_frame_at(H.origin + 12 * j, H.axis + 3 * j, P, has_parent, q);
 }
 
 // ---- window coordinates and normal bins -------------------------------------
@@ -414,7 +433,9 @@ struct SdfDev {
     const float *v;
 };
 
-// Trilinear SDF at object-frame point y; +inf outside the grid.
+// Trilinear SDF at object-frame point y; +inf outside the grid.  The cell's
+// corners are read as pairs along x (4-byte aligned), by 32-bit offsets from four
+// uniform row addresses where the grid's bytes fit them.
 __device__ inline float sdf_trilinear(const SdfDev &S, float yx, float yy, float yz)
 {
     const float ux = (yx - S.ox) * S.inv_h, uy = (yy - S.oy) * S.inv_h, uz = (yz - S.oz) * S.inv_h;
@@ -422,12 +443,27 @@ __device__ inline float sdf_trilinear(const SdfDev &S, float yx, float yy, float
     if (!((ux >= 0.f) & (ux <= gm) & (uy >= 0.f) & (uy <= gm) & (uz >= 0.f) & (uz <= gm))) return INFINITY;
     const int ix = min((int)ux, S.G - 2), iy = min((int)uy, S.G - 2), iz = min((int)uz, S.G - 2);
     const float fx = ux - ix, fy = uy - iy, fz = uz - iz;
-    const int64_t G = S.G;
-    const float *v = S.v + (iz * G + iy) * G + ix;
-    const float c00 = fmaf(fx, v[1] - v[0], v[0]);
-    const float c10 = fmaf(fx, v[G + 1] - v[G], v[G]);
-    const float c01 = fmaf(fx, v[G * G + 1] - v[G * G], v[G * G]);
-    const float c11 = fmaf(fx, v[G * G + G + 1] - v[G * G + G], v[G * G + G]);
+    typedef float pair_t __attribute__((ext_vector_type(2), aligned(4)));
+    pair_t a00, a10, a01, a11;
+    if (S.G <= 1024) {
+        const uint32_t G = (uint32_t)S.G, o = (__umul24(__umul24(iz, G) + iy, G) + (uint32_t)ix) << 2;
+        const char *v = reinterpret_cast<const char *>(S.v);
+        a00 = *(const pair_t *)(v + o);
+        a10 = *(const pair_t *)(v + 4 * (size_t)G + o);
+        a01 = *(const pair_t *)(v + 4 * (size_t)G * G + o);
+        a11 = *(const pair_t *)(v + 4 * (size_t)G * (G + 1) + o);
+    } else {
+        const int64_t G = S.G;
+        const float *v = S.v + (iz * G + iy) * G + ix;
+        a00 = *(const pair_t *)v;
+        a10 = *(const pair_t *)(v + G);
+        a01 = *(const pair_t *)(v + G * G);
+        a11 = *(const pair_t *)(v + G * G + G);
+    }
+    const float c00 = fmaf(fx, a00.y - a00.x, a00.x);
+    const float c10 = fmaf(fx, a10.y - a10.x, a10.x);
+    const float c01 = fmaf(fx, a01.y - a01.x, a01.x);
+    const float c11 = fmaf(fx, a11.y - a11.x, a11.x);
     const float c0 = fmaf(fy, c10 - c00, c00), c1 = fmaf(fy, c11 - c01, c01);
     return fmaf(fz, c1 - c0, c0);
 }
@@ -525,6 +561,8 @@ LpConst lp_const(int m);
 void chunk_workspace(void *ws, int64_t n_points, int64_t n_poses, int64_t draws, ChunkDesc &c);
 lg_status verdict_batch(const BatchLaunch &b, int km, bool m8, hipStream_t s);  // m8: every chunk has an 8-edge cone
 uint32_t realize_blocks(int64_t max_acc, int F, int n_cu);
-lg_status realize_batch(const BatchLaunch &b, int max_dof, hipStream_t s);
+size_t realize_lds_bytes(int F, int J);
+// self_collision: that of every chunk; lds: the largest realize_lds_bytes
+lg_status realize_batch(const BatchLaunch &b, int max_dof, size_t lds, bool self_collision, hipStream_t s);
 
 }  // namespace lg

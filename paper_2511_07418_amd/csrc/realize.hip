@@ -1,12 +1,15 @@
 // Kinematics optimisation (Sec. 5.5, Eq. 7-8, Phase I and II) and the
-// penetration part of the validity criterion (Sec. 3.2), fused in one kernel.
+// penetration part of the validity criterion (Sec. 3.2), in two kernels: the
+// damped steps need every register (two waves per SIMD), the penetration test is
+// bound by the SDF's scattered reads and wants as many waves as fit; in one kernel
+// its reads waited at two waves per SIMD (470,724 accepted sets of 22 joints: 1.7
+// of 3.1 ms).
 //
-// Lane layout: F lanes per accepted set, lane f realises finger f, so a wave
-// covers 64 / F sets (the 64 mod F lanes left over idle) and the set-level
-// reductions (max depth, worst contact error / angle) read the set's lanes
-// with shuffles.
-// Everything per lane lives in registers; the kernel is templated on the
-// largest finger DOF so the small dense solves unroll.
+// Lane layout of both: F lanes per accepted set, lane f realises finger f, so a
+// wave covers 64 / F sets (the 64 mod F lanes left over idle) and the set-level
+// reductions (max depth) read the set's lanes with shuffles.
+// Everything per lane of the steps lives in registers; that kernel is templated
+// on the largest finger DOF so the small dense solves unroll.
 #include <math.h>
 
 #include <algorithm>
@@ -171,34 +174,54 @@ __device__ inline void capsule_project(const float *A, const float *Bp, float r,
 
 
 #define LG_REALIZE_ARGS                                                                                         \
-    DevHand H, const int32_t *__restrict__ wit, SdfDev S, const float *__restrict__ pts,                        \
-        const float *__restrict__ nrm, int N, const float *__restrict__ poses,                                  \
-        const int32_t *__restrict__ set_pt, const int8_t *__restrict__ set_link, int k, int D, int64_t n_sets,  \
+    DevHand H, const int32_t *__restrict__ wit, const float *__restrict__ pts, const float *__restrict__ nrm,   \
+        int N, const float *__restrict__ poses, const int32_t *__restrict__ set_pt,                             \
+        const int8_t *__restrict__ set_link, int k, int D, int64_t n_sets,                                      \
         const int32_t *__restrict__ acc_list, const int32_t *__restrict__ n_acc_dev, int max_acc, IkDev ik,    \
-        float *__restrict__ q_out, float *__restrict__ cerr, float *__restrict__ cang,                          \
-        float *__restrict__ depth_out, uint8_t *__restrict__ valid_out
+        float *__restrict__ q_out, float *__restrict__ cerr, float *__restrict__ cang
 #define LG_REALIZE_PASS                                                                                         \
-    H, wit, S, pts, nrm, N, poses, set_pt, set_link, k, D, n_sets, acc_list, n_acc_dev, max_acc, ik, q_out,     \
-        cerr, cang, depth_out, valid_out
+    H, wit, pts, nrm, N, poses, set_pt, set_link, k, D, n_sets, acc_list, n_acc_dev, max_acc, ik, q_out, cerr,  \
+        cang
 
-// cb: bin centres in LDS; caps: capsule axis end points of every lane's finger
-// at its final configuration (LDS); block bid of nb (grid-stride)
+// t / d, correctly rounded, from the correctly rounded r = 1 / d: the quotient's
+// residual is exact in one fma, so one correction rounds it right (Markstein);
+// the fix-up handles zeros, infinities and NaNs.  Four instructions, not ten.
+__device__ inline float div_by(float t, float d, float r)
+{
+    const float q = t * r;
+    return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-q, d, t), r, q), d, t);
+}
+
+// LDS of a block of realize_sets: the bin centres and per joint its origin [12],
+// axis [3] and limits [2] (read ten times per set; from memory each was a wait)
+struct RealizeLds {
+    float4 cb4[kMaxBins];
+    __attribute__((aligned(16))) float jp[kMaxJoints][20];
+};
+
+// The joint values and contact errors of the accepted sets; block bid of nb
+// (grid-stride).  What bounds it: VALU issue (470,724 sets of 22 joints: 0.60 G
+// wave instructions in 0.92 ms; the same part took 1.2 ms with the joint data in
+// memory, full divisions and the five-joint fingers padded to six).
 template <int DM>
 __device__ __forceinline__ void realize_sets(
-    float *cb, float (*caps)[DM][6], int64_t bid, int64_t nb, const DevHand &H, const int32_t *__restrict__ wit,
-    const SdfDev &S, const float *__restrict__ pts, const float *__restrict__ nrm, int N,
-    const float *__restrict__ poses, const int32_t *__restrict__ set_pt, const int8_t *__restrict__ set_link, int k,
-    int D, int64_t n_sets, const int32_t *__restrict__ acc_list, const int32_t *__restrict__ n_acc_dev, int max_acc,
-    const IkDev &ik, float *__restrict__ q_out, float *__restrict__ cerr, float *__restrict__ cang,
-    float *__restrict__ depth_out, uint8_t *__restrict__ valid_out)
+    RealizeLds &L, int64_t bid, int64_t nb, const DevHand &H, const int32_t *__restrict__ wit,
+    const float *__restrict__ pts, const float *__restrict__ nrm, int N, const float *__restrict__ poses,
+    const int32_t *__restrict__ set_pt, const int8_t *__restrict__ set_link, int k, int D, int64_t n_sets,
+    const int32_t *__restrict__ acc_list, const int32_t *__restrict__ n_acc_dev, int max_acc, const IkDev &ik,
+    float *__restrict__ q_out, float *__restrict__ cerr, float *__restrict__ cang)
 {
-    for (int i = threadIdx.x; i < 3 * H.B; i += kRealizeThreads) cb[i] = H.bin_c[i];
+    for (int i = threadIdx.x; i < H.B; i += kRealizeThreads)
+        L.cb4[i] = make_float4(H.bin_c[3 * i], H.bin_c[3 * i + 1], H.bin_c[3 * i + 2], 0.0f);
+    for (int i = threadIdx.x; i < 17 * H.J; i += kRealizeThreads) {
+        const int j = i / 17, c = i - 17 * j;
+        L.jp[j][c] = c < 12 ? H.origin[12 * j + c] : c < 15 ? H.axis[3 * j + c - 12] : H.limits[2 * j + c - 15];
+    }
     __syncthreads();
     const int64_t gt = bid * kRealizeThreads + threadIdx.x;
     const int spw = 64 / H.F;                    // sets per wave
     const int lane = threadIdx.x & 63, slot = lane / H.F;
     const int f = lane - slot * H.F;             // this lane's finger
-    const int tid = threadIdx.x, base = tid - f;  // the set's first lane in the block
     const int64_t nacc = min((int64_t)*n_acc_dev, (int64_t)max_acc);
     const int64_t stride = ((nb * kRealizeThreads) >> 6) * spw;
     // grid-stride over accepted sets; the F lanes of a set move together, the
@@ -211,10 +234,6 @@ __device__ __forceinline__ void realize_sets(
             if (f < k) {
                 cerr[a * k + f] = INFINITY;
                 cang[a * k + f] = INFINITY;
-            }
-            if (f == 0) {
-                depth_out[a] = __builtin_nanf("");
-                valid_out[a] = 0;
             }
             continue;
         }
@@ -239,8 +258,8 @@ __device__ __forceinline__ void realize_sets(
             if (fl >= 0) used |= 1u << fl;
         }
         if (!ok) used = 0;
-        float dep = -INFINITY, emax = 0.f, amax = 0.f;
         if (f < H.F) {
+            float emax = 0.f, amax = 0.f;
             const int first = H.finger_first[f], d = H.finger_dof[f];
             const int ci = ((used >> f) & 1u) ? __popc(used & ((1u << f) - 1u)) : -1;  // this finger's contact
             float q[DM];
@@ -258,16 +277,20 @@ __device__ __forceinline__ void realize_sets(
                 int32_t w = kNoWitness;
                 if (wit) {
                     const int v = finger_window_voxel(H, P, f, ox, oy, oz);
-                    const int b = nearest_bin(cb, H.B, n[0], n[1], n[2]);
+                    const int b = nearest_bin_any(H.bin_lut, L.cb4, H.B, n[0], n[1], n[2]);
                     if (v >= 0) w = wit[((int64_t)l * H.G * H.G * H.G + v) * H.B + b];
                 }
+                // the joint sample w (see joint_sample; one Philox block per four joints)
+                uint32_t rw[8];
+                philox4x32_10((uint32_t)w, (uint32_t)(8 * f), kPurposeJoint, 0u, H.seed_lo, H.seed_hi, rw);
+                if (DM > 4 && d > 4)
+                    philox4x32_10((uint32_t)w, (uint32_t)(8 * f + 1), kPurposeJoint, 0u, H.seed_lo, H.seed_hi, rw + 4);
 #pragma unroll
                 for (int t = 0; t < DM; ++t) {
                     q[t] = 0.f;
                     if (t < d) {
-                        const int j = first + t;
-                        q[t] = (w >= 0 && w < H.samples) ? joint_sample(H, f, (uint32_t)w, t)
-                                                         : 0.5f * (H.limits[2 * j] + H.limits[2 * j + 1]);
+                        const float lo = L.jp[first + t][15], hi = L.jp[first + t][16];
+                        q[t] = (w >= 0 && w < H.samples) ? fmaf(hi - lo, u01f(rw[t]), lo) : 0.5f * (lo + hi);
                     }
                 }
                 tl = l - first;
@@ -280,12 +303,12 @@ __device__ __forceinline__ void realize_sets(
 #pragma unroll
                     for (int t = 0; t < DM; ++t) {
                         if (t < d) {
-                            const int j = first + t;
-                            T = joint_frame(H, T, t > 0, j, q[t]);
+                            const float *jp = L.jp[first + t];
+                            T = joint_frame_at(jp, jp + 12, T, t > 0, q[t]);
                             o[t][0] = T.m[3];
                             o[t][1] = T.m[7];
                             o[t][2] = T.m[11];
-                            tf_dir(T, H.axis[3 * j], H.axis[3 * j + 1], H.axis[3 * j + 2], z[t][0], z[t][1], z[t][2]);
+                            tf_dir(T, jp[12], jp[13], jp[14], z[t][0], z[t][1], z[t][2]);
                             if (t == tl) Tl = T;
                         }
                     }
@@ -326,7 +349,7 @@ __device__ __forceinline__ void realize_sets(
                         }
                     }
                     // normal equations (J^T J + lambda I) dq = J^T e, Cholesky in place
-                    float M[DM][DM], gv[DM];
+                    float M[DM][DM], gv[DM], Mi[DM];  // Mi: reciprocals of the factor's diagonal
 #pragma unroll
                     for (int i = 0; i < DM; ++i) {
                         float acc = 0.f;
@@ -351,6 +374,7 @@ __device__ __forceinline__ void realize_sets(
                         const float dd = sqrtf(fmaxf(s2, 1e-30f));
                         M[j][j] = dd;
                         const float inv = 1.0f / dd;
+                        Mi[j] = inv;
 #pragma unroll
                         for (int i = j + 1; i < DM; ++i) {
                             float t2 = M[i][j];
@@ -365,21 +389,18 @@ __device__ __forceinline__ void realize_sets(
                         float t2 = gv[i];
 #pragma unroll
                         for (int kk = 0; kk < i; ++kk) t2 = fmaf(-M[i][kk], gv[kk], t2);
-                        gv[i] = t2 / M[i][i];
+                        gv[i] = div_by(t2, M[i][i], Mi[i]);
                     }
 #pragma unroll
                     for (int i = DM - 1; i >= 0; --i) {
                         float t2 = gv[i];
 #pragma unroll
                         for (int kk = i + 1; kk < DM; ++kk) t2 = fmaf(-M[kk][i], gv[kk], t2);
-                        gv[i] = t2 / M[i][i];
+                        gv[i] = div_by(t2, M[i][i], Mi[i]);
                     }
 #pragma unroll
                     for (int t = 0; t < DM; ++t) {
-                        if (t < d) {
-                            const int j = first + t;
-                            q[t] = fminf(fmaxf(q[t] + gv[t], H.limits[2 * j]), H.limits[2 * j + 1]);
-                        }
+                        if (t < d) q[t] = fminf(fmaxf(q[t] + gv[t], L.jp[first + t][15]), L.jp[first + t][16]);
                     }
                 }
             } else {
@@ -395,49 +416,31 @@ __device__ __forceinline__ void realize_sets(
                 for (int t = 0; t < DM; ++t) {
                     q[t] = 0.f;
                     if (t < d) {
-                        const float lo = H.limits[2 * (first + t)], hi = H.limits[2 * (first + t) + 1];
+                        const float lo = L.jp[first + t][15], hi = L.jp[first + t][16];
                         q[t] = fmaf(hi - lo, u01f(w[t]), lo);
                     }
                 }
             }
-            // final configuration: contact quality and penetration of the finger's links
+            // final configuration: contact quality
             Tf T;
 #pragma unroll
             for (int t = 0; t < DM; ++t) {
                 if (t < d) {
                     const int j = first + t;
-                    T = joint_frame(H, T, t > 0, j, q[t]);
-                    const float *cj = H.capsule + 7 * j;
-                    float A[3], Bq[3];
-                    tf_point(T, cj[0], cj[1], cj[2], A[0], A[1], A[2]);
-                    tf_point(T, cj[3], cj[4], cj[5], Bq[0], Bq[1], Bq[2]);
-                    caps[tid][t][0] = A[0];
-                    caps[tid][t][1] = A[1];
-                    caps[tid][t][2] = A[2];
-                    caps[tid][t][3] = Bq[0];
-                    caps[tid][t][4] = Bq[1];
-                    caps[tid][t][5] = Bq[2];
+                    q_out[a * H.J + j] = q[t];
+                    if (t > tl) continue;  // no contact further out
+                    T = joint_frame_at(L.jp[j], L.jp[j] + 12, T, t > 0, q[t]);
                     if (t == tl) {
+                        const float *cj = H.capsule + 7 * j;
+                        float A[3], Bq[3];
+                        tf_point(T, cj[0], cj[1], cj[2], A[0], A[1], A[2]);
+                        tf_point(T, cj[3], cj[4], cj[5], Bq[0], Bq[1], Bq[2]);
                         float pt[3], nt[3];
                         capsule_project(A, Bq, cj[6], p, pt, nt);
                         const float d0 = p[0] - pt[0], d1 = p[1] - pt[1], d2 = p[2] - pt[2];
                         emax = sqrtf(dot3f(d0, d1, d2, d0, d1, d2));
                         amax = acosf(fminf(fmaxf(dot3f(nt[0], nt[1], nt[2], n[0], n[1], n[2]), -1.f), 1.f));
                     }
-                    const int M = H.axis_samples[j];
-                    const float inv = 1.0f / (float)(M - 1);
-                    for (int s = 0; s < M; ++s) {
-                        const float ts = (float)s * inv;
-                        const float x0 = fmaf(ts, Bq[0] - A[0], A[0]) - P[3];
-                        const float x1 = fmaf(ts, Bq[1] - A[1], A[1]) - P[7];
-                        const float x2 = fmaf(ts, Bq[2] - A[2], A[2]) - P[11];
-                        // object frame: R^T (x - t)
-                        const float y0 = fmaf(P[0], x0, fmaf(P[4], x1, P[8] * x2));
-                        const float y1 = fmaf(P[1], x0, fmaf(P[5], x1, P[9] * x2));
-                        const float y2 = fmaf(P[2], x0, fmaf(P[6], x1, P[10] * x2));
-                        dep = fmaxf(dep, cj[6] - sdf_trilinear(S, y0, y1, y2));
-                    }
-                    q_out[a * H.J + j] = q[t];
                 }
             }
             if (ci >= 0) {
@@ -448,46 +451,192 @@ __device__ __forceinline__ void realize_sets(
         if (!ok && f < k) {  // not realisable: no contact is met
             cerr[a * k + f] = INFINITY;
             cang[a * k + f] = INFINITY;
-            emax = INFINITY;
-            amax = INFINITY;
         }
-        // hand self-collision: this finger's links against those of the higher
-        // fingers of the set (the F lanes of a set are in one wave)
-        if (ik.self_collision) {
-            __builtin_amdgcn_wave_barrier();
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            if (f < H.F) {
-                const int first = H.finger_first[f], d = H.finger_dof[f];
-                for (int f2 = f + 1; f2 < H.F; ++f2) {
-                    const int first2 = H.finger_first[f2], d2 = H.finger_dof[f2];
-                    for (int t = 0; t < d; ++t)
-                        for (int t2 = 0; t2 < d2; ++t2) {
-                            const float *c1 = caps[tid][t], *c2 = caps[base + f2][t2];
-                            const float pen = H.capsule[7 * (first + t) + 6] + H.capsule[7 * (first2 + t2) + 6] -
-                                              segment_distance(c1, c1 + 3, c2, c2 + 3);
-                            dep = fmaxf(dep, pen);
-                        }
+    }
+}
+
+// Part [t0, t1] of a segment (parameter 0..1, ends yA, yB in SDF grid
+// coordinates) that can lie in the grid [0, gm]^3, widened by 1e-3 of a cell;
+// empty: t0 > t1.  A NaN constrains nothing.
+__device__ inline void grid_part(const float *yA, const float *yB, float gm, float &t0, float &t1)
+{
+    t0 = 0.f;
+    t1 = 1.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float d = yB[c] - yA[c], lo = -1e-3f - yA[c], hi = gm + 1e-3f - yA[c];
+        if (fabsf(d) < 1e-6f) {
+            if (lo > 1e-3f || hi < -1e-3f) t0 = 2.f;
+            continue;
+        }
+        const float r = 1.0f / d, a = lo * r, b = hi * r;
+        t0 = fmaxf(t0, fminf(a, b));  // fmaxf / fminf drop a NaN
+        t1 = fminf(t1, fmaxf(a, b));
+    }
+}
+
+// A link of a set at its final configuration: axis ends (hand frame), the set's
+// samples before it and its first sample in the grid.
+struct __attribute__((aligned(16))) LinkSeg {
+    float a[3], b[3];
+    int pre, first;
+};
+
+// LDS of a block: a LinkSeg per (set, link) of each wave, and per link the
+// sample spacing 1 / (M - 1) and the radius
+__host__ __device__ inline size_t penetrate_lds(int F, int J)
+{
+    return (size_t)(kRealizeThreads / 64) * (64 / F) * J * sizeof(LinkSeg) + (size_t)J * sizeof(float2);
+}
+
+__device__ inline void wave_fence()
+{
+    __builtin_amdgcn_wave_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// Penetration and validity of the realised sets (q_out, cerr, cang of
+// realize_sets).  A wave takes 64 / F sets.  First each lane walks its finger's
+// links, the joint frames from the joint values as realize_sets computes them,
+// and leaves the axis ends and the number of axis samples that can lie in the
+// SDF's grid in LDS (the others give no depth).  Then all 64 lanes take the
+// samples of one set after another: neighbouring lanes are 1 mm apart on one
+// axis, so their corner reads fall in few cache lines.  With a lane per finger,
+// 64 lanes read 64 unrelated cells each time: 2.6 ms at six waves per SIMD, 1.7 ms
+// at two inside the step kernel (fewer lines evicted between a lane's samples);
+// 470,724 sets of 22 joints now take 1.4 ms, bound by
+// the lines the corner reads touch (28 per read, one a cycle) and by VALU issue.
+// SC: the hand's self-collision too, by the finger lanes (the set's lanes are in
+// one wave).
+template <bool SC>
+__device__ __forceinline__ void penetrate_sets(
+    char *lds, int64_t bid, int64_t nb, const DevHand &H, const SdfDev &S, const float *__restrict__ poses, int k,
+    int D, int64_t n_sets, const int32_t *__restrict__ acc_list, const int32_t *__restrict__ n_acc_dev, int max_acc,
+    const IkDev &ik, const float *__restrict__ q_in, const float *__restrict__ cerr, const float *__restrict__ cang,
+    float *__restrict__ depth_out, uint8_t *__restrict__ valid_out)
+{
+    const int J = H.J, F = H.F, spw = 64 / F;
+    const int tid = threadIdx.x, lane = tid & 63, slot = lane / F, f = lane - slot * F;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    LinkSeg *segs = reinterpret_cast<LinkSeg *>(lds) + (size_t)wave * spw * J;  // [set][link]
+    float2 *link = reinterpret_cast<float2 *>(lds + (size_t)(kRealizeThreads / 64) * spw * J * sizeof(LinkSeg));
+    for (int j = tid; j < J; j += kRealizeThreads)
+        link[j] = make_float2(1.0f / (float)(H.axis_samples[j] - 1), H.capsule[7 * j + 6]);
+    __syncthreads();
+    const int64_t nacc = min((int64_t)*n_acc_dev, (int64_t)max_acc);
+    const int first = H.finger_first[f], d = H.finger_dof[f];
+    const float gm = (float)(S.G - 1);
+    for (int64_t a0 = (bid * (kRealizeThreads / 64) + wave) * spw; a0 < nacc; a0 += nb * (kRealizeThreads / 64) * spw) {
+        const int64_t a = a0 + slot;
+        const bool mine = slot < spw && a < nacc;
+        const int64_t id = mine ? acc_list[a] : -1;
+        const bool live = id >= 0 && id < n_sets;  // uniform over a set's lanes
+        const int g = live ? (int)(id / D) : 0;
+        float dep = -INFINITY;
+        int count = 0;  // samples of this lane's finger
+        if (live) {
+            float P[12];
+#pragma unroll
+            for (int i = 0; i < 12; ++i) P[i] = poses[12 * (int64_t)g + i];
+            Tf T;
+            for (int t = 0; t < d; ++t) {
+                const int j = first + t;
+                T = joint_frame(H, T, t > 0, j, q_in[a * J + j]);
+                const float *cj = H.capsule + 7 * j;
+                LinkSeg sg;
+                tf_point(T, cj[0], cj[1], cj[2], sg.a[0], sg.a[1], sg.a[2]);
+                tf_point(T, cj[3], cj[4], cj[5], sg.b[0], sg.b[1], sg.b[2]);
+                const float M1 = (float)(H.axis_samples[j] - 1);
+                // the axis in grid coordinates: R^T (x - t), less the origin, over h
+                float y[2][3];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float *x = e ? sg.b : sg.a;
+                    const float x0 = x[0] - P[3], x1 = x[1] - P[7], x2 = x[2] - P[11];
+                    y[e][0] = (fmaf(P[0], x0, fmaf(P[4], x1, P[8] * x2)) - S.ox) * S.inv_h;
+                    y[e][1] = (fmaf(P[1], x0, fmaf(P[5], x1, P[9] * x2)) - S.oy) * S.inv_h;
+                    y[e][2] = (fmaf(P[2], x0, fmaf(P[6], x1, P[10] * x2)) - S.oz) * S.inv_h;
                 }
+                float t0, t1;
+                grid_part(y[0], y[1], gm, t0, t1);
+                // a sample more on either side covers the rounding of t
+                sg.first = max(0, (int)(t0 * M1) - 1);
+                const int last = t0 > t1 ? -1 : min((int)M1, (int)(t1 * M1) + 2);
+                sg.pre = max(0, last - sg.first + 1);  // the link's samples; summed below
+                count += sg.pre;
+                segs[slot * J + j] = sg;
             }
-            __builtin_amdgcn_wave_barrier();
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
         }
-        // set-level reductions over the F lanes of the set (all active: same set)
-        {
-            const int first_lane = lane - f;
-            float d2 = dep, e2 = emax, a2 = amax;
-            for (int j = 0; j < H.F; ++j) {
-                d2 = fmaxf(d2, __shfl(dep, first_lane + j, 64));
-                e2 = fmaxf(e2, __shfl(emax, first_lane + j, 64));
-                a2 = fmaxf(a2, __shfl(amax, first_lane + j, 64));
+        // samples of the set before this lane's finger, and of the whole set
+        int before = 0, total = 0;
+        for (int q = 0; q < F; ++q) {
+            const int n = __shfl(count, lane - f + q, 64);
+            before += q < f ? n : 0;
+            total += n;
+        }
+        if (live)
+            for (int t = 0; t < d; ++t) {
+                int &pre = segs[slot * J + first + t].pre;
+                const int n = pre;
+                pre = before;
+                before += n;
             }
-            dep = d2;
-            emax = e2;
-            amax = a2;
+        wave_fence();
+        // hand self-collision: this finger's links against those of the higher fingers of the set
+        if (SC && live)
+            for (int f2 = f + 1; f2 < F; ++f2) {
+                const int first2 = H.finger_first[f2], d2 = H.finger_dof[f2];
+                for (int t = 0; t < d; ++t)
+                    for (int t2 = 0; t2 < d2; ++t2) {
+                        const LinkSeg &c1 = segs[slot * J + first + t], &c2 = segs[slot * J + first2 + t2];
+                        const float pen = H.capsule[7 * (first + t) + 6] + H.capsule[7 * (first2 + t2) + 6] -
+                                          segment_distance(c1.a, c1.b, c2.a, c2.b);
+                        dep = fmaxf(dep, pen);
+                    }
+            }
+        const int n_slots = (int)min((int64_t)spw, nacc - a0);
+        for (int sl = 0; sl < n_slots; ++sl) {
+            const int n = __builtin_amdgcn_readlane(total, sl * F);
+            if (n == 0) continue;  // not a set, or no sample in the grid
+            const float *P = poses + 12 * (int64_t)__builtin_amdgcn_readlane(g, sl * F);
+            const LinkSeg *sg = segs + sl * J;
+            float dp = -INFINITY;
+            int lo = 0;
+            for (int i = lane; i < n; i += 64) {
+                while (lo + 1 < J && sg[lo + 1].pre <= i) ++lo;  // the link: the last one with pre <= i
+                const LinkSeg c = sg[lo];
+                const float2 l = link[lo];
+                const float ts = (float)(c.first + i - c.pre) * l.x;
+                const float x0 = fmaf(ts, c.b[0] - c.a[0], c.a[0]) - P[3];
+                const float x1 = fmaf(ts, c.b[1] - c.a[1], c.a[1]) - P[7];
+                const float x2 = fmaf(ts, c.b[2] - c.a[2], c.a[2]) - P[11];
+                // object frame: R^T (x - t)
+                const float y0 = fmaf(P[0], x0, fmaf(P[4], x1, P[8] * x2));
+                const float y1 = fmaf(P[1], x0, fmaf(P[5], x1, P[9] * x2));
+                const float y2 = fmaf(P[2], x0, fmaf(P[6], x1, P[10] * x2));
+                dp = fmaxf(dp, l.y - sdf_trilinear(S, y0, y1, y2));
+            }
+            for (int off = 32; off > 0; off >>= 1) dp = fmaxf(dp, __shfl_xor(dp, off, 64));
+            if (slot == sl) dep = fmaxf(dep, dp);
         }
-        if (f == 0) {
-            depth_out[a] = dep;
-            valid_out[a] = (emax <= ik.tol_pos && amax <= ik.tol_ang && dep <= ik.margin) ? 1 : 0;
+        wave_fence();  // the segments are rewritten by the next sets
+        // the set's depth over its F lanes
+        float dm = dep;
+        for (int q = 0; q < F; ++q) dm = fmaxf(dm, __shfl(dep, lane - f + q, 64));
+        if (mine && f == 0) {
+            if (!live) {  // not a set id
+                depth_out[a] = __builtin_nanf("");
+                valid_out[a] = 0;
+                continue;
+            }
+            // worst contact (a finger without contact counts 0)
+            float emax = k < F ? 0.f : cerr[a * k], amax = k < F ? 0.f : cang[a * k];
+            for (int i = 0; i < k; ++i) {
+                emax = fmaxf(emax, cerr[a * k + i]);
+                amax = fmaxf(amax, cang[a * k + i]);
+            }
+            depth_out[a] = dm;
+            valid_out[a] = (emax <= ik.tol_pos && amax <= ik.tol_ang && dm <= ik.margin) ? 1 : 0;
         }
     }
 }
@@ -497,17 +646,27 @@ template <int DM>
 __global__ void __launch_bounds__(kRealizeThreads) __attribute__((amdgpu_waves_per_eu(2)))
 k_realize(LG_REALIZE_ARGS)
 {
-    __shared__ float cb[3 * kMaxBins];
-    __shared__ float caps[kRealizeThreads][DM][6];
-    realize_sets<DM>(cb, caps, blockIdx.x, gridDim.x, LG_REALIZE_PASS);
+    __shared__ RealizeLds L;
+    realize_sets<DM>(L, blockIdx.x, gridDim.x, LG_REALIZE_PASS);
 }
 
 // 7 or 8 joints per finger: one wave per SIMD rather than spilling
 __global__ void __launch_bounds__(kRealizeThreads) k_realize_wide(LG_REALIZE_ARGS)
 {
-    __shared__ float cb[3 * kMaxBins];
-    __shared__ float caps[kRealizeThreads][8][6];
-    realize_sets<8>(cb, caps, blockIdx.x, gridDim.x, LG_REALIZE_PASS);
+    __shared__ RealizeLds L;
+    realize_sets<8>(L, blockIdx.x, gridDim.x, LG_REALIZE_PASS);
+}
+
+template <bool SC>
+__global__ void __launch_bounds__(kRealizeThreads)
+k_penetrate(DevHand H, SdfDev S, const float *__restrict__ poses, int k, int D, int64_t n_sets,
+            const int32_t *__restrict__ acc_list, const int32_t *__restrict__ n_acc_dev, int max_acc, IkDev ik,
+            const float *__restrict__ q, const float *__restrict__ cerr, const float *__restrict__ cang,
+            float *__restrict__ depth, uint8_t *__restrict__ valid)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    penetrate_sets<SC>(lds, blockIdx.x, gridDim.x, H, S, poses, k, D, n_sets, acc_list, n_acc_dev, max_acc, ik, q,
+                       cerr, cang, depth, valid);
 }
 
 // The same over the accepted sets of several chunks (max_acc = the chunk's
@@ -517,14 +676,25 @@ __global__ void __launch_bounds__(kRealizeThreads) __attribute__((amdgpu_waves_p
 k_realize_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx, const uint32_t *__restrict__ first,
                 int n)
 {
-    __shared__ float cb[3 * kMaxBins];
-    __shared__ float caps[kRealizeThreads][DM][6];
+    __shared__ RealizeLds L;
     const int j = batch_member(first, n, blockIdx.x);
     const ChunkDesc &c = d[idx[j]];
     const int64_t n_sets = (int64_t)c.P * c.D;
-    realize_sets<DM>(cb, caps, blockIdx.x - first[j], first[j + 1] - first[j], c.H, c.wit, c.S, c.pts, c.nrm, c.N,
-                     c.poses, c.set_pt, c.set_link, c.k, c.D, n_sets, c.acc, c.n_acc, (int)n_sets, c.ik, c.q, c.err,
-                     c.ang, c.depth, c.valid);
+    realize_sets<DM>(L, blockIdx.x - first[j], first[j + 1] - first[j], c.H, c.wit, c.pts, c.nrm, c.N, c.poses,
+                     c.set_pt, c.set_link, c.k, c.D, n_sets, c.acc, c.n_acc, (int)n_sets, c.ik, c.q, c.err, c.ang);
+}
+
+template <bool SC>
+__global__ void __launch_bounds__(kRealizeThreads)
+k_penetrate_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx,
+                  const uint32_t *__restrict__ first, int n)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int j = batch_member(first, n, blockIdx.x);
+    const ChunkDesc &c = d[idx[j]];
+    const int64_t n_sets = (int64_t)c.P * c.D;
+    penetrate_sets<SC>(lds, blockIdx.x - first[j], first[j + 1] - first[j], c.H, c.S, c.poses, c.k, c.D, n_sets,
+                       c.acc, c.n_acc, (int)n_sets, c.ik, c.q, c.err, c.ang, c.depth, c.valid);
 }
 
 #undef LG_REALIZE_ARGS
@@ -561,21 +731,31 @@ extern "C" lg_status lg_realize(const lg_field *field, const lg_sdf *sdf, const 
     LG_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     const dim3 grid(realize_blocks(max_acc, H.F, n_cu));
     const int32_t *wit = field->has_witness ? field->d_wit : nullptr;
+    const int64_t n_sets = (int64_t)n_poses * draws;
 #define LG_REALIZE(KERNEL)                                                                                      \
-    hipLaunchKernelGGL(KERNEL, grid, dim3(kRealizeThreads), 0, s, H, wit, S, pts, nrm, n_points, poses,     \
-                       set_pt, set_link, k, draws, (int64_t)n_poses * draws, acc_list, n_acc_dev, max_acc, ik,  \
-                       q_out, contact_err,                                                                      \
-                       contact_ang, depth, valid)
+    hipLaunchKernelGGL(KERNEL, grid, dim3(kRealizeThreads), 0, s, H, wit, pts, nrm, n_points, poses, set_pt,     \
+                       set_link, k, draws, n_sets, acc_list, n_acc_dev, max_acc, ik, q_out, contact_err, contact_ang)
     if (field->max_dof <= 4)
         LG_REALIZE(k_realize<4>);
+    else if (field->max_dof <= 5)
+        LG_REALIZE(k_realize<5>);
     else if (field->max_dof <= 6)
         LG_REALIZE(k_realize<6>);
     else
         LG_REALIZE(k_realize_wide);
 #undef LG_REALIZE
+    const size_t lds = penetrate_lds(H.F, H.J);
+    if (ik.self_collision)
+        hipLaunchKernelGGL(k_penetrate<true>, grid, dim3(kRealizeThreads), lds, s, H, S, poses, k, draws, n_sets, acc_list,
+                           n_acc_dev, max_acc, ik, q_out, contact_err, contact_ang, depth, valid);
+    else
+        hipLaunchKernelGGL(k_penetrate<false>, grid, dim3(kRealizeThreads), lds, s, H, S, poses, k, draws, n_sets, acc_list,
+                           n_acc_dev, max_acc, ik, q_out, contact_err, contact_ang, depth, valid);
     LG_HIP(hipGetLastError());
     return LG_OK;
 }
+
+size_t lg::realize_lds_bytes(int F, int J) { return penetrate_lds(F, J); }
 
 uint32_t lg::realize_blocks(int64_t max_acc, int F, int n_cu)
 {
@@ -584,15 +764,21 @@ uint32_t lg::realize_blocks(int64_t max_acc, int F, int n_cu)
     return (uint32_t)std::max<int64_t>(1, (threads + kRealizeThreads - 1) / kRealizeThreads);
 }
 
-lg_status lg::realize_batch(const BatchLaunch &b, int max_dof, hipStream_t s)
+lg_status lg::realize_batch(const BatchLaunch &b, int max_dof, size_t lds, bool self_collision, hipStream_t s)
 {
     if (b.n <= 0 || b.blocks == 0) return LG_OK;
     if (max_dof <= 4)
         hipLaunchKernelGGL(k_realize_batch<4>, dim3(b.blocks), dim3(kRealizeThreads), 0, s, b.d, b.idx, b.first, b.n);
+    else if (max_dof <= 5)
+        hipLaunchKernelGGL(k_realize_batch<5>, dim3(b.blocks), dim3(kRealizeThreads), 0, s, b.d, b.idx, b.first, b.n);
     else if (max_dof <= 6)
         hipLaunchKernelGGL(k_realize_batch<6>, dim3(b.blocks), dim3(kRealizeThreads), 0, s, b.d, b.idx, b.first, b.n);
     else
         hipLaunchKernelGGL(k_realize_batch<8>, dim3(b.blocks), dim3(kRealizeThreads), 0, s, b.d, b.idx, b.first, b.n);
+    if (self_collision)
+        hipLaunchKernelGGL(k_penetrate_batch<true>, dim3(b.blocks), dim3(kRealizeThreads), lds, s, b.d, b.idx, b.first, b.n);
+    else
+        hipLaunchKernelGGL(k_penetrate_batch<false>, dim3(b.blocks), dim3(kRealizeThreads), lds, s, b.d, b.idx, b.first, b.n);
     LG_HIP(hipGetLastError());
     return LG_OK;
 }

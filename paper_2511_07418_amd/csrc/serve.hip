@@ -370,7 +370,7 @@ static lg_status launch_chunk(lg_server *S, Req *q)
 // are grouped by the template bucket of the kernels that have one.
 static int fm_bucket(int F) { return F <= 3 ? 3 : F <= 4 ? 4 : F <= 5 ? 5 : 8; }
 static int km_bucket(int k) { return k <= 3 ? 3 : k <= 4 ? 4 : k <= 5 ? 5 : k <= 6 ? 6 : 8; }
-static int dm_bucket(int d) { return d <= 4 ? 4 : d <= 6 ? 6 : 8; }
+static int dm_bucket(int d) { return d <= 4 ? 4 : d <= 5 ? 5 : d <= 6 ? 6 : 8; }
 
 // host view of a slot's table while it is filled
 struct TableWriter {
@@ -540,7 +540,8 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
     for (int m : all)
         if (cd[m].realize) rz.push_back(m);
     auto max_dof = [&](int m) { return B.members[m]->r.field->max_dof; };
-    for (auto &g : buckets(rz, [&](int m) { return dm_bucket(max_dof(m)); })) {
+    // realize launches by joints per finger and by whether self-collisions are tested
+    for (auto &g : buckets(rz, [&](int m) { return (dm_bucket(max_dof(m)) << 1) | (cd[m].ik.self_collision ? 1 : 0); })) {
         lr.push_back({BatchLaunch{}, g[0]});
         if ((st = T.list(g, blocks(g, ik_blocks), lr.back().b)) != LG_OK) return st;
     }
@@ -564,8 +565,10 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
     if ((st = compact_count_batch(sc, false, B.s)) != LG_OK) return st;
     if ((st = compact_scan_batch(ss, false, B.s)) != LG_OK) return st;
     if ((st = compact_scatter_batch(sc, false, B.s)) != LG_OK) return st;
+    size_t seg_lds = 0;
+    for (int m : rz) seg_lds = std::max(seg_lds, realize_lds_bytes(cd[m].H.F, cd[m].H.J));
     for (const Keyed &g : lr)
-        if ((st = realize_batch(g.b, max_dof(g.rep), B.s)) != LG_OK) return st;
+        if ((st = realize_batch(g.b, max_dof(g.rep), seg_lds, cd[g.rep].ik.self_collision != 0, B.s)) != LG_OK) return st;
     if (la.blocks) {
         hipLaunchKernelGGL(k_accumulate_batch, dim3(la.blocks), dim3(kAccThreads), 0, B.s, la.d, la.idx, la.first, la.n);
         LG_HIP(hipGetLastError());
