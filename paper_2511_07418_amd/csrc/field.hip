@@ -86,6 +86,7 @@ void free_field(lg_field *f)
     (void)hipFree(f->d_merged);
     (void)hipFree(f->d_wit);
     (void)hipFree(f->d_cull);
+    (void)hipFree(f->d_mask);
     (void)hipSetDevice(cur);
     delete f;
 }
@@ -301,6 +302,8 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
     H.cull_row = (G + 31) / 32;
     const size_t cull_bytes = (size_t)(kCullLevels + 1) * F * G * G * H.cull_row * 4;
     if (e == hipSuccess) e = hipMalloc(&f->d_cull, cull_bytes);
+    const size_t mask_bytes = (size_t)F * G3 * B;
+    if (e == hipSuccess) e = hipMalloc(&f->d_mask, mask_bytes);
     size_t wit_bytes = 0;
     if (e == hipSuccess && p->keep_witness) {
         wit_bytes = (size_t)J * G3 * B * 4;
@@ -318,7 +321,7 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
         free_field(f);
         return st;
     }
-    f->device_bytes = n_all * 4 + (J + PC) * 4 + bits_bytes + merged_bytes + wit_bytes + cull_bytes;
+    f->device_bytes = n_all * 4 + (J + PC) * 4 + bits_bytes + merged_bytes + wit_bytes + cull_bytes + mask_bytes;
     float *base = f->d_params;
     H.origin = base;
     base += n_origin;
@@ -341,6 +344,7 @@ lg_status make_field_shell(const lg_hand_desc *hand, const lg_field_params *p, l
     H.bin_lut = reinterpret_cast<const uint32_t *>(base);
     H.axis_samples = f->d_axis_samples;
     H.cull = f->d_cull;
+    H.link_mask = f->d_mask;
     H.n_palm_surf = PS;
     H.n_palm_caps = PC;
     *out = f;
@@ -480,20 +484,32 @@ static hipError_t build_rounds(lg_field *f, uint32_t *done, unsigned long long *
 
 // Merged finger tables: OR over the links of finger f of their words, laid
 // out as merged[f][w][brick_word(v)] (one plane per 32-bin word w, 4x4x4
-// voxel bricks), from the canonical per-link tables bits[l][v][w].
-__global__ void k_field_merge(DevHand H, const uint32_t *__restrict__ bits, uint32_t *__restrict__ merged)
+// voxel bricks), from the canonical per-link tables bits[l][v][w]; and the links
+// that hold each (voxel, bin) as a byte (a finger has at most 8 links), so that a
+// reverse lookup is one read instead of one per link, each in a table of its own.
+__global__ void k_field_merge(DevHand H, const uint32_t *__restrict__ bits, uint32_t *__restrict__ merged,
+                              uint4 *__restrict__ masks)
 {
     const int G = H.G, W = H.W;
     const int64_t G3 = (int64_t)G * G * G, G3W = G3 * W;
     const int f = blockIdx.y;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < G3W; i += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t acc = 0;
+        uint32_t acc = 0, m[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // m: a byte per bin
         const int first = H.finger_first[f], d = H.finger_dof[f];
-        for (int t = 0; t < d; ++t) acc |= bits[(int64_t)(first + t) * G3W + i];
+        for (int t = 0; t < d; ++t) {
+            const uint32_t w = bits[(int64_t)(first + t) * G3W + i];
+            acc |= w;
+            // four bits to the low bits of four bytes: (x * 0x204081) puts bit b at bit 8 b
+#pragma unroll
+            for (int q = 0; q < 8; ++q) m[q] |= ((((w >> (4 * q)) & 15u) * 0x204081u) & 0x01010101u) << t;
+        }
         const int64_t v = i / W;
         const int w = (int)(i - v * W);
         const uint32_t ix = (uint32_t)(v % G), iy = (uint32_t)((v / G) % G), iz = (uint32_t)(v / ((int64_t)G * G));
         merged[((int64_t)f * W + w) * G3 + brick_word(ix, iy, iz, (uint32_t)(G / 4))] = acc;
+        uint4 *o = masks + (f * G3W + i) * 2;
+        o[0] = make_uint4(m[0], m[1], m[2], m[3]);
+        o[1] = make_uint4(m[4], m[5], m[6], m[7]);
     }
 }
 
@@ -555,7 +571,8 @@ static lg_status merge_and_count(lg_field *f, hipStream_t st)
     const DevHand &H = f->dh;
     const int64_t G3W = (int64_t)H.G * H.G * H.G * H.W;
     dim3 grid((unsigned)std::min<int64_t>((G3W + 255) / 256, 4096), H.F);
-    hipLaunchKernelGGL(k_field_merge, grid, dim3(256), 0, st, H, f->d_bits, f->d_merged);
+    hipLaunchKernelGGL(k_field_merge, grid, dim3(256), 0, st, H, f->d_bits, f->d_merged,
+                       reinterpret_cast<uint4 *>(f->d_mask));
     LG_HIP(hipGetLastError());
     // the voxels' occupancy and its dilations, for the query's culling
     const int64_t n_row = (int64_t)H.G * H.G * H.cull_row;

@@ -48,6 +48,7 @@ struct DevHand {
     const uint32_t *cull;         // [kCullLevels][F][G][G][cull_row] bits: voxels within cull_reach(level) of an
                                   // occupied one of the finger's window (per axis), one bit per x
     int cull_row;                 // words of a row: ceil(G / 32)
+    const uint8_t *link_mask;     // [F][G^3][B]: bit t set if link t of the finger has the (voxel, bin)
     int finger_first[kMaxFingers];
     int finger_dof[kMaxFingers];
     // Lattice form of the windows (lat != 0): every finger's window has the
@@ -84,6 +85,7 @@ struct lg_field {
     uint32_t *d_merged = nullptr;  // per-finger OR of its links [F][G^3][W]
     int32_t *d_wit = nullptr;      // [J][G^3][B], kNoWitness = none
     uint32_t *d_cull = nullptr;    // DevHand::cull, after it the undilated occupancy
+    uint8_t *d_mask = nullptr;     // DevHand::link_mask
 };
 
 namespace lg {
@@ -314,13 +316,18 @@ __host__ __device__ inline int cull_reach(int level)
     return level < 4 ? level + 1 : level == 4 ? 6 : level == 5 ? 8 : level == 6 ? 12 : 16;
 }
 
-// Voxel of object point p in finger f's window under pose P (-1 outside):
-// window_voxel of finger_affine, or, for lattice windows, the lattice cell
-// less the finger's offset (the query takes the same decisions).
-__device__ inline int finger_window_voxel(const DevHand &H, const float *pose, int f, float px, float py, float pz)
+// Map of pose P that map_window_voxel takes: the lattice's, else finger f's own.
+__device__ inline Affine window_map(const DevHand &H, const float *pose, int f)
+{
+    return H.lat ? lattice_affine(H, pose) : finger_affine(H, pose, f);
+}
+
+// Voxel of object point p in finger f's window (-1 outside): window_voxel of
+// finger_affine, or, for lattice windows, the lattice cell less the finger's
+// offset (the query takes the same decisions).  a: window_map of the pose.
+__device__ inline int map_window_voxel(const DevHand &H, const Affine &a, int f, float px, float py, float pz)
 {
     if (H.lat) {
-        const Affine a = lattice_affine(H, pose);
         int Ix, Iy, Iz;
         lattice_cell(a, px, py, pz, Ix, Iy, Iz);
         const unsigned ix = (unsigned)(Ix - H.lat_o[f][0]), iy = (unsigned)(Iy - H.lat_o[f][1]),
@@ -328,7 +335,12 @@ __device__ inline int finger_window_voxel(const DevHand &H, const float *pose, i
         const bool in = max(ix, max(iy, iz)) < (unsigned)H.G;
         return in ? (int)__umul24(__umul24(iz, H.G) + iy, H.G) + (int)ix : -1;
     }
-    return window_voxel(finger_affine(H, pose, f), H.G, px, py, pz);
+    return window_voxel(a, H.G, px, py, pz);
+}
+
+__device__ inline int finger_window_voxel(const DevHand &H, const float *pose, int f, float px, float py, float pz)
+{
+    return map_window_voxel(H, window_map(H, pose, f), f, px, py, pz);
 }
 
 // Query direction of object normal n under pose P: q = -R_P n.
@@ -339,22 +351,7 @@ __device__ inline void query_dir(const float *pose, float nx, float ny, float nz
     qz = -fmaf(pose[8], nx, fmaf(pose[9], ny, pose[10] * nz));
 }
 
-// argmax_b <d, c_b>, ties to the lowest b; c is [B][3] (LDS or global).
-__device__ inline int nearest_bin(const float *c, int B, float dx, float dy, float dz)
-{
-    float best = -3.0e38f;
-    int bi = 0;
-    for (int b = 0; b < B; ++b) {
-        const float s = fmaf(c[3 * b], dx, fmaf(c[3 * b + 1], dy, c[3 * b + 2] * dz));
-        if (s > best) {
-            best = s;
-            bi = b;
-        }
-    }
-    return bi;
-}
-
-// argmax_b <d, c_b> (ties to the lowest b, as nearest_bin) through the
+// argmax_b <d, c_b> (ties to the lowest b) through the
 // cube-map candidate table: the four candidate slots of the direction's cell
 // (absent ones repeat the first, so the result is unchanged) are evaluated
 // without a branch.  Their centres are float4 rows in LDS, all four read
@@ -403,7 +400,7 @@ __device__ inline int nearest_bin_lut4(const uint32_t *lut, const float4 *c4, in
     return bi;
 }
 
-// nearest_bin of any direction: the table where the direction has one (a zero or
+// argmax_b <d, c_b>, ties to the lowest b, for any direction: the table where the direction has one (a zero or
 // non-finite one, or one whose reciprocal overflows, scans every bin)
 __device__ inline int nearest_bin_any(const uint32_t *lut, const float4 *c4, int B, float dx, float dy, float dz)
 {
@@ -419,11 +416,6 @@ __device__ inline int nearest_bin_any(const uint32_t *lut, const float4 *c4, int
         }
     }
     return bi;
-}
-
-__device__ inline bool table_bit(const uint32_t *tab, int W, int64_t voxel, int b)
-{
-    return (tab[voxel * W + (b >> 5)] >> (b & 31)) & 1u;
 }
 
 // Object signed-distance grid (object frame), [iz][iy][ix] node values.
@@ -491,7 +483,7 @@ struct IkDev {
 // buffers are the request's own, so chunks of a batch share nothing.
 struct ChunkDesc {
     DevHand H;
-    const uint32_t *merged, *bits;
+    const uint32_t *merged;
     const int32_t *wit;  // witness table, or null
     const float *pts, *nrm, *poses;  // poses: the chunk's first pose
     const float4 *bounds;

@@ -17,11 +17,19 @@ constexpr int kChunkPerThread = 32; // compaction: sets per thread
 constexpr int kCompactThreads = 256;
 constexpr int kChunk = kChunkPerThread * kCompactThreads;
 
-// select the r-th (0-based) set bit of x
+// select the r-th (0-based) set bit of x (r < popcount): halves by their popcounts
 __device__ inline int select_in_word(uint32_t x, uint32_t r)
 {
-    for (uint32_t i = 0; i < r; ++i) x &= x - 1u;
-    return __ffs(x) - 1;
+    int at = 0;
+#pragma unroll
+    for (int h = 16; h > 0; h >>= 1) {
+        const uint32_t low = x & ((1u << h) - 1u), c = (uint32_t)__popc(low);
+        const bool up = r >= c;
+        at += up ? h : 0;
+        r -= up ? c : 0u;
+        x = up ? x >> h : low;
+    }
+    return at;
 }
 
 constexpr uint32_t kPurposeFingers = 13u;
@@ -60,30 +68,74 @@ __device__ inline uint32_t eligible_fingers(const uint32_t *__restrict__ dom_cou
     return e;
 }
 
+// inclusive prefix sum over the lanes (row shifts by 1, 2, 4, 8, then the row
+// broadcasts); lanes without a source add 0
+__device__ inline uint32_t wave_scan_incl(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
+// What the reverse lookup of a pose needs in LDS: the bin centres and the map of
+// each finger's window (the lattice's in entry 0 for lattice windows).
+struct LinkLds {
+    float4 cb4[kMaxBins];
+    Affine aff[kMaxFingers];
+};
+
+// fill it (the caller synchronises after)
+__device__ inline void link_lds(LinkLds &L, const DevHand &H, const float *pose)
+{
+    for (int i = threadIdx.x; i < H.B; i += blockDim.x)
+        L.cb4[i] = make_float4(H.bin_c[3 * i], H.bin_c[3 * i + 1], H.bin_c[3 * i + 2], 0.0f);
+    if ((int)threadIdx.x < (H.lat ? 1 : H.F)) L.aff[threadIdx.x] = window_map(H, pose, threadIdx.x);
+}
+
 // Reverse lookup (Sec. 5.5): among the links of finger i whose own table is
 // hit at point idx under the pose, the floor(r * count / 2^32)-th; -1 if none.
-__device__ inline int pick_link(const DevHand &H, const uint32_t *__restrict__ bits, const float *cb,
-                                const float *__restrict__ pts, const float *__restrict__ nrm, int N,
+// aff: window_map of the finger.
+__device__ inline int pick_link(const DevHand &H, const float4 *cb4,
+                                const Affine &aff, const float *__restrict__ pts, const float *__restrict__ nrm, int N,
                                 const float *pose, int i, int idx, uint32_t r)
 {
-    const int64_t G3 = (int64_t)H.G * H.G * H.G;
-    const int v = finger_window_voxel(H, pose, i, pts[idx], pts[N + idx], pts[2 * N + idx]);
+    const int v = map_window_voxel(H, aff, i, pts[idx], pts[N + idx], pts[2 * N + idx]);
     float qx, qy, qz;
     query_dir(pose, nrm[idx], nrm[N + idx], nrm[2 * N + idx], qx, qy, qz);
-    const int b = nearest_bin(cb, H.B, qx, qy, qz);
-    uint32_t mask = 0;
-    const int first = H.finger_first[i], dof = H.finger_dof[i];
-    if (v >= 0)
-        for (int t = 0; t < dof; ++t)
-            if (table_bit(bits + (int64_t)(first + t) * G3 * H.W, H.W, v, b)) mask |= 1u << t;
+    const int b = nearest_bin_any(H.bin_lut, cb4, H.B, qx, qy, qz);
+    const int first = H.finger_first[i];
+    const uint32_t mask = v >= 0 ? H.link_mask[((int64_t)i * H.G * H.G * H.G + v) * H.B + b] : 0u;
     const uint32_t pc = __popc(mask);
     return pc ? first + select_in_word(mask, __umulhi(r, pc)) : -1;
 }
 
+// Words [s kSuper, (s + 1) kSuper) of a domain of NW words (0 past its end), loaded together.
+__device__ inline void load_super(const uint32_t *__restrict__ dom, int NW, int s, uint32_t (&w)[kSuper])
+{
+    static_assert(kSuper == 8, "two 16-byte loads");
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    const uint32_t *d = dom + s * kSuper;
+    if ((s + 1) * kSuper <= NW) {
+        const u32x4 a = *(const u32x4 *)d, b = *(const u32x4 *)(d + 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[i] = a[i];
+            w[4 + i] = b[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kSuper; ++i) w[i] = s * kSuper + i < NW ? d[i] : 0u;
+    }
+}
+
 // The j-th (0-based) set bit of a domain of NW words through its superblock
 // prefix pf (nsb + 1 exclusive popcounts of kSuper-word superblocks): binary
-// search for the last superblock with pf <= j, then a scan of at most kSuper
-// words; -1 if the domain has no j-th bit.
+// search for the last superblock with pf <= j, then its words; -1 if the domain
+// has no j-th bit.
 __device__ inline int select_domain(const uint32_t *pf, int nsb, const uint32_t *__restrict__ dom, int NW, uint32_t j)
 {
     int lo = 0, hi = nsb;  // invariant pf[lo] <= j < pf[hi]
@@ -91,40 +143,59 @@ __device__ inline int select_domain(const uint32_t *pf, int nsb, const uint32_t 
         const int mid = (lo + hi) >> 1;
         if (pf[mid] <= j) lo = mid; else hi = mid;
     }
-    uint32_t rem = j - pf[lo];
-    for (int wi = lo * kSuper; wi < min(NW, (lo + 1) * kSuper); ++wi) {
-        const uint32_t x = dom[wi];
-        const uint32_t pc = __popc(x);
-        if (rem < pc) return wi * 32 + select_in_word(x, rem);
+    uint32_t rem = j - pf[lo], w[kSuper], word = 0, left = 0;
+    load_super(dom, NW, lo, w);
+    int at = -1;
+#pragma unroll
+    for (int i = 0; i < kSuper; ++i) {
+        const uint32_t pc = __popc(w[i]);
+        if (at < 0 && rem < pc) {
+            at = lo * kSuper + i;
+            word = w[i];
+            left = rem;
+        }
         rem -= pc;
     }
-    return -1;
+    return at < 0 ? -1 : at * 32 + select_in_word(word, left);
 }
 
 // Superblock popcount prefixes of the F domains of one pose into LDS
-// (prefix[f * (nsb + 1) + sb]); the caller synchronises after.
+// (prefix[f * (nsb + 1) + sb]); the caller synchronises after.  A wave takes a
+// finger: 64 superblocks at a time, summed by a scan over the lanes (one thread
+// per finger adding up its 256 counts took most of the draw).
 __device__ inline void build_prefix(uint32_t *prefix, const uint32_t *__restrict__ dom, int F, int NW, int nsb)
 {
-    for (int i = threadIdx.x; i < F * nsb; i += blockDim.x) {
-        const int f = i / nsb, sb = i % nsb;
-        uint32_t c = 0;
-        for (int w = sb * kSuper; w < min(NW, (sb + 1) * kSuper); ++w) c += __popc(dom[(int64_t)f * NW + w]);
-        prefix[f * (nsb + 1) + sb + 1] = c;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < F) {
-        uint32_t *pf = prefix + threadIdx.x * (nsb + 1);
-        pf[0] = 0;
-        for (int sb = 1; sb <= nsb; ++sb) pf[sb] += pf[sb - 1];
+    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+    for (int f = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); f < F; f += waves) {
+        const uint32_t *d = dom + (int64_t)f * NW;
+        uint32_t *pf = prefix + f * (nsb + 1);
+        uint32_t run = 0;
+        if (lane == 0) pf[0] = 0;
+        for (int s0 = 0; s0 < nsb; s0 += 64) {
+            const int sb = s0 + lane;
+            uint32_t c = 0;
+            if (sb < nsb) {
+                uint32_t w[kSuper];
+                load_super(d, NW, sb, w);
+#pragma unroll
+                for (int q = 0; q < kSuper; ++q) c += __popc(w[q]);
+            }
+            const uint32_t incl = wave_scan_incl(c);
+            if (sb < nsb) pf[sb + 1] = run + incl;
+            run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
     }
 }
 
 // One workgroup per pose.  Rank structure: exclusive popcount prefix per
 // superblock of 8 domain words, in LDS; a draw binary-searches it and scans
-// at most 8 words.
+// at most 8 words.  A thread per contact of a set (each draws the words it needs);
+// a thread per set walked its contacts' dependent reads one after another.  What
+// bounds it: the latency of those reads (65,536 poses x 64 sets of 5, 30 % of the
+// poses with draws: 0.88 -> 0.40 ms; 256 poses x 16 sets of 3: 21 -> 6 us).
 // the D sets of pose g (one block); prefix: [F][nsb + 1] words of LDS
-__device__ __forceinline__ void draw_pose(uint32_t *prefix, float *cb, uint32_t *counts, const DevHand &H,
-                                          const uint32_t *__restrict__ bits, const float *__restrict__ pts,
+__device__ __forceinline__ void draw_pose(uint32_t *prefix, LinkLds &L, uint32_t *counts, const DevHand &H,
+                                          const float *__restrict__ pts,
                                           const float *__restrict__ nrm, int N, const float *__restrict__ poses,
                                           const uint32_t *__restrict__ dom_bits, const uint32_t *__restrict__ dom_count,
                                           const int32_t *__restrict__ palm_pt, int D, int k, uint32_t seed_lo,
@@ -136,7 +207,6 @@ __device__ __forceinline__ void draw_pose(uint32_t *prefix, float *cb, uint32_t 
     const int F = H.F;
     const int NW = (N + 31) >> 5, nsb = (NW + kSuper - 1) / kSuper;
     const uint32_t *dom = dom_bits + (int64_t)g * F * NW;
-    for (int i = threadIdx.x; i < 3 * H.B; i += blockDim.x) cb[i] = H.bin_c[i];
     if (threadIdx.x < F) counts[threadIdx.x] = dom_count[(int64_t)g * F + threadIdx.x];
     __syncthreads();
     uint32_t elig = 0;
@@ -155,30 +225,32 @@ __device__ __forceinline__ void draw_pose(uint32_t *prefix, float *cb, uint32_t 
         }
         return;  // uniform over the block
     }
+    const float *pose = poses + 12 * (int64_t)g;
+    link_lds(L, H, pose);
     build_prefix(prefix, dom, F, NW, nsb);
     __syncthreads();
-    const float *pose = poses + 12 * (int64_t)g;
-    for (int d = threadIdx.x; d < D; d += blockDim.x) {
-        uint32_t w[16];
-        for (int blk = 0; blk * 4 < 2 * k; ++blk)
-            philox4x32_10((uint32_t)(pose_offset + g), (uint32_t)(4 * d + blk), kPurposeDraw, request_id, seed_lo,
-                          seed_hi, w + 4 * blk);
-        int32_t *sp = set_pt + ((int64_t)g * D + d) * k;
-        int8_t *sl = set_link + ((int64_t)g * D + d) * k;
-        uint32_t fm = choose_fingers(elig, k, (uint32_t)(pose_offset + g), d, request_id, seed_lo, seed_hi);
-        for (int i = 0; i < k; ++i) {
-            const int f = __ffs(fm) - 1;  // finger of contact i
-            fm &= fm - 1u;
-            const int idx = select_domain(prefix + f * (nsb + 1), nsb, dom + (int64_t)f * NW, NW,
-                                          __umulhi(w[i], counts[f]));
-            sp[i] = idx;
-            sl[i] = (int8_t)(idx >= 0 ? pick_link(H, bits, cb, pts, nrm, N, pose, f, idx, w[k + i]) : -1);
-        }
+    const uint32_t gg = (uint32_t)(pose_offset + g);
+    for (int c = threadIdx.x; c < D * k; c += blockDim.x) {
+        const int d = c / k, i = c - d * k;  // contact i of set d
+        uint32_t w[4];
+        auto word = [&](int q) {  // word q of the set's Philox blocks
+            philox4x32_10(gg, (uint32_t)(4 * d + (q >> 2)), kPurposeDraw, request_id, seed_lo, seed_hi, w);
+            return (q & 2) ? ((q & 1) ? w[3] : w[2]) : ((q & 1) ? w[1] : w[0]);
+        };
+        const uint32_t fm = choose_fingers(elig, k, gg, d, request_id, seed_lo, seed_hi);
+        const int f = select_in_word(fm, (uint32_t)i);  // its finger
+        const int idx = select_domain(prefix + f * (nsb + 1), nsb, dom + (int64_t)f * NW, NW,
+                                      __umulhi(word(i), counts[f]));
+        const int64_t at = (int64_t)g * D * k + c;
+        set_pt[at] = idx;
+        set_link[at] = (int8_t)(idx >= 0 ? pick_link(H, L.cb4, L.aff[H.lat ? 0 : f], pts, nrm, N, pose, f, idx,
+                                                     word(k + i))
+                                         : -1);
     }
 }
 
 __global__ void __launch_bounds__(kDrawThreads)
-k_draw(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__ pts, const float *__restrict__ nrm,
+k_draw(DevHand H, const float *__restrict__ pts, const float *__restrict__ nrm,
        int N, const float *__restrict__ poses, const uint32_t *__restrict__ dom_bits,
        const uint32_t *__restrict__ dom_count, const int32_t *__restrict__ palm_pt, int D, int k, uint32_t seed_lo,
        uint32_t seed_hi, uint32_t request_id, int64_t pose_offset, int32_t *__restrict__ set_pt,
@@ -186,9 +258,9 @@ k_draw(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__ p
        double *__restrict__ tstar)
 {
     extern __shared__ uint32_t prefix[];
-    __shared__ float cb[3 * kMaxBins];
+    __shared__ LinkLds L;
     __shared__ uint32_t counts[kMaxFingers];
-    draw_pose(prefix, cb, counts, H, bits, pts, nrm, N, poses, dom_bits, dom_count, palm_pt, D, k, seed_lo, seed_hi,
+    draw_pose(prefix, L, counts, H, pts, nrm, N, poses, dom_bits, dom_count, palm_pt, D, k, seed_lo, seed_hi,
               request_id, pose_offset, set_pt, set_link, pose_valid, verdict, tstar, blockIdx.x);
 }
 
@@ -198,11 +270,11 @@ k_draw_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx, 
              int n)
 {
     extern __shared__ uint32_t prefix[];
-    __shared__ float cb[3 * kMaxBins];
+    __shared__ LinkLds L;
     __shared__ uint32_t counts[kMaxFingers];
     const int j = batch_member(first, n, blockIdx.x);
     const ChunkDesc &c = d[idx[j]];
-    draw_pose(prefix, cb, counts, c.H, c.bits, c.pts, c.nrm, c.N, c.poses, c.dom_bits, c.dom_count, nullptr, c.D,
+    draw_pose(prefix, L, counts, c.H, c.pts, c.nrm, c.N, c.poses, c.dom_bits, c.dom_count, nullptr, c.D,
               c.k, c.seed_lo, c.seed_hi, c.request_id, c.pose_offset, c.set_pt, c.set_link, c.pose_valid, c.verdict,
               c.tstar, (int)(blockIdx.x - first[j]));
 }
@@ -993,19 +1065,6 @@ __device__ inline double wave_min63(double v)
     return v;
 }
 
-// inclusive prefix sum over the lanes (row shifts by 1, 2, 4, 8, then the row
-// broadcasts); lanes without a source add 0
-__device__ inline uint32_t wave_scan_incl(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return x;
-}
-
 // the minimum of (d2, i) over the lanes with `take` (lexicographic), folded
 // into (best, bi); every lane returns the same result
 __device__ inline void wave_lexmin(bool take, double d2, int i, double &best, int &bi)
@@ -1467,13 +1526,17 @@ __global__ void k_opt_pick(const int32_t *__restrict__ valid_poses, const int32_
 
 // links of the (moved) contacts of every set of a pose with non-empty domains,
 // picked with the set's draw words exactly as k_draw does
-__global__ void k_relink(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__ pts,
+__global__ void k_relink(DevHand H, const float *__restrict__ pts,
                          const float *__restrict__ nrm, int N, const float *__restrict__ poses,
                          const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
                          const uint32_t *__restrict__ dom_count, int D, int k, uint32_t seed_lo, uint32_t seed_hi,
                          uint32_t request_id, int64_t pose_offset, const int32_t *__restrict__ set_pt,
                          int8_t *__restrict__ set_link)
 {
+    __shared__ float4 cb4[kMaxBins];
+    for (int i = threadIdx.x; i < H.B; i += blockDim.x)
+        cb4[i] = make_float4(H.bin_c[3 * i], H.bin_c[3 * i + 1], H.bin_c[3 * i + 2], 0.0f);
+    __syncthreads();
     const int64_t n_work = (int64_t)(*n_valid_poses) * D;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_work;
          t += (int64_t)gridDim.x * blockDim.x) {
@@ -1492,7 +1555,8 @@ __global__ void k_relink(DevHand H, const uint32_t *__restrict__ bits, const flo
             fm &= fm - 1u;
             const int idx = sp[i];
             sl[i] = (int8_t)((f >= 0 && idx >= 0 && idx < N)
-                                 ? pick_link(H, bits, H.bin_c, pts, nrm, N, poses + 12 * g, f, idx, w[k + i])
+                                 ? pick_link(H, cb4, window_map(H, poses + 12 * g, f), pts, nrm, N, poses + 12 * g,
+                                             f, idx, w[k + i])
                                  : -1);
         }
     }
@@ -1518,7 +1582,7 @@ __device__ inline int link_finger(const DevHand &H, int l)
 // Sets not extended get set_pt -1, verdict 0, t* NaN; pose_valid[g] = some
 // set of the pose was extended (its verdicts are computed next).
 __global__ void __launch_bounds__(kDrawThreads)
-k_extend(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__ pts, const float *__restrict__ nrm,
+k_extend(DevHand H, const float *__restrict__ pts, const float *__restrict__ nrm,
          int N, const float *__restrict__ poses, const uint32_t *__restrict__ dom_bits,
          const uint32_t *__restrict__ dom_count, int D, int k1, int k_add, const int32_t *__restrict__ set_pt1,
          const int8_t *__restrict__ set_link1, const uint8_t *__restrict__ verdict1, const int32_t *__restrict__ list,
@@ -1527,14 +1591,15 @@ k_extend(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__
          uint8_t *__restrict__ pose_valid, uint8_t *__restrict__ verdict2, double *__restrict__ tstar2)
 {
     extern __shared__ uint32_t prefix[];  // [F][nsb + 1]
-    __shared__ float cb[3 * kMaxBins];
+    __shared__ LinkLds L;
     __shared__ uint32_t counts[kMaxFingers];
     __shared__ int32_t range[2];
     __shared__ uint32_t any;
     const int g = blockIdx.x, F = H.F, k2 = k1 + k_add;
     const int NW = (N + 31) >> 5, nsb = (NW + kSuper - 1) / kSuper;
     const uint32_t *dom = dom_bits + (int64_t)g * F * NW;
-    for (int i = threadIdx.x; i < 3 * H.B; i += blockDim.x) cb[i] = H.bin_c[i];
+    const float *pose = poses + 12 * (int64_t)g;
+    link_lds(L, H, pose);
     if ((int)threadIdx.x < F) counts[threadIdx.x] = dom_count[(int64_t)g * F + threadIdx.x];
     if (threadIdx.x == 0) {
         any = 0;
@@ -1557,7 +1622,6 @@ k_extend(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__
     }
     build_prefix(prefix, dom, F, NW, nsb);
     __syncthreads();
-    const float *pose = poses + 12 * (int64_t)g;
     const uint32_t gg = (uint32_t)(pose_offset + g);
     for (int d = threadIdx.x; d < D; d += blockDim.x) {
         const int64_t sid = (int64_t)g * D + d;
@@ -1611,7 +1675,7 @@ k_extend(DevHand H, const uint32_t *__restrict__ bits, const float *__restrict__
                                           __umulhi(w[i], counts[f]));
             nf[i] = f;
             np[i] = idx;
-            nl[i] = idx >= 0 ? pick_link(H, bits, cb, pts, nrm, N, pose, f, idx, w[k_add + i]) : -1;
+            nl[i] = idx >= 0 ? pick_link(H, L.cb4, L.aff[H.lat ? 0 : f], pts, nrm, N, pose, f, idx, w[k_add + i]) : -1;
         }
         // union in increasing finger order (both groups sorted)
         int a = 0, b = 0;
@@ -1981,7 +2045,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
     const bool split = opt && split_fits(n_poses, p->draws, p) &&
                        workspace_bytes >= search_ws_bytes(n_points, n_poses, p, true);
     const SearchWs ws = search_ws(workspace, n_points, n_poses, p->draws, opt, p->k, opt ? p->opt_inner : 0, split);
-    hipLaunchKernelGGL(k_draw, dim3(n_poses), dim3(kDrawThreads), lds, s, H, field->d_bits, pts, nrm, n_points,
+    hipLaunchKernelGGL(k_draw, dim3(n_poses), dim3(kDrawThreads), lds, s, H, pts, nrm, n_points,
                        poses, dom_bits, dom_count, palm, p->draws, p->k, (uint32_t)p->seed, (uint32_t)(p->seed >> 32),
                        p->request_id, p->pose_offset, set_pt, set_link, ws.pose_valid, verdict, tstar);
     LG_HIP(hipGetLastError());
@@ -2064,7 +2128,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
 #undef LG_OPT
 #undef LG_OPT_M
         LG_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_relink, sgrid, dim3(256), 0, s, H, field->d_bits, pts, nrm, n_points, poses,
+        hipLaunchKernelGGL(k_relink, sgrid, dim3(256), 0, s, H, pts, nrm, n_points, poses,
                            ws.valid_poses, ws.n_valid_poses, dom_count, p->draws, p->k, (uint32_t)p->seed,
                            (uint32_t)(p->seed >> 32), p->request_id, p->pose_offset, set_pt, set_link);
     }
@@ -2158,7 +2222,7 @@ lg_status lg_search_extend(const lg_field *field, const float *pts, const float 
     if (lds > 48 * 1024) return fail(LG_EUNSUPPORTED, "too many points for the draw rank structure");
     hipStream_t s = as_stream(stream);
     const SearchWs ws = search_ws(workspace, n_points, n_poses, p->draws, false);
-    hipLaunchKernelGGL(k_extend, dim3(n_poses), dim3(kDrawThreads), lds, s, H, field->d_bits, pts, nrm, n_points,
+    hipLaunchKernelGGL(k_extend, dim3(n_poses), dim3(kDrawThreads), lds, s, H, pts, nrm, n_points,
                        poses, dom_bits, dom_count, p->draws, k1, ep->k_add, set_pt1, set_link1, verdict1, ep->list,
                        ep->list_n, ep->list_ok, (uint32_t)p->seed, (uint32_t)(p->seed >> 32), ep->request_id,
                        p->pose_offset, set_pt2, set_link2, ws.pose_valid, verdict2, tstar2);

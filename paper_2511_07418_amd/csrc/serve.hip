@@ -415,7 +415,6 @@ static void fill_desc(const lg_server *S, const Req *q, int32_t P, int buf, Chun
     memset(&c, 0, sizeof c);
     c.H = f->dh;
     c.merged = f->d_merged;
-    c.bits = f->d_bits;
     c.wit = f->has_witness ? f->d_wit : nullptr;
     c.pts = reinterpret_cast<const float *>(in + L.pts);
     c.nrm = reinterpret_cast<const float *>(in + L.nrm);
