@@ -538,23 +538,29 @@ __device__ inline int batch_member(const uint32_t *__restrict__ first, int n, ui
 // Batched launchers (one kernel launch each; the member's blocks follow the
 // single-chunk kernel's grid).  Blocks per member:
 //   query, draws: P;  compaction count/scatter: compact_blocks(n);
-//   compaction scan: 1;  verdicts: verdict_blocks;  realize: realize_blocks.
+//   compaction scan: 1;  verdicts: verdict_blocks;  realize: realize_blocks,
+//   penetrate_blocks.
 lg_status query_batch(const BatchLaunch &b, int W, int F, bool lat, hipStream_t s);
 size_t draw_lds_bytes(int F, int N);
 lg_status draw_batch(const BatchLaunch &b, size_t lds, hipStream_t s);
 uint32_t compact_blocks(int64_t n);
-// poses = true: the pose list of the draws; false: the accepted set list
-lg_status compact_count_batch(const BatchLaunch &b, bool poses, hipStream_t s);
-lg_status compact_scan_batch(const BatchLaunch &b, bool poses, hipStream_t s);
-lg_status compact_scatter_batch(const BatchLaunch &b, bool poses, hipStream_t s);
+// poses = true: the pose list of the draws; false: the accepted set list.  form:
+// the largest compact_form of the members' sizes (0: ones only, a block per
+// member; 1: count and scatter over chunks; 2: with a scan between, a block of
+// ones per member).
+int compact_form(int64_t n);
+lg_status compact_batch(const BatchLaunch &chunks, const BatchLaunch &ones, int form, bool poses, hipStream_t s);
 uint32_t verdict_blocks(int64_t n_sets, int n_cu);
 LpConst lp_const(int m);
 // the search workspace's lists of a chunk of P poses (no contact optimisation)
 void chunk_workspace(void *ws, int64_t n_points, int64_t n_poses, int64_t draws, ChunkDesc &c);
 lg_status verdict_batch(const BatchLaunch &b, int km, bool m8, hipStream_t s);  // m8: every chunk has an 8-edge cone
 uint32_t realize_blocks(int64_t max_acc, int F, int n_cu);
+uint32_t penetrate_blocks(int64_t max_acc, int n_cu);
 size_t realize_lds_bytes(int F, int J);
+// b: blocks of the joint steps, pb: of the penetration test (the same members);
 // self_collision: that of every chunk; lds: the largest realize_lds_bytes
-lg_status realize_batch(const BatchLaunch &b, int max_dof, size_t lds, bool self_collision, hipStream_t s);
+lg_status realize_batch(const BatchLaunch &b, const BatchLaunch &pb, int max_dof, size_t lds, bool self_collision,
+                        hipStream_t s);
 
 }  // namespace lg

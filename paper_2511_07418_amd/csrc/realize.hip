@@ -526,9 +526,12 @@ __device__ __forceinline__ void penetrate_sets(
     const int64_t nacc = min((int64_t)*n_acc_dev, (int64_t)max_acc);
     const int first = H.finger_first[f], d = H.finger_dof[f];
     const float gm = (float)(S.G - 1);
-    for (int64_t a0 = (bid * (kRealizeThreads / 64) + wave) * spw; a0 < nacc; a0 += nb * (kRealizeThreads / 64) * spw) {
+    // few sets: fewer than 64 / F per wave, so that every wave has some
+    const int64_t waves = nb * (kRealizeThreads / 64);
+    const int per = (int)max((int64_t)1, min((int64_t)spw, (nacc + waves - 1) / waves));
+    for (int64_t a0 = (bid * (kRealizeThreads / 64) + wave) * per; a0 < nacc; a0 += waves * per) {
         const int64_t a = a0 + slot;
-        const bool mine = slot < spw && a < nacc;
+        const bool mine = slot < per && a < nacc;
         const int64_t id = mine ? acc_list[a] : -1;
         const bool live = id >= 0 && id < n_sets;  // uniform over a set's lanes
         const int g = live ? (int)(id / D) : 0;
@@ -594,7 +597,7 @@ __device__ __forceinline__ void penetrate_sets(
                         dep = fmaxf(dep, pen);
                     }
             }
-        const int n_slots = (int)min((int64_t)spw, nacc - a0);
+        const int n_slots = (int)min((int64_t)per, nacc - a0);
         for (int sl = 0; sl < n_slots; ++sl) {
             const int n = __builtin_amdgcn_readlane(total, sl * F);
             if (n == 0) continue;  // not a set, or no sample in the grid
@@ -745,11 +748,12 @@ extern "C" lg_status lg_realize(const lg_field *field, const lg_sdf *sdf, const 
         LG_REALIZE(k_realize_wide);
 #undef LG_REALIZE
     const size_t lds = penetrate_lds(H.F, H.J);
+    const dim3 pgrid(penetrate_blocks(max_acc, n_cu));
     if (ik.self_collision)
-        hipLaunchKernelGGL(k_penetrate<true>, grid, dim3(kRealizeThreads), lds, s, H, S, poses, k, draws, n_sets, acc_list,
+        hipLaunchKernelGGL(k_penetrate<true>, pgrid, dim3(kRealizeThreads), lds, s, H, S, poses, k, draws, n_sets, acc_list,
                            n_acc_dev, max_acc, ik, q_out, contact_err, contact_ang, depth, valid);
     else
-        hipLaunchKernelGGL(k_penetrate<false>, grid, dim3(kRealizeThreads), lds, s, H, S, poses, k, draws, n_sets, acc_list,
+        hipLaunchKernelGGL(k_penetrate<false>, pgrid, dim3(kRealizeThreads), lds, s, H, S, poses, k, draws, n_sets, acc_list,
                            n_acc_dev, max_acc, ik, q_out, contact_err, contact_ang, depth, valid);
     LG_HIP(hipGetLastError());
     return LG_OK;
@@ -764,7 +768,15 @@ uint32_t lg::realize_blocks(int64_t max_acc, int F, int n_cu)
     return (uint32_t)std::max<int64_t>(1, (threads + kRealizeThreads - 1) / kRealizeThreads);
 }
 
-lg_status lg::realize_batch(const BatchLaunch &b, int max_dof, size_t lds, bool self_collision, hipStream_t s)
+// Blocks of the penetration test: at most what is resident (16 waves a CU), down to
+// a set per wave (1,000 sets of 3 fingers: 40 us with 21 sets per wave).
+uint32_t lg::penetrate_blocks(int64_t max_acc, int n_cu)
+{
+    return (uint32_t)std::max<int64_t>(1, std::min<int64_t>((max_acc + 3) / 4, (int64_t)n_cu * 4));
+}
+
+lg_status lg::realize_batch(const BatchLaunch &b, const BatchLaunch &pb, int max_dof, size_t lds, bool self_collision,
+                            hipStream_t s)
 {
     if (b.n <= 0 || b.blocks == 0) return LG_OK;
     if (max_dof <= 4)
@@ -776,9 +788,11 @@ lg_status lg::realize_batch(const BatchLaunch &b, int max_dof, size_t lds, bool 
     else
         hipLaunchKernelGGL(k_realize_batch<8>, dim3(b.blocks), dim3(kRealizeThreads), 0, s, b.d, b.idx, b.first, b.n);
     if (self_collision)
-        hipLaunchKernelGGL(k_penetrate_batch<true>, dim3(b.blocks), dim3(kRealizeThreads), lds, s, b.d, b.idx, b.first, b.n);
+        hipLaunchKernelGGL(k_penetrate_batch<true>, dim3(pb.blocks), dim3(kRealizeThreads), lds, s, pb.d, pb.idx,
+                           pb.first, pb.n);
     else
-        hipLaunchKernelGGL(k_penetrate_batch<false>, dim3(b.blocks), dim3(kRealizeThreads), lds, s, b.d, b.idx, b.first, b.n);
+        hipLaunchKernelGGL(k_penetrate_batch<false>, dim3(pb.blocks), dim3(kRealizeThreads), lds, s, pb.d, pb.idx,
+                           pb.first, pb.n);
     LG_HIP(hipGetLastError());
     return LG_OK;
 }

@@ -1707,14 +1707,86 @@ __global__ void k_flag_unstable(const int32_t *__restrict__ set_pt, const int8_t
 }
 
 // ---- compaction ------------------------------------------------------------
-// block bid: the number of nonzero flags in its kChunk flags
+// Flags are bytes of value 0 or 1.  The 16 flags from i on (i a multiple of 16),
+// those at n and beyond 0: one load where the array allows it (al: its alignment,
+// 16, 4 or 1).
+__device__ inline uint4 flags16(const uint8_t *__restrict__ flag, int64_t i, int64_t n, int al)
+{
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (i + 16 <= n && al >= 4) {
+        if (al == 16) return *reinterpret_cast<const uint4 *>(flag + i);
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(flag + i);
+        return make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        if (i + q < n) w[q >> 2] |= (uint32_t)flag[i + q] << (8 * (q & 3));
+    v = make_uint4(w[0], w[1], w[2], w[3]);
+    return v;
+}
+__device__ inline int flag_alignment(const uint8_t *flag)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(flag);
+    return a % 16 == 0 ? 16 : a % 4 == 0 ? 4 : 1;
+}
+__device__ inline uint32_t flags_count(const uint4 &v) { return __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w); }
+// the indices of the set flags of v (flags i.. of the array) from list[pos] on
+__device__ inline void flags_write(const uint4 &v, int64_t i, int32_t *__restrict__ list, uint32_t &pos)
+{
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        for (uint32_t x = w[q]; x; x &= x - 1u) list[pos++] = (int32_t)(i + 4 * q + ((__ffs(x) - 1) >> 3));
+}
+
+// Up to kCompactOneMax flags: one block of 1,024 threads, a run of flags each (a
+// multiple of 16), counts scanned over lanes and waves, then each thread writes
+// its run's indices.  A few thousand flags take 3-4 us in one launch (18 us in the
+// three of count, scan and scatter); beyond the limit one CU's reads and writes
+// cost more than they save (65,536 flags 21 us, 262,144 47 us; two launches 10 us).
+constexpr int kCompactOneThreads = 1024;
+constexpr int64_t kCompactOneMax = 32768;
+constexpr int64_t kSelfScanMax = 2048;  // chunks whose counts every scatter block adds up itself (4 us less)
+
+__device__ __forceinline__ void compact_one_block(uint32_t *wsum, const uint8_t *__restrict__ flag, int64_t n,
+                                                  int32_t *__restrict__ list, int32_t *__restrict__ total)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, al = flag_alignment(flag);
+    const int64_t per = ((n + kCompactOneThreads - 1) / kCompactOneThreads + 15) & ~(int64_t)15;
+    const int64_t beg = min(n, tid * per), end = min(n, beg + per);
+    uint32_t c = 0;
+#pragma unroll 4
+    for (int64_t i = beg; i < end; i += 16) c += flags_count(flags16(flag, i, n, al));
+    const uint32_t incl = wave_scan_incl(c);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t pos = incl - c, all = 0;
+    for (int w = 0; w < kCompactOneThreads / 64; ++w) {
+        pos += w < wave ? wsum[w] : 0u;
+        all += wsum[w];
+    }
+    if (tid == 0) *total = (int32_t)all;
+    if (c)
+        for (int64_t i = beg; i < end; i += 16) flags_write(flags16(flag, i, n, al), i, list, pos);
+}
+
+__global__ void __launch_bounds__(kCompactOneThreads)
+k_compact_one(const uint8_t *__restrict__ flag, int64_t n, int32_t *__restrict__ list, int32_t *__restrict__ total)
+{
+    __shared__ uint32_t wsum[kCompactOneThreads / 64];
+    compact_one_block(wsum, flag, n, list, total);
+}
+
+// block bid: the number of set flags in its kChunk flags
 __device__ __forceinline__ void chunk_count_block(uint32_t *part, int64_t bid, const uint8_t *__restrict__ flag,
                                                   int64_t n, uint32_t *__restrict__ chunk_count)
 {
     const int64_t base = bid * kChunk + (int64_t)threadIdx.x * kChunkPerThread;
+    const int al = flag_alignment(flag);
     uint32_t c = 0;
-    for (int i = 0; i < kChunkPerThread; ++i)
-        if (base + i < n) c += flag[base + i] != 0;
+#pragma unroll
+    for (int i = 0; i < kChunkPerThread; i += 16) c += flags_count(flags16(flag, base + i, n, al));
     for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -1753,27 +1825,41 @@ __device__ __forceinline__ void chunk_scan_block(uint32_t *tot, const uint32_t *
     }
 }
 
-// block bid: the indices of its nonzero flags, in order, from chunk_off[bid]
-__device__ __forceinline__ void chunk_scatter_block(uint32_t *pre, int64_t bid, const uint8_t *__restrict__ flag,
-                                                    int64_t n, const uint32_t *__restrict__ chunk_off,
-                                                    int32_t *__restrict__ list)
+// Block bid: the indices of its set flags, in order.  off: the chunks' offsets
+// (of chunk_scan_block), or, for at most kSelfScanMax chunks (self), their counts:
+// the block adds up those before it, and the last one writes the total.
+__device__ __forceinline__ void chunk_scatter_block(uint32_t *wsum, int64_t bid, const uint8_t *__restrict__ flag,
+                                                    int64_t n, const uint32_t *__restrict__ off, bool self,
+                                                    int32_t *__restrict__ list, int32_t *__restrict__ total)
 {
     const int64_t base = bid * kChunk + (int64_t)threadIdx.x * kChunkPerThread;
-    uint32_t c = 0;
-    for (int i = 0; i < kChunkPerThread; ++i)
-        if (base + i < n) c += flag[base + i] != 0;
-    pre[threadIdx.x] = c;
-    __syncthreads();
-    // Hillis-Steele inclusive scan over the block
-    for (int off = 1; off < kCompactThreads; off <<= 1) {
-        const uint32_t v = threadIdx.x >= off ? pre[threadIdx.x - off] : 0u;
-        __syncthreads();
-        pre[threadIdx.x] += v;
-        __syncthreads();
+    const int al = flag_alignment(flag), wave = threadIdx.x >> 6;
+    uint32_t before = 0;
+    if (self) {
+        for (int64_t i = threadIdx.x; i < bid; i += kCompactThreads) before += off[i];
+        for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+        if ((threadIdx.x & 63) == 0) wsum[kCompactThreads / 64 + wave] = before;
     }
-    uint32_t pos = chunk_off[bid] + pre[threadIdx.x] - c;
-    for (int i = 0; i < kChunkPerThread; ++i)
-        if (base + i < n && flag[base + i]) list[pos++] = (int32_t)(base + i);
+    uint4 v[kChunkPerThread / 16];
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < kChunkPerThread / 16; ++i) {
+        v[i] = flags16(flag, base + 16 * i, n, al);
+        c += flags_count(v[i]);
+    }
+    const uint32_t incl = wave_scan_incl(c);
+    if ((threadIdx.x & 63) == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t pos = incl - c;
+    if (self) {
+        for (int w = 0; w < kCompactThreads / 64; ++w) pos += wsum[kCompactThreads / 64 + w];
+    } else {
+        pos += off[bid];
+    }
+    for (int w = 0; w < wave; ++w) pos += wsum[w];
+    if (self && (bid + 1) * kChunk >= n && threadIdx.x == kCompactThreads - 1) *total = (int32_t)(pos + c);
+#pragma unroll
+    for (int i = 0; i < kChunkPerThread / 16; ++i) flags_write(v[i], base + 16 * i, list, pos);
 }
 
 __global__ void __launch_bounds__(kCompactThreads)
@@ -1792,11 +1878,11 @@ k_chunk_scan(const uint32_t *__restrict__ chunk_count, int64_t n_chunks, uint32_
 }
 
 __global__ void __launch_bounds__(kCompactThreads)
-k_chunk_scatter(const uint8_t *__restrict__ verdict, int64_t n, const uint32_t *__restrict__ chunk_off,
-                int32_t *__restrict__ acc_list)
+k_chunk_scatter(const uint8_t *__restrict__ verdict, int64_t n, const uint32_t *__restrict__ off, bool self,
+                int32_t *__restrict__ acc_list, int32_t *__restrict__ n_acc)
 {
-    __shared__ uint32_t pre[kCompactThreads];
-    chunk_scatter_block(pre, blockIdx.x, verdict, n, chunk_off, acc_list);
+    __shared__ uint32_t wsum[2 * kCompactThreads / 64];
+    chunk_scatter_block(wsum, blockIdx.x, verdict, n, off, self, acc_list, n_acc);
 }
 
 // Batched compaction: POSES = the chunk's poses with a usable draw (the
@@ -1813,6 +1899,17 @@ __device__ __forceinline__ CompactView compact_view(const ChunkDesc &c)
 {
     if (POSES) return {c.pose_valid, (int64_t)c.P, c.pchunk_count, c.pchunk_off, c.n_valid_poses, c.valid_poses};
     return {c.verdict, (int64_t)c.P * c.D, c.chunk_count, c.chunk_off, c.n_acc, c.acc};
+}
+
+// every member in one block of its own
+template <bool POSES>
+__global__ void __launch_bounds__(kCompactOneThreads)
+k_compact_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx, const uint32_t *__restrict__ first,
+                int n)
+{
+    __shared__ uint32_t wsum[kCompactOneThreads / 64];
+    const CompactView v = compact_view<POSES>(d[idx[batch_member(first, n, blockIdx.x)]]);
+    compact_one_block(wsum, v.flag, v.n, v.list, v.total);
 }
 
 template <bool POSES>
@@ -1840,17 +1937,36 @@ k_scan_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx, 
 template <bool POSES>
 __global__ void __launch_bounds__(kCompactThreads)
 k_scatter_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx, const uint32_t *__restrict__ first,
-                int n)
+                int n, bool self)
 {
-    __shared__ uint32_t pre[kCompactThreads];
+    __shared__ uint32_t wsum[2 * kCompactThreads / 64];
     const int j = batch_member(first, n, blockIdx.x);
     const CompactView v = compact_view<POSES>(d[idx[j]]);
-    chunk_scatter_block(pre, blockIdx.x - first[j], v.flag, v.n, v.off, v.list);
+    chunk_scatter_block(wsum, blockIdx.x - first[j], v.flag, v.n, self ? v.count : v.off, self, v.list, v.total);
 }
 
 }  // namespace lg
 
 using namespace lg;
+
+// list = the increasing indices of the n flags that are set, *total their number;
+// count, off: a word per kChunk flags (beyond kCompactOneMax)
+static lg_status compact(const uint8_t *flag, int64_t n, uint32_t *count, uint32_t *off, int32_t *list, int32_t *total,
+                         hipStream_t s)
+{
+    if (n <= kCompactOneMax) {
+        hipLaunchKernelGGL(k_compact_one, dim3(1), dim3(kCompactOneThreads), 0, s, flag, n, list, total);
+    } else {
+        const int64_t nc = (n + kChunk - 1) / kChunk;
+        hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)nc), dim3(kCompactThreads), 0, s, flag, n, count);
+        const bool self = nc <= kSelfScanMax;
+        if (!self) hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kCompactThreads), 0, s, count, nc, off, total);
+        hipLaunchKernelGGL(k_chunk_scatter, dim3((unsigned)nc), dim3(kCompactThreads), 0, s, flag, n,
+                           self ? count : off, self, list, total);
+    }
+    LG_HIP(hipGetLastError());
+    return LG_OK;
+}
 
 extern "C" {
 
@@ -2050,14 +2166,8 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
                        p->request_id, p->pose_offset, set_pt, set_link, ws.pose_valid, verdict, tstar);
     LG_HIP(hipGetLastError());
     // list of poses with at least k non-empty domains (ordered)
-    const int64_t npc = (n_poses + kChunk - 1) / kChunk;
-    hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)npc), dim3(kCompactThreads), 0, s, ws.pose_valid,
-                       (int64_t)n_poses, ws.pchunk_count);
-    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kCompactThreads), 0, s, ws.pchunk_count, npc, ws.pchunk_off,
-                       ws.n_valid_poses);
-    hipLaunchKernelGGL(k_chunk_scatter, dim3((unsigned)npc), dim3(kCompactThreads), 0, s, ws.pose_valid,
-                       (int64_t)n_poses, ws.pchunk_off, ws.valid_poses);
-    LG_HIP(hipGetLastError());
+    lg_status st = compact(ws.pose_valid, n_poses, ws.pchunk_count, ws.pchunk_off, ws.valid_poses, ws.n_valid_poses, s);
+    if (st != LG_OK) return st;
     const int64_t n_sets = (int64_t)n_poses * p->draws;
     const LpConst cs = lp_const(p->m_edges);
     // grid-stride LP launch sized to the device (the valid count is on the device)
@@ -2135,16 +2245,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
 #undef LG_VERDICT
 #undef LG_VERDICT_M
     LG_HIP(hipGetLastError());
-    const int64_t n_chunks = (n_sets + kChunk - 1) / kChunk;
-    uint32_t *chunk_count = ws.chunk_count;
-    uint32_t *chunk_off = ws.chunk_off;
-    hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)n_chunks), dim3(kCompactThreads), 0, s, verdict, n_sets,
-                       chunk_count);
-    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kCompactThreads), 0, s, chunk_count, n_chunks, chunk_off, n_acc);
-    hipLaunchKernelGGL(k_chunk_scatter, dim3((unsigned)n_chunks), dim3(kCompactThreads), 0, s, verdict, n_sets,
-                       chunk_off, acc_list);
-    LG_HIP(hipGetLastError());
-    return LG_OK;
+    return compact(verdict, n_sets, ws.chunk_count, ws.chunk_off, acc_list, n_acc, s);
 }
 
 // Bytes of device workspace of lg_compact_unstable: set flags, chunk counts and offsets.
@@ -2183,11 +2284,8 @@ lg_status lg_compact_unstable(const int32_t *set_pt, const int8_t *set_link, con
     const int64_t nc = (n_sets + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(k_flag_unstable, dim3((unsigned)((n_sets + 255) / 256)), dim3(256), 0, s, set_pt, set_link,
                        verdict, n_sets, k, flag);
-    hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)nc), dim3(kCompactThreads), 0, s, flag, n_sets, cc);
-    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kCompactThreads), 0, s, cc, nc, cc + nc, n_list);
-    hipLaunchKernelGGL(k_chunk_scatter, dim3((unsigned)nc), dim3(kCompactThreads), 0, s, flag, n_sets, cc + nc, list);
     LG_HIP(hipGetLastError());
-    return LG_OK;
+    return compact(flag, n_sets, cc, cc + nc, list, n_list, s);
 }
 
 lg_status lg_search_extend(const lg_field *field, const float *pts, const float *nrm, int32_t n_points,
@@ -2227,13 +2325,9 @@ lg_status lg_search_extend(const lg_field *field, const float *pts, const float 
                        ep->list_n, ep->list_ok, (uint32_t)p->seed, (uint32_t)(p->seed >> 32), ep->request_id,
                        p->pose_offset, set_pt2, set_link2, ws.pose_valid, verdict2, tstar2);
     LG_HIP(hipGetLastError());
-    const int64_t npc = (n_poses + kChunk - 1) / kChunk;
-    hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)npc), dim3(kCompactThreads), 0, s, ws.pose_valid,
-                       (int64_t)n_poses, ws.pchunk_count);
-    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kCompactThreads), 0, s, ws.pchunk_count, npc, ws.pchunk_off,
-                       ws.n_valid_poses);
-    hipLaunchKernelGGL(k_chunk_scatter, dim3((unsigned)npc), dim3(kCompactThreads), 0, s, ws.pose_valid,
-                       (int64_t)n_poses, ws.pchunk_off, ws.valid_poses);
+    const lg_status st =
+        compact(ws.pose_valid, n_poses, ws.pchunk_count, ws.pchunk_off, ws.valid_poses, ws.n_valid_poses, s);
+    if (st != LG_OK) return st;
     const int64_t n_sets = (int64_t)n_poses * p->draws;
     LpConst cs;
     for (int e = 0; e < 16; ++e) {
@@ -2256,15 +2350,7 @@ lg_status lg_search_extend(const lg_field *field, const float *pts, const float 
 #undef LG_VERDICT2
 #undef LG_VERDICT2_M
     LG_HIP(hipGetLastError());
-    const int64_t n_chunks = (n_sets + kChunk - 1) / kChunk;
-    hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)n_chunks), dim3(kCompactThreads), 0, s, verdict2, n_sets,
-                       ws.chunk_count);
-    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kCompactThreads), 0, s, ws.chunk_count, n_chunks, ws.chunk_off,
-                       n_acc2);
-    hipLaunchKernelGGL(k_chunk_scatter, dim3((unsigned)n_chunks), dim3(kCompactThreads), 0, s, verdict2, n_sets,
-                       ws.chunk_off, acc_list2);
-    LG_HIP(hipGetLastError());
-    return LG_OK;
+    return compact(verdict2, n_sets, ws.chunk_count, ws.chunk_off, acc_list2, n_acc2, s);
 }
 
 }  // extern "C"
@@ -2345,37 +2431,29 @@ lg_status lg::draw_batch(const BatchLaunch &b, size_t lds, hipStream_t s)
     return LG_OK;
 }
 
-lg_status lg::compact_count_batch(const BatchLaunch &b, bool poses, hipStream_t s)
+int lg::compact_form(int64_t n)
 {
-    if (b.n <= 0 || b.blocks == 0) return LG_OK;
-    if (poses)
-        hipLaunchKernelGGL(k_count_batch<true>, dim3(b.blocks), dim3(kCompactThreads), 0, s, b.d, b.idx, b.first, b.n);
-    else
-        hipLaunchKernelGGL(k_count_batch<false>, dim3(b.blocks), dim3(kCompactThreads), 0, s, b.d, b.idx, b.first, b.n);
-    LG_HIP(hipGetLastError());
-    return LG_OK;
+    return n <= kCompactOneMax ? 0 : (n + kChunk - 1) / kChunk <= kSelfScanMax ? 1 : 2;
 }
 
-lg_status lg::compact_scan_batch(const BatchLaunch &b, bool poses, hipStream_t s)
+lg_status lg::compact_batch(const BatchLaunch &chunks, const BatchLaunch &ones, int form, bool poses, hipStream_t s)
 {
-    if (b.n <= 0 || b.blocks == 0) return LG_OK;
-    if (poses)
-        hipLaunchKernelGGL(k_scan_batch<true>, dim3(b.blocks), dim3(kCompactThreads), 0, s, b.d, b.idx, b.first, b.n);
-    else
-        hipLaunchKernelGGL(k_scan_batch<false>, dim3(b.blocks), dim3(kCompactThreads), 0, s, b.d, b.idx, b.first, b.n);
-    LG_HIP(hipGetLastError());
-    return LG_OK;
-}
-
-lg_status lg::compact_scatter_batch(const BatchLaunch &b, bool poses, hipStream_t s)
-{
-    if (b.n <= 0 || b.blocks == 0) return LG_OK;
-    if (poses)
-        hipLaunchKernelGGL(k_scatter_batch<true>, dim3(b.blocks), dim3(kCompactThreads), 0, s, b.d, b.idx, b.first,
-                           b.n);
-    else
-        hipLaunchKernelGGL(k_scatter_batch<false>, dim3(b.blocks), dim3(kCompactThreads), 0, s, b.d, b.idx, b.first,
-                           b.n);
+    if (ones.n <= 0 || ones.blocks == 0) return LG_OK;
+#define LG_COMPACT(K, B, T, ...)                                                                                 \
+    do {                                                                                                         \
+        if (poses)                                                                                               \
+            hipLaunchKernelGGL(K<true>, dim3(B.blocks), dim3(T), 0, s, B.d, B.idx, B.first, B.n __VA_ARGS__);   \
+        else                                                                                                     \
+            hipLaunchKernelGGL(K<false>, dim3(B.blocks), dim3(T), 0, s, B.d, B.idx, B.first, B.n __VA_ARGS__);  \
+    } while (0)
+    if (form == 0) {
+        LG_COMPACT(k_compact_batch, ones, kCompactOneThreads);
+    } else {
+        LG_COMPACT(k_count_batch, chunks, kCompactThreads);
+        if (form == 2) LG_COMPACT(k_scan_batch, ones, kCompactThreads);
+        LG_COMPACT(k_scatter_batch, chunks, kCompactThreads, , form == 1);
+    }
+#undef LG_COMPACT
     LG_HIP(hipGetLastError());
     return LG_OK;
 }

@@ -509,6 +509,7 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
         int rep;  // a member: its field and parameters give the bucket
     };
     std::vector<Keyed> lq, lv, lr;
+    std::vector<BatchLaunch> lp;  // the penetration launch of each of lr
     BatchLaunch ld, pc, ps, sc, ss, la;
     lg_status st;
     auto one = [](const ChunkDesc &) { return 1u; };
@@ -518,6 +519,7 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
     const int ncu = S->n_cu;
     auto lp_blocks = [ncu](const ChunkDesc &c) { return verdict_blocks((int64_t)c.P * c.D, ncu); };
     auto ik_blocks = [ncu](const ChunkDesc &c) { return realize_blocks((int64_t)c.P * c.D, c.H.F, ncu); };
+    auto pen_blocks = [ncu](const ChunkDesc &c) { return penetrate_blocks((int64_t)c.P * c.D, ncu); };
     auto acc_blocks = [](const ChunkDesc &c) {
         return (uint32_t)std::max<int64_t>(1, std::min<int64_t>(64, ((int64_t)c.P * c.D + 4095) / 4096));
     };
@@ -526,14 +528,19 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
         if ((st = T.list(g, blocks(g, poses), lq.back().b)) != LG_OK) return st;
     }
     if ((st = T.list(all, blocks(all, poses), ld)) != LG_OK) return st;
-    if ((st = T.list(all, blocks(all, pose_chunks), pc)) != LG_OK) return st;
+    int form_p = 0, form_s = 0;
+    for (int m : all) {
+        form_p = std::max(form_p, compact_form(cd[m].P));
+        form_s = std::max(form_s, compact_form((int64_t)cd[m].P * cd[m].D));
+    }
+    if (form_p && (st = T.list(all, blocks(all, pose_chunks), pc)) != LG_OK) return st;
     if ((st = T.list(all, blocks(all, one), ps)) != LG_OK) return st;
     // verdict launches by contact-count class and by whether the cone has 8 edges
     for (auto &g : buckets(all, [&](int m) { return (km_bucket(cd[m].k) << 1) | (cd[m].m == 8 ? 1 : 0); })) {
         lv.push_back({BatchLaunch{}, g[0]});
         if ((st = T.list(g, blocks(g, lp_blocks), lv.back().b)) != LG_OK) return st;
     }
-    if ((st = T.list(all, blocks(all, set_chunks), sc)) != LG_OK) return st;
+    if (form_s && (st = T.list(all, blocks(all, set_chunks), sc)) != LG_OK) return st;
     if ((st = T.list(all, blocks(all, one), ss)) != LG_OK) return st;
     std::vector<int> rz;
     for (int m : all)
@@ -543,6 +550,8 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
     for (auto &g : buckets(rz, [&](int m) { return (dm_bucket(max_dof(m)) << 1) | (cd[m].ik.self_collision ? 1 : 0); })) {
         lr.push_back({BatchLaunch{}, g[0]});
         if ((st = T.list(g, blocks(g, ik_blocks), lr.back().b)) != LG_OK) return st;
+        lp.push_back(BatchLaunch{});
+        if ((st = T.list(g, blocks(g, pen_blocks), lp.back())) != LG_OK) return st;
     }
     if ((st = T.list(all, blocks(all, acc_blocks), la)) != LG_OK) return st;
     size_t lds = 0;
@@ -556,18 +565,17 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
         if ((st = query_batch(g.b, H.W, H.F, H.lat != 0, B.s)) != LG_OK) return st;
     }
     if ((st = draw_batch(ld, lds, B.s)) != LG_OK) return st;
-    if ((st = compact_count_batch(pc, true, B.s)) != LG_OK) return st;
-    if ((st = compact_scan_batch(ps, true, B.s)) != LG_OK) return st;
-    if ((st = compact_scatter_batch(pc, true, B.s)) != LG_OK) return st;
+    if ((st = compact_batch(pc, ps, form_p, true, B.s)) != LG_OK) return st;
     for (const Keyed &g : lv)
         if ((st = verdict_batch(g.b, cd[g.rep].k, cd[g.rep].m == 8, B.s)) != LG_OK) return st;
-    if ((st = compact_count_batch(sc, false, B.s)) != LG_OK) return st;
-    if ((st = compact_scan_batch(ss, false, B.s)) != LG_OK) return st;
-    if ((st = compact_scatter_batch(sc, false, B.s)) != LG_OK) return st;
+    if ((st = compact_batch(sc, ss, form_s, false, B.s)) != LG_OK) return st;
     size_t seg_lds = 0;
     for (int m : rz) seg_lds = std::max(seg_lds, realize_lds_bytes(cd[m].H.F, cd[m].H.J));
-    for (const Keyed &g : lr)
-        if ((st = realize_batch(g.b, max_dof(g.rep), seg_lds, cd[g.rep].ik.self_collision != 0, B.s)) != LG_OK) return st;
+    for (size_t i = 0; i < lr.size(); ++i) {
+        const Keyed &g = lr[i];
+        if ((st = realize_batch(g.b, lp[i], max_dof(g.rep), seg_lds, cd[g.rep].ik.self_collision != 0, B.s)) != LG_OK)
+            return st;
+    }
     if (la.blocks) {
         hipLaunchKernelGGL(k_accumulate_batch, dim3(la.blocks), dim3(kAccThreads), 0, B.s, la.d, la.idx, la.first, la.n);
         LG_HIP(hipGetLastError());
