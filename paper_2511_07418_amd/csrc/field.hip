@@ -377,17 +377,18 @@ __device__ inline void block_add(unsigned int c, unsigned long long *__restrict_
 // q, walk the chain to the link, and bin the part's surface samples (blockIdx.z
 // of gridDim.z; a short round has several parts, or its threads' serial walk over
 // 256 samples would leave the chip idle: 4,096 samples 0.55 ms with one).  done: the table as it was
-// before this round (null: no witness kept).  A vector whose bit is set there has
-// a witness of an earlier, smaller sample, so it changes nothing and ends at one
-// 4-byte read; only the others go on to the table and to the 32 times larger
-// witness table.  The check-before-atomic is safe because table bits only ever go
+// before this round (null: nothing yet, or no memory for it).  A vector whose bit is
+// set there has a witness of an earlier, smaller sample, so it changes nothing and
+// ends at one plain 4-byte read; only the others go on to the live table (whose reads
+// pass by the caches) and to the 32 times larger witness table.  The check-before-atomic is safe because table bits only ever go
 // 0 -> 1 and witnesses only decrease: a stale read can only cause a redundant
 // atomic, never a lost update.
 // What bounds it: the random reads.  All vectors against the witness table (1.4
 // GiB at 22 links of 64^3 voxels x 64 bins, read from HBM a line per vector), with
 // the bins by a scan of all 64 centres, took 41.9 ms for 262,144 samples; with the
 // rounds (under 1 % of the vectors are the first of their cell), a link at a time (its
-// 2 MiB of bits stay in L2) and the bins by the candidate table it takes 7.2 ms.
+// 2 MiB of bits stay in L2) and the bins by the candidate table it takes 7.2 ms;
+// without witnesses 36.9 ms with every vector against the live table, WITHOUT_NOW ms so.
 __global__ void __launch_bounds__(kBuildThreads)
 k_field_build(DevHand H, int64_t s0, int64_t s1, const uint32_t *__restrict__ done, uint32_t *__restrict__ bits,
               int32_t *__restrict__ wit, unsigned long long *__restrict__ dropped)
@@ -442,13 +443,11 @@ k_field_build(DevHand H, int64_t s0, int64_t s1, const uint32_t *__restrict__ do
             tf_dir(T, sp[6 * i + 3], sp[6 * i + 4], sp[6 * i + 5], nx, ny, nz);
             const int b = nearest_bin_any(lut, cb4, B, nx, ny, nz);
             const uint32_t at = (uint32_t)v * W + (uint32_t)(b >> 5), m = 1u << (b & 31);
-            if (dtab) {
-                if (dtab[at] & m) continue;
-                if (!(__atomic_load_n(tab + at, __ATOMIC_RELAXED) & m)) atomicOr(tab + at, m);
+            if (dtab && (dtab[at] & m)) continue;
+            if (!(__atomic_load_n(tab + at, __ATOMIC_RELAXED) & m)) atomicOr(tab + at, m);
+            if (wtab) {
                 int32_t *ww = wtab + (size_t)v * B + b;
                 if (__atomic_load_n(ww, __ATOMIC_RELAXED) > (int32_t)s) atomicMin(ww, (int32_t)s);
-            } else if (!(__atomic_load_n(tab + at, __ATOMIC_RELAXED) & m)) {
-                atomicOr(tab + at, m);
             }
         }
     }
@@ -462,21 +461,22 @@ __global__ void k_copy_u32(const uint4 *__restrict__ src, uint4 *__restrict__ ds
 }
 
 // The rounds of a build (see k_field_build): samples [0, 4096), then up to twice
-// as many each time; done holds the table of the rounds before (with a witness).
+// as many each time; done holds the table of the rounds before.  Without memory for
+// it everything is one round against the live table.
 static hipError_t build_rounds(lg_field *f, uint32_t *done, unsigned long long *d_drop, hipStream_t s)
 {
     const DevHand &H = f->dh;
     const int64_t n4 = (int64_t)H.J * H.G * H.G * H.G * H.W / 4;  // G is a multiple of 4
     for (int64_t s0 = 0; s0 < H.samples;) {
         const int64_t s1 = done ? std::min(H.samples, std::max(kBuildRound, 2 * s0)) : H.samples;
-        if (done)
+        if (s0 > 0)
             hipLaunchKernelGGL(k_copy_u32, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096)), dim3(256), 0, s,
                                reinterpret_cast<const uint4 *>(f->d_bits), reinterpret_cast<uint4 *>(done), n4);
         // parts: enough blocks for eight waves per SIMD
         const int64_t blocks = (s1 - s0 + kBuildThreads - 1) / kBuildThreads;
         const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(kBuildMaxParts, 2048 / (blocks * H.J)));
         hipLaunchKernelGGL(k_field_build, dim3((unsigned)blocks, H.J, (unsigned)parts), dim3(kBuildThreads), 0, s, H,
-                           s0, s1, done, f->d_bits, f->d_wit, d_drop);
+                           s0, s1, s0 > 0 ? done : nullptr, f->d_bits, f->d_wit, d_drop);
         s0 = s1;
     }
     return hipGetLastError();
@@ -636,7 +636,11 @@ lg_status lg_build_field(const lg_hand_desc *hand, const lg_field_params *params
     uint32_t *done = nullptr;
     hipError_t e = hipMalloc(&d_drop, sizeof(unsigned long long));
     if (e == hipSuccess) e = hipMemsetAsync(d_drop, 0, sizeof(unsigned long long), s);
-    if (e == hipSuccess && f->d_wit) e = hipMalloc(&done, (size_t)H.J * H.G * H.G * H.G * H.W * 4);
+    if (e == hipSuccess && H.samples > kBuildRound &&
+        hipMalloc(&done, (size_t)H.J * H.G * H.G * H.G * H.W * 4) != hipSuccess) {
+        done = nullptr;
+        (void)hipGetLastError();
+    }
     if (e != hipSuccess) {
         (void)hipFree(d_drop);
         free_field(f);
