@@ -388,7 +388,7 @@ __device__ inline void block_add(unsigned int c, unsigned long long *__restrict_
 // the bins by a scan of all 64 centres, took 41.9 ms for 262,144 samples; with the
 // rounds (under 1 % of the vectors are the first of their cell), a link at a time (its
 // 2 MiB of bits stay in L2) and the bins by the candidate table it takes 7.2 ms;
-// without witnesses 36.9 ms with every vector against the live table, WITHOUT_NOW ms so.
+// without witnesses 36.9 ms with every vector against the live table, 6.0 ms so.
 __global__ void __launch_bounds__(kBuildThreads)
 k_field_build(DevHand H, int64_t s0, int64_t s1, const uint32_t *__restrict__ done, uint32_t *__restrict__ bits,
               int32_t *__restrict__ wit, unsigned long long *__restrict__ dropped)

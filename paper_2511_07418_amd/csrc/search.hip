@@ -891,22 +891,29 @@ k_verdict_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ id
 }
 
 // ---- contact-point optimisation (Sec. 5.4, Alg. 2) ---------------------------
-// A uniform cell grid over the object's points serves the projection of a
-// candidate onto a contact domain (nearest domain point).  Cells are cubes of
-// edge c = max(sigma, extent / kGridMax); points are bucketed by a counting
-// sort.  The search scans shells of cells at Chebyshev distance R = 0, 1, ...
-// around the candidate's cell; points in unscanned cells are at least R c away,
-// so once the best distance is below R c (less a rounding margin) it is exact
-// (project_domain_wave).  Distances are FP64, ties go to the lowest point index.
+// A cell grid over the object's points serves the projection of a candidate onto a
+// contact domain (nearest domain point): rows of cells along x, of edge c across a
+// row and c / 2 along it; a row's points are contiguous, so a search reads any
+// stretch of a row as one range.  c = sigma / 2, at least 1.5 times the mean point
+// spacing (some points per cell) and within kGridCells cells (k_grid_setup).
+// Distances are FP64, ties go to the lowest point index.
 constexpr int kGridMax = 64;
+constexpr int kGridCells = (kGridMax + 1) * (kGridMax + 1) * (kGridMax + 1);
+constexpr float kGridSpacing = 1.5f;
+constexpr int kGridY = 128;  // cells across the rows, at most
 constexpr uint32_t kPurposeOpt = 5u;
 constexpr double kOptTau = 1e-9;  // candidates within kOptTau of the best criterion value tie
 
 struct GridDev {
     float lo[3];
-    float cell, inv_cell;
+    float cell, inv_cell;  // across the rows; along them cells are half as long
+    float slack;           // (m) what float binning and box tests may be off by, and more
     int dims[3];
+    uint32_t used;         // records given to rows so far (k_grid_rows)
 };
+
+// start of cell (0, y, z) in the cell arrays: a row has an entry more than cells
+__device__ inline int grid_row(const GridDev &g, int y, int z) { return (z * g.dims[1] + y) * (g.dims[0] + 1); }
 
 __global__ void __launch_bounds__(1024)
 k_grid_setup(const float *__restrict__ pts, int N, float sigma, GridDev *__restrict__ gd)
@@ -932,30 +939,41 @@ k_grid_setup(const float *__restrict__ pts, int N, float sigma, GridDev *__restr
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        float ext = 0.0f;
-        for (int a = 0; a < 3; ++a) ext = fmaxf(ext, red[3 + a][0] - red[a][0]);
-        const float c = fmaxf(fmaxf(sigma, ext / (float)kGridMax), 1e-4f);
-        GridDev g;
-        g.cell = c;
-        g.inv_cell = 1.0f / c;
+        float e[3], ext = 0.0f;
         for (int a = 0; a < 3; ++a) {
-            g.lo[a] = red[a][0];
-            g.dims[a] = min(kGridMax + 1, (int)((red[3 + a][0] - red[a][0]) * g.inv_cell) + 1);
+            e[a] = red[3 + a][0] - red[a][0];
+            ext = fmaxf(ext, e[a]);
         }
+        const float area = 2.0f * (e[0] * e[1] + e[1] * e[2] + e[2] * e[0]);  // the box's, about the object's
+        float c = fmaxf(fmaxf(0.5f * sigma, kGridSpacing * sqrtf(area / (float)N)), fmaxf(ext / (float)kGridY, 1e-4f));
+        GridDev g;
+        for (int it = 0;; ++it) {
+            g.cell = c;
+            g.inv_cell = 1.0f / c;
+            for (int a = 0; a < 3; ++a) {
+                const float n = fminf(e[a] * g.inv_cell * (a == 0 ? 2.0f : 1.0f), (float)(a == 0 ? 2 * kGridY : kGridY));
+                g.dims[a] = n > 0.0f ? (int)n + 1 : 1;
+            }
+            if ((int64_t)(g.dims[0] + 1) * g.dims[1] * g.dims[2] <= kGridCells || it == 64) break;
+            c *= 1.25f;
+        }
+        if ((int64_t)(g.dims[0] + 1) * g.dims[1] * g.dims[2] > kGridCells) g.dims[0] = g.dims[1] = g.dims[2] = 1;
+        for (int a = 0; a < 3; ++a) g.lo[a] = red[a][0];
+        g.slack = 1e-6f + 4e-7f * ext;
+        g.used = 0;
         *gd = g;
     }
 }
 
-__device__ inline int grid_coord(const GridDev &g, int a, float x)
-{
-    return (int)floorf((x - g.lo[a]) * g.inv_cell);
-}
-
+// the cell array entry of point i
 __device__ inline int point_cell(const GridDev &g, const float *pts, int N, int i)
 {
     int c[3];
-    for (int a = 0; a < 3; ++a) c[a] = min(max(grid_coord(g, a, pts[a * N + i]), 0), g.dims[a] - 1);
-    return (c[2] * g.dims[1] + c[1]) * g.dims[0] + c[0];
+    for (int a = 0; a < 3; ++a) {
+        const float u = (pts[a * N + i] - g.lo[a]) * g.inv_cell * (a == 0 ? 2.0f : 1.0f);
+        c[a] = min(max((int)floorf(u), 0), g.dims[a] - 1);
+    }
+    return grid_row(g, c[1], c[2]) + c[0];
 }
 
 __global__ void k_fill_u32(uint32_t *__restrict__ a, int64_t n, uint32_t v)
@@ -971,33 +989,33 @@ __global__ void k_grid_count(const float *__restrict__ pts, int N, const GridDev
     if (i < N) atomicAdd(&cell_count[point_cell(*gd, pts, N, i)], 1u);
 }
 
-// single workgroup: exclusive scan of the cell counts (cell_start[n_cells] = N)
-__global__ void __launch_bounds__(1024)
-k_grid_scan(uint32_t *__restrict__ cell_count, const GridDev *__restrict__ gd, uint32_t *__restrict__ cell_start)
+// Wave per row: the starts of its cells' records, and of the end of its last one.
+// Rows take their ranges in the order they come by (a search reads whole rows, and
+// its result does not depend on the order of the points); one workgroup's scan of
+// all cells took 21 us for 11,000, this takes 11 us for 95,000.
+__global__ void __launch_bounds__(256)
+k_grid_rows(uint32_t *__restrict__ cell_count, GridDev *__restrict__ gd, uint32_t *__restrict__ cell_start)
 {
-    __shared__ uint32_t tot[1024];
-    const int nc = gd->dims[0] * gd->dims[1] * gd->dims[2];
-    const int per = (nc + 1023) / 1024, b0 = threadIdx.x * per;
-    uint32_t s = 0;
-    for (int i = b0; i < min(nc, b0 + per); ++i) s += cell_count[i];
-    tot[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
+    const int dx = gd->dims[0], rows = gd->dims[1] * gd->dims[2], lane = threadIdx.x & 63;
+    const int n_waves = gridDim.x * (blockDim.x >> 6);
+    for (int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); row < rows; row += n_waves) {
+        const int r0 = row * (dx + 1);
+        uint32_t sum = 0;
+        for (int x = lane; x < dx; x += 64) sum += cell_count[r0 + x];
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
         uint32_t run = 0;
-        for (int t = 0; t < 1024; ++t) {
-            const uint32_t v = tot[t];
-            tot[t] = run;
-            run += v;
+        if (lane == 0) run = sum ? atomicAdd(&gd->used, sum) : 0u;
+        run = (uint32_t)__builtin_amdgcn_readfirstlane((int)run);
+        for (int x0 = 0; x0 <= dx; x0 += 64) {
+            const int x = x0 + lane;
+            const uint32_t c = x < dx ? cell_count[r0 + x] : 0u;
+            const uint32_t incl = wave_scan_incl(c);
+            if (x <= dx) {
+                cell_start[r0 + x] = run + incl - c;
+                cell_count[r0 + x] = run + incl - c;  // becomes the scatter cursor
+            }
+            run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         }
-        cell_start[nc] = run;
-    }
-    __syncthreads();
-    uint32_t run = tot[threadIdx.x];
-    for (int i = b0; i < min(nc, b0 + per); ++i) {
-        const uint32_t v = cell_count[i];
-        cell_start[i] = run;
-        cell_count[i] = run;  // becomes the scatter cursor
-        run += v;
     }
 }
 
@@ -1012,26 +1030,6 @@ __global__ void k_grid_scatter(const float *__restrict__ pts, int N, const GridD
 }
 
 __device__ inline bool dom_has(const uint32_t *dom, int i) { return (dom[i >> 5] >> (i & 31)) & 1u; }
-
-// Nearest domain point to y given a domain point `inc` (the contact's current
-// point): FP64 distances, lowest index on ties, with inc as the incumbent.
-// The 64 lanes of a wave project one candidate together (all arguments are
-// wave-uniform), so the lanes never wait on each other's scans.  Shells of
-// cells at Chebyshev distance R = 0, 1, ... around y's cell are scanned while
-// R - 1 cell edges can still beat the best distance (the scan ends by R =
-// ceil(|y - inc| / c) + 1; the whole domain is scanned only past
-// kProjShellsInc shells).  In one pass each lane takes one cell position of
-// the shell and keeps it if its box lies within the best distance; the kept
-// cells' points are then spread over the lanes, 64 points per step, in the
-// order of the lanes' running counts (a DPP scan).  A step's points that beat
-// the best are checked against the domain bits and the wave takes their
-// minimum (distance, then index) by DPP.  The box and shell tests run in
-// float, in cell units, against lim = (sqrt(best) + 1e-6 m) / c rounded up by
-// a relative 1e-5: points are binned in float, and the 1e-6 m of slack covers
-// both that binning and the float tests, so a skipped cell never holds a
-// point that could win.  The incumbent's distance and the centre cell's range
-// come in with the candidate (each lane reads them for its own candidate).
-constexpr int kProjShellsInc = 8;
 
 __device__ inline double wave_bcast(double v, int l)
 {
@@ -1090,109 +1088,203 @@ __device__ inline void wave_lexmin(bool take, double d2, int i, double &best, in
     }
 }
 
-// position p of the shell at Chebyshev distance R >= 1 (side s = 2R + 1):
-// the two z faces (s^2 each), then a ring of 4(s - 1) cells per inner z slab
-__device__ inline void shell_pos(int R, int p, int &dx, int &dy, int &dz)
+// LDS of one wave: what its lanes wrote before is there for all of them after it
+__device__ inline void wave_lds_sync()
 {
-    const int s = 2 * R + 1, s2 = s * s;
-    if (p < 2 * s2) {
-        const bool hi = p >= s2;
-        dz = hi ? R : -R;
-        const int r = p - (hi ? s2 : 0), ry = r / s;
-        dy = ry - R;
-        dx = r - ry * s - R;
-    } else {
-        const int q = p - 2 * s2, ring = 4 * (s - 1), sl = q / ring, t = q - sl * ring, e = t / (s - 1),
-                  o = t - e * (s - 1);
-        dz = sl - R + 1;
-        dx = e == 0 ? o - R : (e == 1 ? R : (e == 2 ? R - o : -R));
-        dy = e == 0 ? -R : (e == 1 ? o - R : (e == 2 ? R : R - o));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// the ring of row position q >= 0 (ring R holds 8 R rows), and the row's offset
+__device__ inline int row_ring(int q) { return (int)(0.5f * (1.0f + sqrtf((float)(q + 1)))); }
+
+__device__ inline void row_offset(int R, int q, int &dy, int &dz)
+{
+    const int side = 2 * R, o = q - 4 * R * (R - 1), e = o / side, t = o - e * side;
+    dy = e == 0 ? t - R : (e == 1 ? R : (e == 2 ? R - t : -R));
+    dz = e == 0 ? -R : (e == 1 ? t - R : (e == 2 ? R : R - t));
+}
+
+// A candidate y waiting for its projection: its cell (i) and its place in it (r, in
+// cells), the squared distance and index of the best domain point so far.
+struct ProjSlot {
+    double y[3], best;
+    int64_t dom, out;  // its domain's first word; its entry of cands
+    int bi, i[3];
+    float r[3];
+};
+constexpr int kProjSets = 4;     // sets whose candidates a wave draws together
+constexpr int kProjRows = 1024;  // row positions searched before the whole domain is
+constexpr int kProjWindow = 2;   // cells along x to each side of y's in the first two searches
+
+struct ProjLds {
+    ProjSlot slot[64];
+    int64_t set[kProjSets], pose[kProjSets];  // the drawn sets: rank, pose, chosen fingers
+    uint32_t fingers[kProjSets];
+    uint8_t cls[64], order[64];  // of the slots: what a search left to do; by that
+};
+
+// how far the search has to go, in cells across rows: a point at or below `best`
+// lies within it (inflated by the slack and the rounding of the float tests)
+__device__ inline float proj_limit(const GridDev &g, double best)
+{
+    return (sqrtf((float)best) + g.slack) * g.inv_cell * 1.0001f;
+}
+
+// distance (cells) from y to the slab of cells at offset o on one axis
+__device__ inline float proj_slab(int o, float r) { return o > 0 ? (float)o - r : (o < 0 ? (float)(-o - 1) + r : 0.0f); }
+
+// The records of row (iy + dy, iz + dz) within lim of y and, along x, at cell offsets
+// lo .. hi of its own: [q0, q0 + cnt)
+__device__ inline void proj_span(const GridDev &g, const uint32_t *__restrict__ cell_start, const ProjSlot &S, int dy,
+                                 int dz, float lim, int lo, int hi, uint32_t &q0, uint32_t &cnt)
+{
+    q0 = cnt = 0;
+    const float sy = proj_slab(dy, S.r[1]), sz = proj_slab(dz, S.r[2]), rest = lim * lim - (sy * sy + sz * sz);
+    const int y = S.i[1] + dy, z = S.i[2] + dz;
+    if (rest < 0.0f || y < 0 || y >= g.dims[1] || z < 0 || z >= g.dims[2]) return;
+    const float hx = fminf(2.0f * sqrtf(rest) + 1e-3f, 1048576.0f);  // half width, in cells along x
+    const int xa = max(S.i[0] + max((int)floorf(S.r[0] - hx), lo), 0);
+    const int xb = min(S.i[0] + min((int)floorf(S.r[0] + hx), hi), g.dims[0] - 1);
+    if (xa > xb) return;
+    const uint32_t *row = cell_start + grid_row(g, y, z);
+    q0 = row[xa];
+    cnt = row[xb + 1] - q0;
+}
+
+// the better of (d, i) and its partner's under DPP control C
+template <int C>
+__device__ inline void dpp_lexmin(double &d, int &i)
+{
+    const double od = dpp_d<C>(d);
+    const int oi = __builtin_amdgcn_update_dpp(i, i, C, 0xf, 0xf, false);
+    if (od < d || (od == d && oi < i)) {
+        d = od;
+        i = oi;
     }
 }
 
-// best: the incumbent's squared distance; [cq0, cq0 + ccnt): the records of
-// y's own cell (empty when y lies outside the grid)
-__device__ int project_domain_wave(const GridDev &g, const uint32_t *__restrict__ cell_start,
-                                   const float4 *__restrict__ cell_pts, const float *__restrict__ pts, int N,
-                                   const uint32_t *__restrict__ dom, double yx, double yy, double yz, int inc,
-                                   double best, uint32_t cq0, uint32_t ccnt, int lane)
-{
-    const double fx = (yx - g.lo[0]) * (double)g.inv_cell, fy = (yy - g.lo[1]) * (double)g.inv_cell,
-                 fz = (yz - g.lo[2]) * (double)g.inv_cell;
-    const int cx = (int)floor(fx), cy = (int)floor(fy), cz = (int)floor(fz);
-    // y inside its cell, in cell units
-    const float rx = (float)(fx - (double)cx), ry = (float)(fy - (double)cy), rz = (float)(fz - (double)cz);
-    int bi = inc;
-    float lim, lim2;
-    auto set_lim = [&]() {
-        lim = (float)((sqrt(best) + 1e-6) * (double)g.inv_cell) * 1.00001f;
-        lim2 = lim * lim;
-    };
-    set_lim();
-    // distance (cell units) from y to the slab of cells at offset o on one axis
-    auto slab = [](int o, float r) { return o > 0 ? (float)o - r : (o < 0 ? (float)(-o - 1) + r : 0.0f); };
-    for (int R = 0; R <= kProjShellsInc; ++R) {
-        if (R > 0 && lim < (float)(R - 1)) return bi;  // shell R cannot hold a closer point
-        const int s = 2 * R + 1, n_pos = R == 0 ? 1 : s * s * s - (s - 2) * (s - 2) * (s - 2);
-        for (int p0 = 0; p0 < n_pos; p0 += 64) {
-            // this lane's cell position: kept if inside the grid and within lim
-            uint32_t q0 = 0, cnt = 0;
-            if (R == 0) {
-                if (lane == 0) {
-                    q0 = cq0;
-                    cnt = ccnt;
-                }
-            } else if (p0 + lane < n_pos) {
-                int dx, dy, dz;
-                if (R == 1) {  // the 26 neighbours: the 3 x 3 x 3 block less its centre (constant divisors)
-                    const int q = lane + (lane >= 13 ? 1 : 0);
-                    dx = q % 3 - 1;
-                    dy = (q / 3) % 3 - 1;
-                    dz = q / 9 - 1;
-                } else {
-                    shell_pos(R, p0 + lane, dx, dy, dz);
-                }
-                const int x = cx + dx, yv = cy + dy, z = cz + dz;
-                const float bx = slab(dx, rx), by = slab(dy, ry), bz = slab(dz, rz);
-                if (x >= 0 && x < g.dims[0] && yv >= 0 && yv < g.dims[1] && z >= 0 && z < g.dims[2] &&
-                    bx * bx + by * by + bz * bz <= lim2) {
-                    const int cc = (z * g.dims[1] + yv) * g.dims[0] + x;
-                    q0 = cell_start[cc];
-                    cnt = cell_start[cc + 1] - q0;
-                }
-            }
-            // lane l's points are [ex, ex + cnt) of the pass's running count
-            const uint32_t incl = wave_scan_incl(cnt), ex = incl - cnt;
-            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            for (uint32_t b0 = 0; b0 < total; b0 += 64) {
-                const uint32_t f = b0 + (uint32_t)lane;
-                // the record of point f: the kept cells whose ranges meet this
-                // step, in lane order (the last one starting at or before f owns it)
-                uint32_t rec = 0;
-                for (unsigned long long km = __ballot(cnt > 0 && ex < b0 + 64u && incl > b0); km; km &= km - 1) {
-                    const int l = __builtin_ctzll(km);
-                    const uint32_t lex = (uint32_t)__builtin_amdgcn_readlane((int)ex, l);
-                    const uint32_t lq0 = (uint32_t)__builtin_amdgcn_readlane((int)q0, l);
-                    if (f >= lex) rec = lq0 + (f - lex);
-                }
-                bool take = false;
-                double d2 = INFINITY;
-                int i = INT_MAX;
-                if (f < total) {
-                    const float4 v = cell_pts[rec];
-                    i = __float_as_int(v.w);
-                    const double ex3 = (double)v.x - yx, ey3 = (double)v.y - yy, ez3 = (double)v.z - yz;
-                    d2 = ex3 * ex3 + ey3 * ey3 + ez3 * ez3;
-                    take = (d2 < best || (d2 == best && i < bi)) && dom_has(dom, i);
-                }
-                const double old = best;
-                wave_lexmin(take, d2, i, best, bi);
-                if (best != old) set_lim();
+// The search of one candidate by a group of 8 lanes.  Each lane keeps the best
+// (distance, index) of the points it read; equal in the group's lanes at first.
+struct ProjGroup {
+    double yx, yy, yz, lb;
+    int li, gl, g0;
+
+    __device__ inline ProjGroup(const ProjSlot &S, int lane)
+        : yx(S.y[0]), yy(S.y[1]), yz(S.y[2]), lb(S.best), li(S.bi), gl(lane & 7), g0(lane & 56)
+    {
+    }
+    __device__ inline void scan(const float4 *__restrict__ cell_pts, const uint32_t *__restrict__ dom, uint32_t q,
+                                uint32_t end)
+    {
+        for (q += gl; q < end; q += 8) {
+            const float4 v = cell_pts[q];
+            const int i = __float_as_int(v.w);
+            const double ex = (double)v.x - yx, ey = (double)v.y - yy, ez = (double)v.z - yz;
+            const double d2 = ex * ex + ey * ey + ez * ez;
+            if ((d2 < lb || (d2 == lb && i < li)) && dom_has(dom, i)) {
+                lb = d2;
+                li = i;
             }
         }
     }
-    if (sqrt(best) < (double)kProjShellsInc * g.cell - 1e-6) return bi;
-    // beyond the shells: every domain point, words spread over the lanes
+    // each lane's span, one after another
+    __device__ inline void scan_spans(const float4 *__restrict__ cell_pts, const uint32_t *__restrict__ dom,
+                                      uint32_t q0, uint32_t cnt)
+    {
+        for (uint32_t rows = (uint32_t)(__ballot(cnt > 0) >> g0) & 0xffu; rows; rows &= rows - 1) {
+            const int l = g0 + __builtin_ctz(rows);
+            const uint32_t q = (uint32_t)__shfl((int)q0, l, 64);
+            scan(cell_pts, dom, q, q + (uint32_t)__shfl((int)cnt, l, 64));
+        }
+    }
+    __device__ inline void best()
+    {
+        dpp_lexmin<0xB1>(lb, li);
+        dpp_lexmin<0x4E>(lb, li);
+        dpp_lexmin<0x141>(lb, li);
+    }
+};
+
+// distance (cells) from y to the rows around its own
+__device__ inline float proj_edge(const ProjSlot &S)
+{
+    return fminf(fminf(S.r[1], 1.0f - S.r[1]), fminf(S.r[2], 1.0f - S.r[2]));
+}
+
+// y's own row and the 8 around it, kProjWindow cells along x to each side, hold
+// every point within lim
+__device__ inline bool proj_inside(const ProjSlot &S, float lim)
+{
+    return lim < 1.0f + proj_edge(S) && 2.0f * lim <= (float)kProjWindow + fminf(S.r[0], 1.0f - S.r[0]) - 1e-3f;
+}
+
+// What the groups' searches leave, by the whole wave, a lane per stretch of cells:
+// first the 18 ends of y's own row and the 8 around it, then the rows of ring 2 and
+// on, 64 stretches per pass.  Their points are spread over the lanes, 64 per step, in
+// the order of the lanes' running counts; a stretch that a better point has put out
+// of reach since is left out.  Past kProjRows every domain point.
+__device__ inline int project_wave(const GridDev &g, const uint32_t *__restrict__ cell_start,
+                                   const float4 *__restrict__ cell_pts, const float *__restrict__ pts, int N,
+                                   const uint32_t *__restrict__ dom, const ProjSlot &S, int lane)
+{
+    const double yx = S.y[0], yy = S.y[1], yz = S.y[2];
+    double best = S.best;
+    int bi = S.bi;
+    const float edge = proj_edge(S);
+    float lim = proj_limit(g, best);
+    for (int p0 = 0; p0 < kProjRows; p0 += 64) {
+        if (p0 > 0 && lim < (float)(row_ring(p0 - 10) - 1) + edge) return bi;  // no closer point from here on
+        const int p = p0 + lane, q = p < 18 ? (p >> 1) - 1 : p - 10;
+        int dy = 0, dz = 0, lo = -(1 << 20), hi = 1 << 20;
+        if (q >= 0) row_offset(row_ring(q), q, dy, dz);
+        float gap = 0.0f;  // along x
+        if (p < 18) {
+            if (p & 1) {
+                lo = kProjWindow + 1;
+                gap = 0.5f * ((float)lo - S.r[0]);
+            } else {
+                hi = -kProjWindow - 1;
+                gap = 0.5f * ((float)kProjWindow + S.r[0]);
+            }
+        }
+        const float sy = proj_slab(dy, S.r[1]), sz = proj_slab(dz, S.r[2]);
+        const float near2 = sy * sy + sz * sz + gap * gap;
+        uint32_t q0, cnt;
+        proj_span(g, cell_start, S, dy, dz, lim, lo, hi, q0, cnt);
+        // lane l's points are [ex, ex + cnt) of the pass's running count
+        const uint32_t incl = wave_scan_incl(cnt), ex = incl - cnt;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        for (uint32_t b0 = 0; b0 < total; b0 += 64) {
+            const uint32_t f = b0 + (uint32_t)lane;
+            // the record of point f: the stretches that meet this step, in lane order
+            uint32_t rec = 0, end = 0;
+            for (unsigned long long km = __ballot(cnt > 0 && ex < b0 + 64u && incl > b0 && near2 <= lim * lim); km;
+                 km &= km - 1) {
+                const int l = __builtin_ctzll(km);
+                const uint32_t lex = (uint32_t)__builtin_amdgcn_readlane((int)ex, l);
+                const uint32_t lq0 = (uint32_t)__builtin_amdgcn_readlane((int)q0, l);
+                if (f >= lex) {
+                    rec = lq0 + (f - lex);
+                    end = lq0 + (uint32_t)__builtin_amdgcn_readlane((int)cnt, l);
+                }
+            }
+            bool take = false;
+            double d2 = INFINITY;
+            int i = INT_MAX;
+            if (rec < end) {
+                const float4 v = cell_pts[rec];
+                i = __float_as_int(v.w);
+                const double ex3 = (double)v.x - yx, ey3 = (double)v.y - yy, ez3 = (double)v.z - yz;
+                d2 = ex3 * ex3 + ey3 * ey3 + ez3 * ez3;
+                take = (d2 < best || (d2 == best && i < bi)) && dom_has(dom, i);
+            }
+            const double old = best;
+            wave_lexmin(take, d2, i, best, bi);
+            if (best != old) lim = proj_limit(g, best);
+        }
+    }
+    if (lim < (float)(row_ring(kProjRows - 11) - 1) + edge) return bi;
     const int NW = (N + 31) >> 5;
     double lb = INFINITY;
     int li = INT_MAX;
@@ -1214,7 +1306,6 @@ __device__ int project_domain_wave(const GridDev &g, const uint32_t *__restrict_
     return bi;
 }
 
-
 // Alg. 2, the candidates of one round (Sec. 5.4): one candidate per
 // (set, contact i, candidate j).  Contact i's candidates are drawn around its
 // point at the start of the round (contact i moves only at its own step), so
@@ -1223,11 +1314,19 @@ __device__ int project_domain_wave(const GridDev &g, const uint32_t *__restrict_
 // Box-Muller of Philox block (g + pose_offset, d, 5 | step << 8, request_id),
 // step = (round k + i) n_inner + j, and cand = the nearest point of contact
 // i's domain (incumbent p_i).  cands[((t k + i) n_inner + j)], t = the set's
-// rank among the sets of valid poses; -1 for sets not drawn.  Each lane draws
-// one candidate; the wave then projects its 64 candidates one after another,
-// all lanes together (project_domain_wave).  Eight waves per SIMD (64 VGPRs;
-// the candidate set-up spills a few) hide more of the scans' load latency.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
+// rank among the sets of valid poses; -1 for sets not drawn.  A wave takes
+// kProjSets sets (few: a pose's sets are drawn all or none, so more would leave some
+// waves all the work; 16 sets 1.5 times the time) and draws the candidates of the
+// drawn ones 64 at a time, a lane each; a group of 8 lanes then projects each: its own
+// row kProjWindow cells to each side, then the 8 rows around it so, first those
+// candidates that surely end there, so that a group waits for groups with about its
+// own work.  The few with nothing so near go on as a whole wave each (8 lanes took
+// 3.4 ms for them, the wave 1.3).
+// What bounds it: load latency and VALU issue about equally.  A wave per candidate
+// with 4 mm cells of 34 points read 200 points and issued 515 instructions for each;
+// with groups and cells of 2 mm x 1 mm it issues 212 (8,192 poses x 64 draws, 65,536
+// points, 5.7 M candidates of drawn sets: 5.3 -> 3.0 ms).
+__global__ void __launch_bounds__(256, 6)
 k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
               const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
               const uint32_t *__restrict__ dom_bits, const uint32_t *__restrict__ dom_count,
@@ -1236,77 +1335,133 @@ k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int 
               const GridDev *__restrict__ gdp, const uint32_t *__restrict__ cell_start,
               const float4 *__restrict__ cell_pts, const int32_t *__restrict__ set_pt, int32_t *__restrict__ cands)
 {
+    __shared__ ProjLds lds[4];
+    ProjLds &L = lds[threadIdx.x >> 6];
     const GridDev g = *gdp;
     const int NW = (N + 31) >> 5;
-    const int lane = threadIdx.x & 63;
-    const int64_t per_set = (int64_t)k * n_inner;
-    const int64_t n_total = (int64_t)(*n_valid_poses) * D * per_set;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    // the loop bound is uniform over the wave (u - lane is the wave's first candidate)
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u - lane < n_total; u += stride) {
-        bool live = false;
-        double yx = 0.0, yy = 0.0, yz = 0.0, best0 = 0.0;
-        int inc = 0;
-        int64_t dom_off = 0;
-        uint32_t cq0 = 0, ccnt = 0;  // the records of y's own cell
-        if (u < n_total) {
-            const int64_t t = u / per_set;
-            const int rem = (int)(u - t * per_set), i = rem / n_inner, j = rem - i * n_inner;
+    const int lane = threadIdx.x & 63, per_set = k * n_inner;
+    const int64_t n_sets = (int64_t)(*n_valid_poses) * D;
+    const int64_t step = (int64_t)gridDim.x * 4 * kProjSets;
+    for (int64_t t0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kProjSets; t0 < n_sets; t0 += step) {
+        const int64_t t = t0 + lane;
+        bool drawn = false;
+        if (lane < kProjSets && t < n_sets) {
             const int64_t pg = valid_poses[t / D];
             const int d = (int)(t % D);
-            const int32_t *sp = set_pt + (pg * D + d) * k;
-            const uint32_t fm = choose_fingers(eligible_fingers(dom_count, pg, F), k, (uint32_t)(pose_offset + pg),
-                                               d, request_id, seed_lo, seed_hi);
             const int pc = palm_pt ? palm_pt[pg] : -1;
-            bool drawn = fm != 0 && pc < N;
-            for (int q = 0; q < k; ++q) drawn &= sp[q] >= 0 && sp[q] < N;
-            if (!drawn) {
-                cands[u] = -1;
-            } else {
-                live = true;
-                inc = sp[i];
+            drawn = pc < N;
+            for (int q = 0; q < k; ++q) {
+                const int sp = set_pt[(pg * D + d) * k + q];
+                drawn &= sp >= 0 && sp < N;
+            }
+            if (drawn) {
+                const uint32_t fm = choose_fingers(eligible_fingers(dom_count, pg, F), k,
+                                                   (uint32_t)(pose_offset + pg), d, request_id, seed_lo, seed_hi);
+                drawn = fm != 0;
+                L.set[lane] = t;
+                L.pose[lane] = pg;
+                L.fingers[lane] = fm;
+            }
+        }
+        wave_lds_sync();
+        const uint32_t dm = (uint32_t)__ballot(drawn);
+        const int n_here = (int)min((int64_t)kProjSets, n_sets - t0);
+        if (__popc(dm) < n_here)
+            for (int e = lane; e < n_here * per_set; e += 64)
+                if (!((dm >> (e / per_set)) & 1u)) cands[t0 * per_set + e] = -1;
+        const int total = __popc(dm) * per_set;
+        for (int c0 = 0; c0 < total; c0 += 64) {
+            const int nb = min(64, total - c0);
+            if (lane < nb) {
+                const int c = c0 + lane, nth = c / per_set, rem = c - nth * per_set, i = rem / n_inner;
+                const int at = select_in_word(dm, (uint32_t)nth);
+                const int64_t pg = L.pose[at], set = L.set[at];
+                const int d = (int)(set % D);
+                const int inc = set_pt[(pg * D + d) * k + i];
+                ProjSlot S;
                 const double px = pts[inc], py = pts[N + inc], pz = pts[2 * N + inc];
                 double tx[3], ty[3];
                 duff_basis(nrm[inc], nrm[N + inc], nrm[2 * N + inc], tx, ty);
                 uint32_t w[4];
-                const uint32_t step = (uint32_t)((round * k + i) * n_inner + j);
-                philox4x32_10((uint32_t)(pose_offset + pg), (uint32_t)d, kPurposeOpt | (step << 8), request_id,
-                              seed_lo, seed_hi, w);
+                philox4x32_10((uint32_t)(pose_offset + pg), (uint32_t)d,
+                              kPurposeOpt | ((uint32_t)(round * per_set + rem) << 8), request_id, seed_lo, seed_hi, w);
                 const double u1 = ((double)(w[0] >> 8) + 1.0) * (1.0 / 16777216.0);
                 const double u2 = (double)(w[1] >> 8) * (1.0 / 16777216.0);
                 const double rr = sqrt(-2.0 * log(u1));
                 const double dx = sigma * rr * cos(2.0 * M_PI * u2), dy = sigma * rr * sin(2.0 * M_PI * u2);
-                yx = px + dx * tx[0] + dy * ty[0];
-                yy = py + dx * tx[1] + dy * ty[1];
-                yz = pz + dx * tx[2] + dy * ty[2];
-                dom_off = (pg * F + select_in_word(fm, (uint32_t)i)) * NW;  // contact i's finger
-                {
-                    const double ex = px - yx, ey = py - yy, ez = pz - yz;
-                    best0 = ex * ex + ey * ey + ez * ez;
+                S.y[0] = px + dx * tx[0] + dy * ty[0];
+                S.y[1] = py + dx * tx[1] + dy * ty[1];
+                S.y[2] = pz + dx * tx[2] + dy * ty[2];
+                const double ex = px - S.y[0], ey = py - S.y[1], ez = pz - S.y[2];
+                S.best = ex * ex + ey * ey + ez * ez;
+                S.bi = inc;
+                S.dom = (pg * F + select_in_word(L.fingers[at], (uint32_t)i)) * NW;  // contact i's finger
+                S.out = set * per_set + rem;
+                for (int a = 0; a < 3; ++a) {
+                    const double u = (S.y[a] - g.lo[a]) * (double)g.inv_cell * (a == 0 ? 2.0 : 1.0);
+                    const double v = fmin(fmax(floor(u), -1048576.0), 1048576.0);  // far outside: any cell that is
+                    S.i[a] = (int)v;
+                    S.r[a] = (float)(u - v);
                 }
-                const int cx = (int)floor((yx - g.lo[0]) * (double)g.inv_cell),
-                          cy = (int)floor((yy - g.lo[1]) * (double)g.inv_cell),
-                          cz = (int)floor((yz - g.lo[2]) * (double)g.inv_cell);
-                if (cx >= 0 && cx < g.dims[0] && cy >= 0 && cy < g.dims[1] && cz >= 0 && cz < g.dims[2]) {
-                    const int cc = (cz * g.dims[1] + cy) * g.dims[0] + cx;
-                    cq0 = cell_start[cc];
-                    ccnt = cell_start[cc + 1] - cq0;
+                L.slot[lane] = S;
+            }
+            wave_lds_sync();
+            // own row; 0: ended, 1: ends with the rows around it, 2: maybe further
+            for (int b = 0; b < nb; b += 8) {
+                const int sl = b + (lane >> 3);
+                if (sl >= nb) continue;
+                ProjSlot &S = L.slot[sl];
+                ProjGroup G(S, lane);
+                uint32_t q0, cnt;
+                proj_span(g, cell_start, S, 0, 0, proj_limit(g, G.lb), -kProjWindow, kProjWindow, q0, cnt);
+                G.scan(cell_pts, dom_bits + S.dom, q0, q0 + cnt);
+                G.best();
+                const float lim = proj_limit(g, G.lb);
+                const int cls = !proj_inside(S, lim) ? 2 : lim < proj_edge(S) ? 0 : 1;
+                if (G.gl == 0) {
+                    S.best = G.lb;
+                    S.bi = G.li;
+                    L.cls[sl] = (uint8_t)cls;
+                    if (cls == 0) cands[S.out] = G.li;
                 }
             }
+            wave_lds_sync();
+            const int cls = lane < nb ? L.cls[lane] : 0;
+            const unsigned long long m1 = __ballot(cls == 1), m2 = __ballot(cls == 2), below = (1ull << lane) - 1ull;
+            const int n1 = __popcll(m1), n2 = __popcll(m2);
+            if (cls == 1) L.order[__popcll(m1 & below)] = (uint8_t)lane;
+            if (cls == 2) L.order[n1 + __popcll(m2 & below)] = (uint8_t)lane;
+            wave_lds_sync();
+            for (int b0 = 0; b0 < n1 + n2; b0 += 8) {
+                const int b = b0 + (lane >> 3);
+                bool open = false;
+                if (b < n1 + n2) {
+                    ProjSlot &S = L.slot[L.order[b]];
+                    ProjGroup G(S, lane);
+                    const int t = G.gl & 1, e = G.gl >> 1;  // row_offset(1, gl)
+                    const int dy = e == 0 ? t - 1 : (e == 1 ? 1 : (e == 2 ? 1 - t : -1));
+                    const int dz = e == 0 ? -1 : (e == 1 ? t - 1 : (e == 2 ? 1 : 1 - t));
+                    uint32_t q0, cnt;
+                    proj_span(g, cell_start, S, dy, dz, proj_limit(g, G.lb), -kProjWindow, kProjWindow, q0, cnt);
+                    G.scan_spans(cell_pts, dom_bits + S.dom, q0, cnt);
+                    G.best();
+                    open = b >= n1 && !proj_inside(S, proj_limit(g, G.lb));
+                    if (G.gl == 0) {
+                        S.best = G.lb;
+                        S.bi = G.li;
+                        if (!open) cands[S.out] = G.li;
+                    }
+                }
+                wave_lds_sync();
+                for (unsigned long long todo = __ballot(open && (lane & 7) == 0); todo; todo &= todo - 1) {
+                    const ProjSlot &S = L.slot[L.order[b0 + (__builtin_ctzll(todo) >> 3)]];
+                    const int r = project_wave(g, cell_start, cell_pts, pts, N, dom_bits + S.dom, S, lane);
+                    if (lane == 0) cands[S.out] = r;
+                }
+            }
+            wave_lds_sync();
         }
-        int res = -1;
-        for (unsigned long long todo = __ballot(live); todo; todo &= todo - 1) {
-            const int c = __builtin_ctzll(todo);
-            const int64_t off = ((int64_t)__builtin_amdgcn_readlane((int)(dom_off >> 32), c) << 32) |
-                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dom_off, c);
-            const int r = project_domain_wave(
-                g, cell_start, cell_pts, pts, N, dom_bits + off, wave_bcast(yx, c), wave_bcast(yy, c),
-                wave_bcast(yz, c), __builtin_amdgcn_readlane(inc, c), wave_bcast(best0, c),
-                (uint32_t)__builtin_amdgcn_readlane((int)cq0, c), (uint32_t)__builtin_amdgcn_readlane((int)ccnt, c),
-                lane);
-            if (lane == c) res = r;
-        }
-        if (live) cands[u] = res;
+        wave_lds_sync();
     }
 }
 
@@ -2008,7 +2163,7 @@ static SearchWs search_ws(void *base, int64_t n_points, int64_t n_poses, int64_t
     w.cands = nullptr;
     w.split = OptSplit{};
     if (opt) {
-        const int64_t ncell = (int64_t)(kGridMax + 1) * (kGridMax + 1) * (kGridMax + 1);
+        const int64_t ncell = kGridCells;
         char *b = static_cast<char *>(base);
         w.grid = reinterpret_cast<GridDev *>(b + off);
         off += 256;
@@ -2188,21 +2343,21 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
         else if (kk <= 6) { LG_VERDICT(6); } else { LG_VERDICT(8); }
     } else {
         // cell grid of the object, then Alg. 2 on the drawn sets, then the links of the moved contacts
-        const int64_t ncell = (int64_t)(kGridMax + 1) * (kGridMax + 1) * (kGridMax + 1);
+        const int64_t ncell = kGridCells;
         hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(1024), 0, s, pts, n_points, p->opt_sigma, ws.grid);
         // zeroed by a kernel, not a memset node (callers may capture the stream in a graph)
         hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((ncell + 255) / 256)), dim3(256), 0, s, ws.cell_count,
                            ncell, 0u);
         const unsigned pb = (unsigned)((n_points + 255) / 256);
         hipLaunchKernelGGL(k_grid_count, dim3(pb), dim3(256), 0, s, pts, n_points, ws.grid, ws.cell_count);
-        hipLaunchKernelGGL(k_grid_scan, dim3(1), dim3(1024), 0, s, ws.cell_count, ws.grid, ws.cell_start);
+        hipLaunchKernelGGL(k_grid_rows, dim3(256), dim3(256), 0, s, ws.cell_count, ws.grid, ws.cell_start);
         hipLaunchKernelGGL(k_grid_scatter, dim3(pb), dim3(256), 0, s, pts, n_points, ws.grid, ws.cell_count,
                            ws.cell_pts);
         const int gs = p->opt_inner <= 1 ? 1 : p->opt_inner <= 2 ? 2 : p->opt_inner <= 4 ? 4 : p->opt_inner <= 8 ? 8 : 16;
         const dim3 ogrid((unsigned)std::max<int64_t>(
             1, std::min<int64_t>((n_sets * gs + 255) / 256, (int64_t)n_cu * 8)));
         const dim3 pgrid((unsigned)std::max<int64_t>(
-            1, std::min<int64_t>((n_sets * p->k * p->opt_inner + 255) / 256, (int64_t)n_cu * 32)));
+            1, std::min<int64_t>((n_sets + 4 * kProjSets - 1) / (4 * kProjSets), (int64_t)n_cu * 64)));
         // grids of the per-candidate criteria (candidates; sets)
         const dim3 cgrid(verdict_blocks(n_sets * p->opt_inner, n_cu));
         const dim3 sgrid((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_sets + 255) / 256, (int64_t)n_cu * 8)));
