@@ -104,12 +104,16 @@ __global__ void k_fill_i32(int32_t *__restrict__ p, int64_t n, int32_t v)
 //   +x: d ~ (1, -t, -s)   -x: d ~ (-1, -t, s)   +y: d ~ (s, 1, t)
 //   -y: d ~ (s, -1, -t)   +z: d ~ (s, -t, 1)    -z: d ~ (-s, -t, -1),
 // and to cell (is, it) of a kLutRes x kLutRes grid over (s, t).  A cell lists,
-// in increasing order, every bin whose dot product can come within kLutMargin
-// of the best one anywhere in the closed cell (checked on a dense sub-grid of
-// the cell; the margin exceeds the dot-product variation between sub-grid
-// points), so the argmax over the candidates equals the argmax over all bins,
-// also for a direction on a cell or face boundary.  Cells with more than four
-// candidates are marked for the full search (0xffffffff).
+// in increasing order, every bin that can be the best anywhere in the closed cell:
+// at some point of a dense sub-grid of the cell its dot product is within reach of the
+// best bin's a there, that is within |c_b - c_a| times the distance to the farthest
+// direction the point stands for (the dot products' difference changes by no more; a
+// cube's points are at least as far apart as their directions), plus a margin for
+// float products and a direction on a cell or face boundary.  So the argmax over the
+// candidates equals the argmax over all bins.  With the pair's own reach instead of
+// twice the sub-grid's step 5 % of the cells hold more than two bins (16 %).  Their
+// entries have the top bit set, cells with more than four candidates are marked for
+// the full search (0xffffffff).
 __device__ inline void cube_direction(int face, double s, double t, double *d)
 {
     switch (face) {
@@ -125,14 +129,14 @@ __device__ inline void cube_direction(int face, double s, double t, double *d)
 constexpr int kLutSub = 9;  // sub-grid points per cell edge, both edges included
 
 // One wave per cell, lanes over its sub-grid points; a lane marks the bins near
-// the best at its points, the marks are joined by shuffles: 42 us, 30 ms on one
+// the best at its points, the marks are joined by shuffles: 90 us, 30 ms on one
 // CPU thread.
 __global__ void __launch_bounds__(64) k_bin_lut(const float *__restrict__ bc, int B, uint32_t *__restrict__ lut)
 {
     const int R = kLutRes, cell = blockIdx.x, lane = threadIdx.x;
     const int is = cell % R, it = cell / R % R, face = cell / (R * R);
     const double sub_step = 2.0 / R / (kLutSub - 1);   // in face coordinates
-    const double margin = 2.0 * sub_step + 1e-4;        // angular spacing <= coordinate spacing
+    const double reach = 0.5 * sqrt(2.0) * sub_step;    // to the farthest direction of a sub-grid point
     unsigned long long cand = 0;
     for (int q = lane; q < kLutSub * kLutSub; q += 64) {
         const double sv = -1.0 + 2.0 * (is + (double)(q % kLutSub) / (kLutSub - 1)) / R;
@@ -141,18 +145,28 @@ __global__ void __launch_bounds__(64) k_bin_lut(const float *__restrict__ bc, in
         cube_direction(face, sv, tv, d);
         const double rn = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
         double best = -2.0;
-        for (int b = 0; b < B; ++b)
-            best = fmax(best, (bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) * rn);
-        for (int b = 0; b < B; ++b)
-            if ((bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) * rn >= best - margin) cand |= 1ull << b;
+        int a = 0;
+        for (int b = 0; b < B; ++b) {
+            const double v = (bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) * rn;
+            if (v > best) {
+                best = v;
+                a = b;
+            }
+        }
+        for (int b = 0; b < B; ++b) {
+            const double v = (bc[3 * b] * d[0] + bc[3 * b + 1] * d[1] + bc[3 * b + 2] * d[2]) * rn;
+            const double ex = (double)bc[3 * b] - bc[3 * a], ey = (double)bc[3 * b + 1] - bc[3 * a + 1],
+                         ez = (double)bc[3 * b + 2] - bc[3 * a + 2];
+            if (v >= best - reach * sqrt(ex * ex + ey * ey + ez * ez) - 1e-4) cand |= 1ull << b;
+        }
     }
     for (int off = 32; off > 0; off >>= 1) cand |= __shfl_xor(cand, off, 64);
     if (lane != 0) return;
     uint32_t e = 0xffffffffu;
     if (__popcll(cand) <= 4) {
-        // absent slots repeat the first candidate (the kernels evaluate all four)
+        // absent slots repeat the first candidate
         const int first = __ffsll((long long)cand) - 1;
-        e = 0;
+        e = __popcll(cand) > 2 ? 0x80000000u : 0u;
         for (int i = 0; i < 4; ++i) {
             const int b = cand ? __ffsll((long long)cand) - 1 : first;
             cand &= cand - 1;

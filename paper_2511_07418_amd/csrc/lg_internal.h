@@ -352,11 +352,11 @@ __device__ inline void query_dir(const float *pose, float nx, float ny, float nz
 }
 
 // argmax_b <d, c_b> (ties to the lowest b) through the
-// cube-map candidate table: the four candidate slots of the direction's cell
-// (absent ones repeat the first, so the result is unchanged) are evaluated
-// without a branch.  Their centres are float4 rows in LDS, all four read
-// before the first dot product.  A cell with more than four candidates scans
-// every bin.
+// cube-map candidate table: the first two candidate slots of the direction's cell
+// (an absent second repeats the first, so the result is unchanged) are evaluated
+// without a branch, the other two where an entry of the wave has them (its top bit;
+// 5 % of the cells: a third of the chunks of a smooth object skip them).  The centres
+// are float4 rows in LDS.  A cell with more than four candidates scans every bin.
 __device__ inline int nearest_bin_lut4(const uint32_t *lut, const float4 *c4, int B, float dx, float dy, float dz)
 {
     // face and face coordinates by the cube-map instructions (the table is
@@ -373,28 +373,24 @@ __device__ inline int nearest_bin_lut4(const uint32_t *lut, const float4 *c4, in
     const uint32_t e = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(lut) + boff);
     float best = -3.0e38f;
     int bi = 0;
-    if (e == 0xffffffffu) {  // more than four candidates: every bin
-        for (int b = 0; b < B; ++b) {
-            const float4 c = c4[b];
-            const float sc = fmaf(c.x, dx, fmaf(c.y, dy, c.z * dz));
-            if (sc > best) {
-                best = sc;
-                bi = b;
-            }
+    auto take = [&](uint32_t off) {  // off: bin * 16, the byte offset of its float4 centre
+        const float4 c = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(c4) + off);
+        const float s = fmaf(c.x, dx, fmaf(c.y, dy, c.z * dz));
+        if (s > best) {
+            best = s;
+            bi = (int)(off >> 4);
         }
-        return bi;
-    }
-    // byte offsets (bin * 16) of the four slots' float4 centres
-    const uint32_t off[4] = {(e << 4) & 0xff0u, (e >> 4) & 0xff0u, (e >> 12) & 0xff0u, (e >> 20) & 0xff0u};
-    float4 ck[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) ck[k] = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(c4) + off[k]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float sc = fmaf(ck[k].x, dx, fmaf(ck[k].y, dy, ck[k].z * dz));
-        if (sc > best) {
-            best = sc;
-            bi = (int)(off[k] >> 4);
+    };
+    take((e << 4) & 0x3f0u);
+    take((e >> 4) & 0x3f0u);
+    if ((int)e < 0) {  // more than two candidates
+        if (e != 0xffffffffu) {
+            take((e >> 12) & 0x3f0u);
+            take((e >> 20) & 0x3f0u);
+        } else {  // more than four: every bin
+            best = -3.0e38f;
+            bi = 0;
+            for (int b = 0; b < B; ++b) take((uint32_t)b << 4);
         }
     }
     return bi;
