@@ -22,11 +22,14 @@
 // window, or every occupied voxel of it, is skipped: its 64 domain bits are
 // zero without a lookup, and a chunk that no finger keeps is not loaded at all.
 //
-// What bounds it: VALU issue (65,536 poses x 65,536 points, 22 joints: 5.6 G wave
-// instructions in 8.9 ms; 8.0 G in 12.0 ms before the culling by voxels, the bin
-// index in float arithmetic, the in-brick word by three multiply-adds and the
-// scalar chunk bookkeeping).  About 110 instructions per kept chunk: 9 for the
-// direction, 45 for its bin, 30 for the cell and word, 9 per kept finger.
+// What bounds it: VALU issue, with the L1's line rate close behind (65,536 poses x
+// 65,536 points, 22 joints: 5.3 G wave instructions and 3.6 G line accesses, 94 % and
+// 70 % of what 8.6 ms allow; 7 waves per SIMD 2 % slower than 8).  8.0 G instructions
+// in 12.0 ms before the culling by voxels, the bin index in float arithmetic, the
+// in-brick word by three multiply-adds, the scalar chunk bookkeeping and two
+// candidate bins instead of four; the last 0.5 ms were registers kept in scratch
+// memory across the units.  About 105 instructions per kept chunk: 9 for the
+// direction, 40 for its bin, 30 for the cell and word, 9 per kept finger.
 #include <math.h>
 
 #include <algorithm>
@@ -213,7 +216,10 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
     for (int unit = wave; unit < nunit; unit += waves) {
         uint32_t acc[FM];
 #pragma unroll
-        for (int f = 0; f < FM; ++f) acc[f] = 0;
+        for (int f = 0; f < FM; ++f) {
+            acc[f] = 0;
+            asm volatile("" : "+v"(acc[f]));  // made here, not kept (in scratch memory) from before the loop
+        }
         const int u0 = unit * uc, c_end = min(nchunks, u0 + uc);
         for (int c0 = u0; c0 < c_end; c0 += 8) {
           uint32_t keep[FM];
@@ -283,9 +289,11 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
                 }
             }
             const int j2 = 2 * (chunk - u0);
+            uint32_t cb2 = cbit;  // tested again: FM lane masks kept from above take 2 FM scalar registers
+            asm volatile("" : "+s"(cb2));
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
-                if (!(keep[f] & cbit)) continue;  // the ballot would be 0
+                if (!(keep[f] & cb2)) continue;  // the ballot would be 0
                 const bool hit = (int)(word[f] << (~b & 31)) < 0;  // bit b % 32
                 const unsigned long long m = __ballot(hit);
                 // the chunk's two ballot halves into lanes j2, j2 + 1 (j2 is uniform)
@@ -295,10 +303,12 @@ __device__ __forceinline__ void query_pose(QueryLds<FM, LAT> &L, const DevHand &
           }
         }
         const int wi = u0 * 2 + lane;
+        int row = g;
+        asm volatile("" : "+s"(row));  // likewise the addresses
         if (lane < 2 * uc && wi < NW) {
 #pragma unroll
             for (int f = 0; f < FM; ++f)
-                if (f < F) dom_bits[((int64_t)g * F + f) * NW + wi] = acc[f];
+                if (f < F) dom_bits[((int64_t)row * F + f) * NW + wi] = acc[f];
         }
         // counts per lane from the block's words (bits past N are 0)
 #pragma unroll
