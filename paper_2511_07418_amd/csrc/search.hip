@@ -1158,10 +1158,9 @@ __device__ inline void dpp_lexmin(double &d, int &i)
 {
     const double od = dpp_d<C>(d);
     const int oi = __builtin_amdgcn_update_dpp(i, i, C, 0xf, 0xf, false);
-    if (od < d || (od == d && oi < i)) {
-        d = od;
-        i = oi;
-    }
+    const bool less = ((int)(od < d) | ((int)(od == d) & (int)(oi < i))) != 0;  // no branches
+    d = less ? od : d;
+    i = less ? oi : i;
 }
 
 // The search of one candidate by a group of 8 lanes.  Each lane keeps the best
@@ -1182,9 +1181,10 @@ struct ProjGroup {
             const int i = __float_as_int(v.w);
             const double ex = (double)v.x - yx, ey = (double)v.y - yy, ez = (double)v.z - yz;
             const double d2 = ex * ex + ey * ey + ez * ez;
-            if ((d2 < lb || (d2 == lb && i < li)) && dom_has(dom, i)) {
-                lb = d2;
-                li = i;
+            if (((int)(d2 < lb) | ((int)(d2 == lb) & (int)(i < li))) != 0) {
+                const bool in = dom_has(dom, i);
+                lb = in ? d2 : lb;
+                li = in ? i : li;
             }
         }
     }
@@ -1325,8 +1325,9 @@ __device__ inline int project_wave(const GridDev &g, const uint32_t *__restrict_
 // What bounds it: load latency and VALU issue about equally.  A wave per candidate
 // with 4 mm cells of 34 points read 200 points and issued 515 instructions for each;
 // with groups and cells of 2 mm x 1 mm it issues 212 (8,192 poses x 64 draws, 65,536
-// points, 5.7 M candidates of drawn sets: 5.3 -> 3.0 ms).
-__global__ void __launch_bounds__(256, 6)
+// points, 5.7 M candidates of drawn sets: 5.3 -> 2.9 ms).  Seven waves per SIMD; 6 2 % and 8 18 %
+// slower, through the candidate set-up's spills.
+__global__ void __launch_bounds__(256, 7)
 k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
               const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
               const uint32_t *__restrict__ dom_bits, const uint32_t *__restrict__ dom_count,
