@@ -170,14 +170,14 @@ def build_flops(w, vectors: int, dropped: int) -> float:
     per (joint sample, link) the joint frame (two 3x4 products, 63 each, the
     first joint of a finger has one; Rodrigues 34) and the composite window
     map (84); per contact vector the window map (18); per contact vector inside
-    the window the normal (15) and the nearest of the B bin centres by their
-    definition (5 B)."""
-    hand, S, B = w.hand, w.field.samples, w.field.bins
+    the window the normal (15) and its bin: the cell of the candidate table (8)
+    and two candidates' products (10)."""
+    hand, S = w.hand, w.field.samples
     per_sample = 0
     for f in range(hand.n_fingers):
         d = len(hand.finger_joints(f))
         per_sample += d * (63 + 34 + 84) + (d - 1) * 63
-    return float(S) * per_sample + 18.0 * vectors + (15.0 + 5.0 * B) * (vectors - dropped)
+    return float(S) * per_sample + 18.0 * vectors + 33.0 * (vectors - dropped)
 
 
 def realize_flops_per_set(w) -> float:

@@ -1325,8 +1325,8 @@ __device__ inline int project_wave(const GridDev &g, const uint32_t *__restrict_
 // What bounds it: load latency and VALU issue about equally.  A wave per candidate
 // with 4 mm cells of 34 points read 200 points and issued 515 instructions for each;
 // with groups and cells of 2 mm x 1 mm it issues 212 (8,192 poses x 64 draws, 65,536
-// points, 5.7 M candidates of drawn sets: 5.3 -> 2.9 ms).  Seven waves per SIMD; 6 2 % and 8 18 %
-// slower, through the candidate set-up's spills.
+// points, 5.7 M candidates of drawn sets: 5.3 -> 2.9 ms).  Seven waves per SIMD: six
+// are 2 % slower, eight 18 % (the candidates' set-up spills).
 __global__ void __launch_bounds__(256, 7)
 k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
               const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
