@@ -33,6 +33,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -359,14 +360,18 @@ k_query_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx,
 // a bin b set in the finger's merged word(s) at voxel(x) has c_b . q >= cos_hit.
 // Same sweep and block stores as k_query.  Per point the cone is built once as
 // a bin mask over the bins of its polar band that some finger's entry holds;
-// each finger's test is then one AND with its entry.
+// each finger's test is then one AND with its entry.  What bounds it: VALU issue;
+// with 32 bins the masks are 32 bits wide (16,384 poses x 37,176 points without
+// bounds 2.35 ms, 2.55 with 64-bit ones); with 64 bins and bounds 8,191 poses x
+// 30,011 points take 1.6 ms (2.05 before the culling by voxels).
 template <int W, int FM>
 __global__ void __launch_bounds__(kQueryThreads)
 k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__restrict__ pts,
              const float *__restrict__ nrm, int N, const float *__restrict__ poses, const float4 *__restrict__ bounds,
              float cos_hit, uint32_t *__restrict__ dom_bits, uint32_t *__restrict__ dom_count, int uc)
 {
-    __shared__ float cb[3 * kMaxBins];
+    using mask_t = typename std::conditional<W == 1, uint32_t, unsigned long long>::type;  // a bit per bin
+    __shared__ float cb[3 * kMaxBins];  // rows of 3 floats: fewer bank conflicts than of 4
     __shared__ Affine aff[FM];
     __shared__ float4 win[FM];
     __shared__ uint32_t cnt[FM][kQueryWaves];
@@ -422,13 +427,15 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
             const float zlo = qz <= -cos_hit ? -1.f : fmaf(qz, cos_hit, -sq * sin_hit);
             const int blo = max(0, (int)floorf(0.5f * fmaf((float)B, 1.f - zhi, -1.f)) - 1);
             const int bhi = min(B - 1, (int)ceilf(0.5f * fmaf((float)B, 1.f - zlo, -1.f)) + 1);
-            const unsigned long long band = blo > bhi ? 0ull
-                                                      : ((bhi - blo == 63 ? ~0ull : ((1ull << (bhi - blo + 1)) - 1ull))
-                                                         << blo);
-            unsigned long long ent[FM];
+            constexpr int kBits = 8 * (int)sizeof(mask_t);
+            const mask_t band = blo > bhi ? (mask_t)0
+                                          : (mask_t)((bhi - blo == kBits - 1 ? ~(mask_t)0
+                                                                             : (((mask_t)1 << (bhi - blo + 1)) - (mask_t)1))
+                                                     << blo);
+            mask_t ent[FM];
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
-                ent[f] = 0ull;
+                ent[f] = 0;
                 if (keep[f] & cbit) {  // 0 for fingers past F
                     // biased window coordinates (see window_voxel): inside iff all in [G, 2G)
                     const Affine &a = aff[f];
@@ -441,29 +448,29 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
                         const uint32_t *tab = merged + (int64_t)f * W * G3;
                         const uint32_t wv = brick_word(ix, iy, iz, GB);
                         ent[f] = tab[wv];
-                        if (W == 2) ent[f] |= (unsigned long long)tab[G3 + wv] << 32;
+                        if constexpr (W == 2) ent[f] |= (mask_t)tab[G3 + wv] << 32;
                     }
                 }
             }
             const int j2 = 2 * (chunk - u0);
             // the point's cone as a bin mask over the band's bins that some
             // finger's entry holds (the per-finger test is then one AND)
-            unsigned long long cone = 0ull;
+            mask_t cone = 0;
             {
-                unsigned long long u = 0ull;
+                mask_t u = 0;
 #pragma unroll
                 for (int f = 0; f < FM; ++f) u |= ent[f];
-                unsigned long long m = u & band;
+                mask_t m = u & band;
                 while (m) {
-                    const int b = __ffsll((long long)m) - 1;
-                    m &= m - 1ull;
-                    if (fmaf(cb[3 * b], qx, fmaf(cb[3 * b + 1], qy, cb[3 * b + 2] * qz)) >= cos_hit) cone |= 1ull << b;
+                    const int b = W == 1 ? __ffs((int)m) - 1 : __ffsll((long long)m) - 1;
+                    m &= m - (mask_t)1;
+                    if (fmaf(cb[3 * b], qx, fmaf(cb[3 * b + 1], qy, cb[3 * b + 2] * qz)) >= cos_hit) cone |= (mask_t)1 << b;
                 }
             }
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
                 if (!(keep[f] & cbit)) continue;  // the ballot would be 0
-                const bool hit = (ent[f] & cone) != 0ull;
+                const bool hit = (ent[f] & cone) != 0;
                 const unsigned long long bm = __ballot(hit);
                 acc[f] = write_lane(acc[f], (uint32_t)bm, j2);
                 acc[f] = write_lane(acc[f], (uint32_t)(bm >> 32), j2 + 1);
