@@ -215,11 +215,11 @@ __device__ __forceinline__ void draw_pose(uint32_t *prefix, LinkLds &L, uint32_t
     const bool empty = __popc(elig) < k || (palm_pt && palm_pt[g] == -2);
     if (threadIdx.x == 0) pose_valid[g] = empty ? 0 : 1;
     if (empty) {
-        for (int i = threadIdx.x; i < D * k; i += blockDim.x) {
+        for (int64_t i = threadIdx.x; i < (int64_t)D * k; i += blockDim.x) {  // D k may exceed 2^31
             set_pt[(int64_t)g * D * k + i] = -1;
             set_link[(int64_t)g * D * k + i] = -1;
         }
-        for (int d = threadIdx.x; d < D; d += blockDim.x) {  // no LP for these sets
+        for (int64_t d = threadIdx.x; d < D; d += blockDim.x) {  // no LP for these sets
             verdict[(int64_t)g * D + d] = 0;
             tstar[(int64_t)g * D + d] = __builtin_nan("");
         }
@@ -230,18 +230,24 @@ __device__ __forceinline__ void draw_pose(uint32_t *prefix, LinkLds &L, uint32_t
     build_prefix(prefix, dom, F, NW, nsb);
     __syncthreads();
     const uint32_t gg = (uint32_t)(pose_offset + g);
-    for (int c = threadIdx.x; c < D * k; c += blockDim.x) {
-        const int d = c / k, i = c - d * k;  // contact i of set d
+    // contact i of set d, blockDim.x contacts apart (D k may exceed 2^31)
+    const uint32_t step_d = blockDim.x / (uint32_t)k, step_i = blockDim.x - step_d * (uint32_t)k;
+    uint32_t d = threadIdx.x / (uint32_t)k;
+    for (uint32_t i = threadIdx.x - d * (uint32_t)k; d < (uint32_t)D; d += step_d, i += step_i) {
+        if (i >= (uint32_t)k) {
+            i -= (uint32_t)k;
+            if (++d >= (uint32_t)D) break;
+        }
         uint32_t w[4];
         auto word = [&](int q) {  // word q of the set's Philox blocks
-            philox4x32_10(gg, (uint32_t)(4 * d + (q >> 2)), kPurposeDraw, request_id, seed_lo, seed_hi, w);
+            philox4x32_10(gg, 4u * d + ((uint32_t)q >> 2), kPurposeDraw, request_id, seed_lo, seed_hi, w);
             return (q & 2) ? ((q & 1) ? w[3] : w[2]) : ((q & 1) ? w[1] : w[0]);
         };
-        const uint32_t fm = choose_fingers(elig, k, gg, d, request_id, seed_lo, seed_hi);
-        const int f = select_in_word(fm, (uint32_t)i);  // its finger
+        const uint32_t fm = choose_fingers(elig, k, gg, (int)d, request_id, seed_lo, seed_hi);
+        const int f = select_in_word(fm, i);  // its finger
         const int idx = select_domain(prefix + f * (nsb + 1), nsb, dom + (int64_t)f * NW, NW,
                                       __umulhi(word(i), counts[f]));
-        const int64_t at = (int64_t)g * D * k + c;
+        const int64_t at = ((int64_t)g * D + d) * k + i;
         set_pt[at] = idx;
         set_link[at] = (int8_t)(idx >= 0 ? pick_link(H, L.cb4, L.aff[H.lat ? 0 : f], pts, nrm, N, pose, f, idx,
                                                      word(k + i))
@@ -1779,7 +1785,8 @@ k_extend(DevHand H, const float *__restrict__ pts, const float *__restrict__ nrm
     build_prefix(prefix, dom, F, NW, nsb);
     __syncthreads();
     const uint32_t gg = (uint32_t)(pose_offset + g);
-    for (int d = threadIdx.x; d < D; d += blockDim.x) {
+    for (int64_t dd = threadIdx.x; dd < D; dd += blockDim.x) {
+        const int d = (int)dd;
         const int64_t sid = (int64_t)g * D + d;
         const int32_t *sp1 = set_pt1 + sid * k1;
         const int8_t *sl1 = set_link1 + sid * k1;
