@@ -516,7 +516,10 @@ k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__rest
 
 using namespace lg;
 
-static int query_threads(int n_poses) { return n_poses <= 256 ? 1024 : n_poses <= 512 ? 512 : kQueryThreads; }
+// Threads of a pose's block.  2,048 blocks of 256 threads fill the chip; fewer poses
+// get more waves each (16,384 points, 4 fingers: 700 poses 87 us with 256 threads, 57
+// with 512; 1,024 poses 95 and 70).
+static int query_threads(int n_poses) { return n_poses <= 256 ? 1024 : n_poses <= 1024 ? 512 : kQueryThreads; }
 
 static lg_status query_domains(const lg_field *field, const float *pts, const float *nrm, int32_t n_points,
                                const float *poses, int32_t n_poses, const float4 *bounds, uint32_t *dom_bits,
