@@ -53,7 +53,7 @@ k_concave_depth(SdfDev S, const float *__restrict__ pts, const float *__restrict
             const float bx = fmaf(b, y[0], ax), by = fmaf(b, y[1], ay), bz = fmaf(b, y[2], az);
             for (int ic = 0; ic <= m; ++ic) {
                 const float c = step * (float)ic;
-                worst = fmaxf(worst, -sdf_trilinear(S, fmaf(c, nx, bx), fmaf(c, ny, by), fmaf(c, nz, bz)));
+                worst = fmaxf(worst, -sdf_trilinear<false>(S, fmaf(c, nx, bx), fmaf(c, ny, by), fmaf(c, nz, bz)));
             }
         }
     }

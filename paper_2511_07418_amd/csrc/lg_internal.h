@@ -421,9 +421,13 @@ struct SdfDev {
     const float *v;
 };
 
-// Trilinear SDF at object-frame point y; +inf outside the grid.  The cell's
+// Trilinear SDF at object-frame point y; +inf outside the grid.  PAIRS: the cell's
 // corners are read as pairs along x (4-byte aligned), by 32-bit offsets from four
-// uniform row addresses where the grid's bytes fit them.
+// uniform row addresses where the grid's bytes fit them (the penetration test,
+// bound by its reads and addresses).  Without, as eight words from one address: fewer
+// registers, and a short loop over nearby samples overlaps its iterations (the
+// concave filter, 16,384 points x 125 samples: 37.5 us, 41.4 with pairs).
+template <bool PAIRS>
 __device__ inline float sdf_trilinear(const SdfDev &S, float yx, float yy, float yz)
 {
     const float ux = (yx - S.ox) * S.inv_h, uy = (yy - S.oy) * S.inv_h, uz = (yz - S.oz) * S.inv_h;
@@ -431,27 +435,27 @@ __device__ inline float sdf_trilinear(const SdfDev &S, float yx, float yy, float
     if (!((ux >= 0.f) & (ux <= gm) & (uy >= 0.f) & (uy <= gm) & (uz >= 0.f) & (uz <= gm))) return INFINITY;
     const int ix = min((int)ux, S.G - 2), iy = min((int)uy, S.G - 2), iz = min((int)uz, S.G - 2);
     const float fx = ux - ix, fy = uy - iy, fz = uz - iz;
-    typedef float pair_t __attribute__((ext_vector_type(2), aligned(4)));
-    pair_t a00, a10, a01, a11;
-    if (S.G <= 1024) {
+    float c00, c10, c01, c11;
+    if (PAIRS && S.G <= 1024) {
+        typedef float pair_t __attribute__((ext_vector_type(2), aligned(4)));
         const uint32_t G = (uint32_t)S.G, o = (__umul24(__umul24(iz, G) + iy, G) + (uint32_t)ix) << 2;
         const char *v = reinterpret_cast<const char *>(S.v);
-        a00 = *(const pair_t *)(v + o);
-        a10 = *(const pair_t *)(v + 4 * (size_t)G + o);
-        a01 = *(const pair_t *)(v + 4 * (size_t)G * G + o);
-        a11 = *(const pair_t *)(v + 4 * (size_t)G * (G + 1) + o);
+        const pair_t a00 = *(const pair_t *)(v + o);
+        const pair_t a10 = *(const pair_t *)(v + 4 * (size_t)G + o);
+        const pair_t a01 = *(const pair_t *)(v + 4 * (size_t)G * G + o);
+        const pair_t a11 = *(const pair_t *)(v + 4 * (size_t)G * (G + 1) + o);
+        c00 = fmaf(fx, a00.y - a00.x, a00.x);
+        c10 = fmaf(fx, a10.y - a10.x, a10.x);
+        c01 = fmaf(fx, a01.y - a01.x, a01.x);
+        c11 = fmaf(fx, a11.y - a11.x, a11.x);
     } else {
         const int64_t G = S.G;
         const float *v = S.v + (iz * G + iy) * G + ix;
-        a00 = *(const pair_t *)v;
-        a10 = *(const pair_t *)(v + G);
-        a01 = *(const pair_t *)(v + G * G);
-        a11 = *(const pair_t *)(v + G * G + G);
+        c00 = fmaf(fx, v[1] - v[0], v[0]);
+        c10 = fmaf(fx, v[G + 1] - v[G], v[G]);
+        c01 = fmaf(fx, v[G * G + 1] - v[G * G], v[G * G]);
+        c11 = fmaf(fx, v[G * G + G + 1] - v[G * G + G], v[G * G + G]);
     }
-    const float c00 = fmaf(fx, a00.y - a00.x, a00.x);
-    const float c10 = fmaf(fx, a10.y - a10.x, a10.x);
-    const float c01 = fmaf(fx, a01.y - a01.x, a01.x);
-    const float c11 = fmaf(fx, a11.y - a11.x, a11.x);
     const float c0 = fmaf(fy, c10 - c00, c00), c1 = fmaf(fy, c11 - c01, c01);
     return fmaf(fz, c1 - c0, c0);
 }

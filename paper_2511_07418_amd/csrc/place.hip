@@ -185,7 +185,7 @@ k_place_palm(DevHand H, SdfDev S, const float *__restrict__ pts, const float *__
             const float y0 = fmaf(R[0], x0, fmaf(R[3], x1, R[6] * x2));
             const float y1 = fmaf(R[1], x0, fmaf(R[4], x1, R[7] * x2));
             const float y2 = fmaf(R[2], x0, fmaf(R[5], x1, R[8] * x2));
-            depth = fmaxf(depth, cp[6] - sdf_trilinear(S, y0, y1, y2));
+            depth = fmaxf(depth, cp[6] - sdf_trilinear<false>(S, y0, y1, y2));
         }
     }
     palm_pt[g] = depth <= margin ? i : -2;

@@ -617,7 +617,7 @@ __device__ __forceinline__ void penetrate_sets(
                 const float y0 = fmaf(P[0], x0, fmaf(P[4], x1, P[8] * x2));
                 const float y1 = fmaf(P[1], x0, fmaf(P[5], x1, P[9] * x2));
                 const float y2 = fmaf(P[2], x0, fmaf(P[6], x1, P[10] * x2));
-                dp = fmaxf(dp, l.y - sdf_trilinear(S, y0, y1, y2));
+                dp = fmaxf(dp, l.y - sdf_trilinear<true>(S, y0, y1, y2));
             }
             for (int off = 32; off > 0; off >>= 1) dp = fmaxf(dp, __shfl_xor(dp, off, 64));
             if (slot == sl) dep = fmaxf(dep, dp);
