@@ -585,25 +585,25 @@ __device__ __forceinline__ void penetrate_sets(
                 before += n;
             }
         wave_fence();
-        // hand self-collision: this finger's links against those of the higher fingers of the set
-        if (SC && live)
-            for (int f2 = f + 1; f2 < F; ++f2) {
-                const int first2 = H.finger_first[f2], d2 = H.finger_dof[f2];
-                for (int t = 0; t < d; ++t)
-                    for (int t2 = 0; t2 < d2; ++t2) {
-                        const LinkSeg &c1 = segs[slot * J + first + t], &c2 = segs[slot * J + first2 + t2];
-                        const float pen = H.capsule[7 * (first + t) + 6] + H.capsule[7 * (first2 + t2) + 6] -
-                                          segment_distance(c1.a, c1.b, c2.a, c2.b);
-                        dep = fmaxf(dep, pen);
-                    }
-            }
         const int n_slots = (int)min((int64_t)per, nacc - a0);
         for (int sl = 0; sl < n_slots; ++sl) {
             const int n = __builtin_amdgcn_readlane(total, sl * F);
-            if (n == 0) continue;  // not a set, or no sample in the grid
+            // not a set, or nothing to test: no sample in the grid and no other link
+            if (SC ? __builtin_amdgcn_readlane((int)live, sl * F) == 0 : n == 0) continue;
             const float *P = poses + 12 * (int64_t)__builtin_amdgcn_readlane(g, sl * F);
             const LinkSeg *sg = segs + sl * J;
             float dp = -INFINITY;
+            // hand self-collision: the links of finger f1 against all of the later fingers
+            if (SC)
+                for (int f1 = 0; f1 + 1 < F; ++f1) {
+                    const int l0 = H.finger_first[f1], l1 = l0 + H.finger_dof[f1], m = J - l1;
+                    const float rm = 1.0f / (float)m;
+                    for (int i = lane; i < (l1 - l0) * m; i += 64) {
+                        const int t = (int)(((float)i + 0.5f) * rm);  // i / m (i < 512: exact)
+                        const int j1 = l0 + t, j2 = l1 + i - t * m;
+                        dp = fmaxf(dp, link[j1].y + link[j2].y - segment_distance(sg[j1].a, sg[j1].b, sg[j2].a, sg[j2].b));
+                    }
+                }
             int lo = 0;
             for (int i = lane; i < n; i += 64) {
                 while (lo + 1 < J && sg[lo + 1].pre <= i) ++lo;  // the link: the last one with pre <= i
