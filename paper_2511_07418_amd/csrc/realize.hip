@@ -13,6 +13,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lg_internal.h"
 
@@ -475,6 +476,13 @@ __device__ inline void grid_part(const float *yA, const float *yB, float gm, flo
     }
 }
 
+// Sets whose samples a wave takes side by side when it has kManySets or more: a
+// hand's few samples in the grid then fill the lanes, and their reads overlap (65,536
+// sets of 12 links 209 -> 171 us with the joint steps, 262,144 of 22 links 1,103 ->
+// 1,047).  With fewer sets per wave one set after another over all lanes is the
+// faster one (300 sets of 22 links 73 us, 96 with four side by side).
+constexpr int kManySets = 8, kSideBySide = 4;
+
 // A link of a set at its final configuration: axis ends (hand frame), the set's
 // samples before it and its first sample in the grid.
 struct __attribute__((aligned(16))) LinkSeg {
@@ -499,15 +507,16 @@ __device__ inline void wave_fence()
 // realize_sets).  A wave takes 64 / F sets.  First each lane walks its finger's
 // links, the joint frames from the joint values as realize_sets computes them,
 // and leaves the axis ends and the number of axis samples that can lie in the
-// SDF's grid in LDS (the others give no depth).  Then all 64 lanes take the
-// samples of one set after another: neighbouring lanes are 1 mm apart on one
-// axis, so their corner reads fall in few cache lines.  With a lane per finger,
-// 64 lanes read 64 unrelated cells each time: 2.6 ms at six waves per SIMD, 1.7 ms
-// at two inside the step kernel (fewer lines evicted between a lane's samples);
-// 470,724 sets of 22 joints now take 1.4 ms, bound by
-// the lines the corner reads touch (28 per read, one a cycle) and by VALU issue.
-// SC: the hand's self-collision too, by the finger lanes (the set's lanes are in
-// one wave).
+// SDF's grid in LDS (the others give no depth).  Then the lanes take the
+// samples of one set after another, or of a few side by side: neighbouring lanes
+// are 1 mm apart on one axis, so their corner reads fall in few cache lines.  With
+// a lane per finger, 64 lanes read 64 unrelated cells each time: 2.6 ms at six waves
+// per SIMD, 1.7 ms at two inside the step kernel (fewer lines evicted between a
+// lane's samples); 470,724 sets of 22 joints now take 1.3 ms, bound by the lines the
+// corner reads touch (28 per read, one a cycle) and by VALU issue.
+// SC: the hand's self-collision too, a set's pairs of links over the same lanes (a
+// finger's lane for its links took 448 pairs one after another at 8 fingers of 8
+// links: 300 sets 503 us with the joint steps, now 122).
 template <bool SC>
 __device__ __forceinline__ void penetrate_sets(
     char *lds, int64_t bid, int64_t nb, const DevHand &H, const SdfDev &S, const float *__restrict__ poses, int k,
@@ -586,42 +595,64 @@ __device__ __forceinline__ void penetrate_sets(
             }
         wave_fence();
         const int n_slots = (int)min((int64_t)per, nacc - a0);
-        for (int sl = 0; sl < n_slots; ++sl) {
-            const int n = __builtin_amdgcn_readlane(total, sl * F);
-            // not a set, or nothing to test: no sample in the grid and no other link
-            if (SC ? __builtin_amdgcn_readlane((int)live, sl * F) == 0 : n == 0) continue;
-            const float *P = poses + 12 * (int64_t)__builtin_amdgcn_readlane(g, sl * F);
-            const LinkSeg *sg = segs + sl * J;
-            float dp = -INFINITY;
-            // hand self-collision: the links of finger f1 against all of the later fingers
-            if (SC)
-                for (int f1 = 0; f1 + 1 < F; ++f1) {
-                    const int l0 = H.finger_first[f1], l1 = l0 + H.finger_dof[f1], m = J - l1;
-                    const float rm = 1.0f / (float)m;
-                    for (int i = lane; i < (l1 - l0) * m; i += 64) {
-                        const int t = (int)(((float)i + 0.5f) * rm);  // i / m (i < 512: exact)
-                        const int j1 = l0 + t, j2 = l1 + i - t * m;
-                        dp = fmaxf(dp, link[j1].y + link[j2].y - segment_distance(sg[j1].a, sg[j1].b, sg[j2].a, sg[j2].b));
-                    }
+        // depths of the wave's sets, NS at a time, 64 / NS lanes for each
+        auto depths = [&](auto at_a_time) {
+            constexpr int NS = decltype(at_a_time)::value, kLanes = 64 / NS;
+            for (int sl0 = 0; sl0 < n_slots; sl0 += NS) {
+                const int sl = NS == 1 ? sl0 : sl0 + lane / kLanes, sub = lane % kLanes;  // this lane's set
+                int n, gs;
+                bool on;  // a set, and something to test
+                if constexpr (NS == 1) {
+                    n = __builtin_amdgcn_readlane(total, sl * F);
+                    gs = __builtin_amdgcn_readlane(g, sl * F);
+                    on = SC ? __builtin_amdgcn_readlane((int)live, sl * F) != 0 : n > 0;
+                    if (!on) continue;
+                } else {
+                    const bool is = sl < n_slots;
+                    n = __shfl(total, sl * F, 64);
+                    gs = __shfl(g, sl * F, 64);
+                    on = __shfl((int)live, sl * F, 64) != 0 && is;
+                    n = is ? n : 0;
+                    if (__ballot(SC ? on : n > 0) == 0) continue;
                 }
-            int lo = 0;
-            for (int i = lane; i < n; i += 64) {
-                while (lo + 1 < J && sg[lo + 1].pre <= i) ++lo;  // the link: the last one with pre <= i
-                const LinkSeg c = sg[lo];
-                const float2 l = link[lo];
-                const float ts = (float)(c.first + i - c.pre) * l.x;
-                const float x0 = fmaf(ts, c.b[0] - c.a[0], c.a[0]) - P[3];
-                const float x1 = fmaf(ts, c.b[1] - c.a[1], c.a[1]) - P[7];
-                const float x2 = fmaf(ts, c.b[2] - c.a[2], c.a[2]) - P[11];
-                // object frame: R^T (x - t)
-                const float y0 = fmaf(P[0], x0, fmaf(P[4], x1, P[8] * x2));
-                const float y1 = fmaf(P[1], x0, fmaf(P[5], x1, P[9] * x2));
-                const float y2 = fmaf(P[2], x0, fmaf(P[6], x1, P[10] * x2));
-                dp = fmaxf(dp, l.y - sdf_trilinear<true>(S, y0, y1, y2));
+                const float *P = poses + 12 * (int64_t)gs;
+                const LinkSeg *sg = segs + sl * J;
+                float dp = -INFINITY;
+                // hand self-collision: the links of finger f1 against all of the later fingers
+                if (SC && on)
+                    for (int f1 = 0; f1 + 1 < F; ++f1) {
+                        const int l0 = H.finger_first[f1], l1 = l0 + H.finger_dof[f1], m = J - l1;
+                        const float rm = 1.0f / (float)m;
+                        for (int i = sub; i < (l1 - l0) * m; i += kLanes) {
+                            const int t = (int)(((float)i + 0.5f) * rm);  // i / m (i < 512: exact)
+                            const int j1 = l0 + t, j2 = l1 + i - t * m;
+                            dp = fmaxf(dp, link[j1].y + link[j2].y - segment_distance(sg[j1].a, sg[j1].b, sg[j2].a, sg[j2].b));
+                        }
+                    }
+                int lo = 0;
+                for (int i = sub; i < n; i += kLanes) {
+                    while (lo + 1 < J && sg[lo + 1].pre <= i) ++lo;  // the link: the last one with pre <= i
+                    const LinkSeg c = sg[lo];
+                    const float2 l = link[lo];
+                    const float ts = (float)(c.first + i - c.pre) * l.x;
+                    const float x0 = fmaf(ts, c.b[0] - c.a[0], c.a[0]) - P[3];
+                    const float x1 = fmaf(ts, c.b[1] - c.a[1], c.a[1]) - P[7];
+                    const float x2 = fmaf(ts, c.b[2] - c.a[2], c.a[2]) - P[11];
+                    // object frame: R^T (x - t)
+                    const float y0 = fmaf(P[0], x0, fmaf(P[4], x1, P[8] * x2));
+                    const float y1 = fmaf(P[1], x0, fmaf(P[5], x1, P[9] * x2));
+                    const float y2 = fmaf(P[2], x0, fmaf(P[6], x1, P[10] * x2));
+                    dp = fmaxf(dp, l.y - sdf_trilinear<true>(S, y0, y1, y2));
+                }
+                for (int off = kLanes / 2; off > 0; off >>= 1) dp = fmaxf(dp, __shfl_xor(dp, off, 64));
+                if constexpr (NS > 1) dp = __shfl(dp, (slot - sl0) * kLanes, 64);  // of the finger lanes' set
+                if (slot >= sl0 && slot < sl0 + NS) dep = fmaxf(dep, dp);
             }
-            for (int off = 32; off > 0; off >>= 1) dp = fmaxf(dp, __shfl_xor(dp, off, 64));
-            if (slot == sl) dep = fmaxf(dep, dp);
-        }
+        };
+        if (per >= kManySets)
+            depths(std::integral_constant<int, kSideBySide>());
+        else
+            depths(std::integral_constant<int, 1>());
         wave_fence();  // the segments are rewritten by the next sets
         // the set's depth over its F lanes
         float dm = dep;
