@@ -1322,17 +1322,19 @@ __device__ inline int project_wave(const GridDev &g, const uint32_t *__restrict_
 // i's domain (incumbent p_i).  cands[((t k + i) n_inner + j)], t = the set's
 // rank among the sets of valid poses; -1 for sets not drawn.  A wave takes
 // kProjSets sets (few: 16 made 8,800 waves of 640 candidates, one and a half times
-// what the chip holds, and 1.5 times the time) and draws the candidates of the
-// drawn ones 64 at a time, a lane each; a group of 8 lanes then projects each: its own
-// row kProjWindow cells to each side, then the 8 rows around it so, first those
-// candidates that surely end there, so that a group waits for groups with about its
-// own work.  The few with nothing so near go on as a whole wave each (8 lanes took
-// 3.4 ms for them, the wave 1.3).
+// what the chip holds, and 1.5 times the time), and where those would not fill the
+// chip (fill waves) fewer, down to 8 candidates of one set (512 sets of 80 candidates
+// each: 845 us with four sets per wave, 86 so, 301 with a wave per candidate).  It
+// draws the candidates of the drawn ones 64 at a time, a lane each; a group of 8
+// lanes then projects each: its own row kProjWindow cells to each side, then the 8
+// rows around it so, first those candidates that surely end there, so that a group
+// waits for groups with about its own work.  The few with nothing so near go on as a
+// whole wave each (8 lanes took 3.4 ms for them, the wave 1.3).
 // What bounds it: load latency and VALU issue about equally.  A wave per candidate
 // with 4 mm cells of 34 points read 200 points and issued 515 instructions for each;
 // with groups and cells of 2 mm x 1 mm it issues 212 (8,192 poses x 64 draws, 65,536
 // points, 5.7 M candidates of drawn sets: 5.3 -> 2.9 ms).  Seven waves per SIMD: six
-// are 2 % slower, eight 18 % (the candidates' set-up spills).
+// are 2 % slower, eight 18 %; at seven 33 registers of the set-up live in scratch memory.
 __global__ void __launch_bounds__(256, 7)
 k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int N,
               const int32_t *__restrict__ valid_poses, const int32_t *__restrict__ n_valid_poses,
@@ -1340,7 +1342,8 @@ k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int 
               const int32_t *__restrict__ palm_pt, int F, int D, int k, int round, int n_inner, double sigma,
               uint32_t seed_lo, uint32_t seed_hi, uint32_t request_id, int64_t pose_offset,
               const GridDev *__restrict__ gdp, const uint32_t *__restrict__ cell_start,
-              const float4 *__restrict__ cell_pts, const int32_t *__restrict__ set_pt, int32_t *__restrict__ cands)
+              const float4 *__restrict__ cell_pts, const int32_t *__restrict__ set_pt, int fill,
+              int32_t *__restrict__ cands)
 {
     __shared__ ProjLds lds[4];
     ProjLds &L = lds[threadIdx.x >> 6];
@@ -1348,11 +1351,20 @@ k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int 
     const int NW = (N + 31) >> 5;
     const int lane = threadIdx.x & 63, per_set = k * n_inner;
     const int64_t n_sets = (int64_t)(*n_valid_poses) * D;
-    const int64_t step = (int64_t)gridDim.x * 4 * kProjSets;
-    for (int64_t t0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kProjSets; t0 < n_sets; t0 += step) {
+    // a wave's unit: spw sets, or a part of one set's candidates
+    const uint32_t n_waves = gridDim.x * 4, share = min(n_waves, (uint32_t)fill), sets = (uint32_t)n_sets;  // < 2^31
+    const uint32_t spw = sets / kProjSets >= share ? (uint32_t)kProjSets : max(1u, (sets + share - 1) / share);
+    const uint32_t parts = spw > 1 || sets == 0 ? 1u : min((uint32_t)(per_set + 7) >> 3, share / sets);
+    const int part_n = (int)((per_set + parts - 1) / parts + 7) & ~7;  // candidates of a part
+    const uint32_t units = (sets + spw - 1) / spw * parts;
+    for (uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6))); u < units;
+         u += n_waves) {
+        const uint32_t q = parts > 1 ? u / parts : u;
+        const int part = (int)(u - q * parts);
+        const int64_t t0 = (int64_t)q * spw;
         const int64_t t = t0 + lane;
         bool drawn = false;
-        if (lane < kProjSets && t < n_sets) {
+        if (lane < (int)spw && t < n_sets) {
             const int64_t pg = valid_poses[t / D];
             const int d = (int)(t % D);
             const int pc = palm_pt ? palm_pt[pg] : -1;
@@ -1372,13 +1384,13 @@ k_opt_project(const float *__restrict__ pts, const float *__restrict__ nrm, int 
         }
         wave_lds_sync();
         const uint32_t dm = (uint32_t)__ballot(drawn);
-        const int n_here = (int)min((int64_t)kProjSets, n_sets - t0);
+        const int n_here = (int)min((int64_t)spw, n_sets - t0);
         if (__popc(dm) < n_here)
-            for (int e = lane; e < n_here * per_set; e += 64)
+            for (int e = lane + 64 * part; e < n_here * per_set; e += 64 * (int)parts)
                 if (!((dm >> (e / per_set)) & 1u)) cands[t0 * per_set + e] = -1;
-        const int total = __popc(dm) * per_set;
-        for (int c0 = 0; c0 < total; c0 += 64) {
-            const int nb = min(64, total - c0);
+        const int total = __popc(dm) * per_set, end = parts > 1 ? min(total, (part + 1) * part_n) : total;
+        for (int c0 = part * part_n; c0 < end; c0 += 64) {
+            const int nb = min(64, end - c0);
             if (lane < nb) {
                 const int c = c0 + lane, nth = c / per_set, rem = c - nth * per_set, i = rem / n_inner;
                 const int at = select_in_word(dm, (uint32_t)nth);
@@ -2364,8 +2376,13 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
         const int gs = p->opt_inner <= 1 ? 1 : p->opt_inner <= 2 ? 2 : p->opt_inner <= 4 ? 4 : p->opt_inner <= 8 ? 8 : 16;
         const dim3 ogrid((unsigned)std::max<int64_t>(
             1, std::min<int64_t>((n_sets * gs + 255) / 256, (int64_t)n_cu * 8)));
+        // projections: kProjSets sets per wave, or waves that fill the chip (seven per SIMD) as far as there
+        // are 8 candidates for each
+        const int fill = n_cu * 28;
+        const int64_t whole = (n_sets + 4 * kProjSets - 1) / (4 * kProjSets);
+        const int64_t split8 = (n_sets * ((p->k * p->opt_inner + 7) / 8) + 3) / 4;
         const dim3 pgrid((unsigned)std::max<int64_t>(
-            1, std::min<int64_t>((n_sets + 4 * kProjSets - 1) / (4 * kProjSets), (int64_t)n_cu * 64)));
+            1, std::min<int64_t>(std::max(whole, std::min<int64_t>(split8, fill / 4)), (int64_t)n_cu * 64)));
         // grids of the per-candidate criteria (candidates; sets)
         const dim3 cgrid(verdict_blocks(n_sets * p->opt_inner, n_cu));
         const dim3 sgrid((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_sets + 255) / 256, (int64_t)n_cu * 8)));
@@ -2386,7 +2403,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
             hipLaunchKernelGGL(k_opt_project, pgrid, dim3(256), 0, s, pts, nrm, n_points, ws.valid_poses,
                                ws.n_valid_poses, dom_bits, dom_count, palm, H.F, p->draws, p->k, r, p->opt_inner,
                                (double)p->opt_sigma, (uint32_t)p->seed, (uint32_t)(p->seed >> 32), p->request_id,
-                               p->pose_offset, ws.grid, ws.cell_start, ws.cell_pts, set_pt, ws.cands);
+                               p->pose_offset, ws.grid, ws.cell_start, ws.cell_pts, set_pt, fill, ws.cands);
             if (split) {
                 const lg_status so = opt_split_round(pts, nrm, n_points, ws, dom_count, palm, H.F, p, kk, m8, cs,
                                                      sgrid, cgrid, r == p->opt_outer - 1, set_pt, verdict, tstar, s);
