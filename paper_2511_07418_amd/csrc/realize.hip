@@ -719,7 +719,7 @@ k_realize_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ id
 }
 
 template <bool SC>
-__global__ void __launch_bounds__(kRealizeThreads)
+__global__ void __launch_bounds__(kRealizeThreads) __attribute__((amdgpu_waves_per_eu(4)))
 k_penetrate_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx,
                   const uint32_t *__restrict__ first, int n)
 {
