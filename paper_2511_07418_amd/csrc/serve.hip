@@ -238,7 +238,23 @@ struct Req {
 // host memory and copied to the device ahead of the batch's kernels.  A table
 // holds kMaxBatch chunk descriptors and up to kMaxLaunch member lists.
 constexpr int kMaxBatch = 64;
-constexpr int kMaxLaunch = 48;
+
+// Template buckets of the batched kernels (fingers, contacts, joints per finger, 1..8
+// each): members of different buckets go into launches, and member lists, of their own.
+constexpr int fm_bucket(int F) { return F <= 3 ? 3 : F <= 4 ? 4 : F <= 5 ? 5 : 8; }
+constexpr int km_bucket(int k) { return k <= 3 ? 3 : k <= 4 ? 4 : k <= 5 ? 5 : k <= 6 ? 6 : 8; }
+constexpr int dm_bucket(int d) { return d <= 4 ? 4 : d <= 5 ? 5 : d <= 6 ? 6 : 8; }
+constexpr int bucket_count(int (*bucket)(int))
+{
+    int n = 1;
+    for (int v = 2; v <= 8; ++v) n += bucket(v) != bucket(v - 1) ? 1 : 0;
+    return n;
+}
+// the lists of a batch that has every bucket (launch_batch makes no others)
+constexpr int kMaxLaunch = 2 * 2 * bucket_count(fm_bucket)    // query, with the bin words and the windows' form
+                           + 2 * bucket_count(km_bucket)      // verdicts, with 8-edge cones or others
+                           + 2 * 2 * bucket_count(dm_bucket)  // joint steps and penetration, with self-collision or not
+                           + 6;  // draws; compaction of poses and of sets, chunks and ones; accumulation
 constexpr int kMaxBatchSlots = 8;
 constexpr size_t kListBytes = align_up(2 * kMaxBatch) + align_up(4 * (kMaxBatch + 1));
 constexpr size_t kTableBytes = align_up(sizeof(ChunkDesc) * kMaxBatch) + kMaxLaunch * kListBytes;
@@ -368,9 +384,6 @@ static lg_status launch_chunk(lg_server *S, Req *q)
 // ---- batched launches ----------------------------------------------------------
 // The next chunk of each member goes through one launch per stage; members
 // are grouped by the template bucket of the kernels that have one.
-static int fm_bucket(int F) { return F <= 3 ? 3 : F <= 4 ? 4 : F <= 5 ? 5 : 8; }
-static int km_bucket(int k) { return k <= 3 ? 3 : k <= 4 ? 4 : k <= 5 ? 5 : k <= 6 ? 6 : 8; }
-static int dm_bucket(int d) { return d <= 4 ? 4 : d <= 5 ? 5 : d <= 6 ? 6 : 8; }
 
 // host view of a slot's table while it is filled
 struct TableWriter {
