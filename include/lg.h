@@ -440,7 +440,7 @@ typedef struct lg_server lg_server;
 typedef struct {
     uint64_t budget_bytes;  /* device memory reserved for admitted requests */
     int32_t max_active;     /* requests in flight at once, 1..64 */
-    int32_t chunk_poses;    /* poses per scheduling quantum, >= 1 */
+    int32_t chunk_poses;    /* poses per scheduling quantum, >= 1 (batched: at most 131,072 are taken) */
     int32_t batched;        /* 1: batched launches over a descriptor table (see above) */
     int32_t batch_slots;    /* batched mode: batches in flight at once, 1..8 (0: 4) */
 } lg_server_params;

@@ -22,6 +22,9 @@ constexpr int kMaxBins = 64;
 constexpr uint32_t kPurposeJoint = 1u;
 constexpr uint32_t kPurposeDraw = 3u;
 constexpr int32_t kNoWitness = 0x7fffffff;
+// Poses of one launch that gives each a block of up to 256 threads: a grid holds fewer than
+// 2^32 threads (beyond, only the first few poses were computed), so more go in several launches.
+constexpr int32_t kMaxGridPoses = 1 << 23;
 constexpr int kCullLevels = 8;  // dilations of a finger's occupied voxels (cull_reach)
 constexpr int kLutRes = 28;  // cube-map cells per face edge of the bin table (18.4 KiB in LDS)
 

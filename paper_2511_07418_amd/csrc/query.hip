@@ -537,22 +537,28 @@ static lg_status query_domains(const lg_field *field, const float *pts, const fl
     // A pose is one block.  Few poses leave the chip short of waves, so they
     // get larger blocks (up to 16 waves).
     const int tb = query_threads(n_poses), uc = query_unit(n_points, tb / 64);
-#define LG_QUERY_C(W, FM, LAT, CULL)                                                                        \
-    hipLaunchKernelGGL((k_query<W, FM, LAT, CULL>), dim3(n_poses), dim3(tb), 0, s, H, field->d_merged, pts,  \
-                       nrm, n_points, poses, bounds, dom_bits, dom_count, uc)
+    const int64_t row = (int64_t)H.F * ((n_points + 31) / 32);
+    for (int64_t g0 = 0; g0 < n_poses; g0 += kMaxGridPoses) {
+        const dim3 grid((unsigned)std::min<int64_t>(n_poses - g0, kMaxGridPoses));
+        const float *po = poses + 12 * g0;
+        uint32_t *db = dom_bits + row * g0, *dc = dom_count + H.F * g0;
+#define LG_QUERY_C(W, FM, LAT, CULL)                                                                              \
+    hipLaunchKernelGGL((k_query<W, FM, LAT, CULL>), grid, dim3(tb), 0, s, H, field->d_merged, pts, nrm, n_points, \
+                       po, bounds, db, dc, uc)
 #define LG_QUERY(W, FM, LAT)                                                                                 \
     do { if (bounds || !LAT) LG_QUERY_C(W, FM, LAT, true); else LG_QUERY_C(W, FM, LAT, !LAT); } while (0)
 #define LG_QUERY_F(W, LAT)                                                                                   \
     if (H.F <= 3) LG_QUERY(W, 3, LAT); else if (H.F <= 4) LG_QUERY(W, 4, LAT);                               \
     else if (H.F <= 5) LG_QUERY(W, 5, LAT); else LG_QUERY(W, 8, LAT)
-    if (H.lat) {
-        if (H.W == 1) { LG_QUERY_F(1, true); } else { LG_QUERY_F(2, true); }
-    } else {
-        if (H.W == 1) { LG_QUERY_F(1, false); } else { LG_QUERY_F(2, false); }
-    }
+        if (H.lat) {
+            if (H.W == 1) { LG_QUERY_F(1, true); } else { LG_QUERY_F(2, true); }
+        } else {
+            if (H.W == 1) { LG_QUERY_F(1, false); } else { LG_QUERY_F(2, false); }
+        }
 #undef LG_QUERY_F
 #undef LG_QUERY
 #undef LG_QUERY_C
+    }
     LG_HIP(hipGetLastError());
     return LG_OK;
 }
@@ -655,16 +661,20 @@ extern "C" lg_status lg_query_domains_cone(const lg_field *field, const float *p
         return fail(LG_EINVAL, "null device buffer");
     hipStream_t s = as_stream(stream);
     const DevHand &H = field->dh;
-#define LG_QCONE(W, FM)                                                                                        \
-    hipLaunchKernelGGL((k_query_cone<W, FM>), dim3(n_poses), dim3(kQueryThreads), 0, s, H, field->d_merged, pts, \
-                       nrm, n_points, poses, reinterpret_cast<const float4 *>(bounds), cos_hit, dom_bits, dom_count,     \
-                       query_unit(n_points, kQueryWaves))
-    if (H.W == 1) {
-        if (H.F <= 3) LG_QCONE(1, 3); else if (H.F <= 4) LG_QCONE(1, 4); else if (H.F <= 5) LG_QCONE(1, 5); else LG_QCONE(1, 8);
-    } else {
-        if (H.F <= 3) LG_QCONE(2, 3); else if (H.F <= 4) LG_QCONE(2, 4); else if (H.F <= 5) LG_QCONE(2, 5); else LG_QCONE(2, 8);
-    }
+    const int64_t row = (int64_t)H.F * ((n_points + 31) / 32);
+    for (int64_t g0 = 0; g0 < n_poses; g0 += kMaxGridPoses) {
+        const dim3 grid((unsigned)std::min<int64_t>(n_poses - g0, kMaxGridPoses));
+#define LG_QCONE(W, FM)                                                                                          \
+    hipLaunchKernelGGL((k_query_cone<W, FM>), grid, dim3(kQueryThreads), 0, s, H, field->d_merged, pts, nrm,     \
+                       n_points, poses + 12 * g0, reinterpret_cast<const float4 *>(bounds), cos_hit,             \
+                       dom_bits + row * g0, dom_count + H.F * g0, query_unit(n_points, kQueryWaves))
+        if (H.W == 1) {
+            if (H.F <= 3) LG_QCONE(1, 3); else if (H.F <= 4) LG_QCONE(1, 4); else if (H.F <= 5) LG_QCONE(1, 5); else LG_QCONE(1, 8);
+        } else {
+            if (H.F <= 3) LG_QCONE(2, 3); else if (H.F <= 4) LG_QCONE(2, 4); else if (H.F <= 5) LG_QCONE(2, 5); else LG_QCONE(2, 8);
+        }
 #undef LG_QCONE
+    }
     LG_HIP(hipGetLastError());
     return LG_OK;
 }

@@ -1757,7 +1757,7 @@ __device__ inline int link_finger(const DevHand &H, int l)
 // set of the pose was extended (its verdicts are computed next).
 __global__ void __launch_bounds__(kDrawThreads)
 k_extend(DevHand H, const float *__restrict__ pts, const float *__restrict__ nrm,
-         int N, const float *__restrict__ poses, const uint32_t *__restrict__ dom_bits,
+         int N, int g0, const float *__restrict__ poses, const uint32_t *__restrict__ dom_bits,
          const uint32_t *__restrict__ dom_count, int D, int k1, int k_add, const int32_t *__restrict__ set_pt1,
          const int8_t *__restrict__ set_link1, const uint8_t *__restrict__ verdict1, const int32_t *__restrict__ list,
          const int32_t *__restrict__ list_n, const uint8_t *__restrict__ list_ok, uint32_t seed_lo, uint32_t seed_hi,
@@ -1769,7 +1769,7 @@ k_extend(DevHand H, const float *__restrict__ pts, const float *__restrict__ nrm
     __shared__ uint32_t counts[kMaxFingers];
     __shared__ int32_t range[2];
     __shared__ uint32_t any;
-    const int g = blockIdx.x, F = H.F, k2 = k1 + k_add;
+    const int g = g0 + (int)blockIdx.x, F = H.F, k2 = k1 + k_add;
     const int NW = (N + 31) >> 5, nsb = (NW + kSuper - 1) / kSuper;
     const uint32_t *dom = dom_bits + (int64_t)g * F * NW;
     const float *pose = poses + 12 * (int64_t)g;
@@ -2336,9 +2336,15 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
     const bool split = opt && split_fits(n_poses, p->draws, p) &&
                        workspace_bytes >= search_ws_bytes(n_points, n_poses, p, true);
     const SearchWs ws = search_ws(workspace, n_points, n_poses, p->draws, opt, p->k, opt ? p->opt_inner : 0, split);
-    hipLaunchKernelGGL(k_draw, dim3(n_poses), dim3(kDrawThreads), lds, s, H, pts, nrm, n_points,
-                       poses, dom_bits, dom_count, palm, p->draws, p->k, (uint32_t)p->seed, (uint32_t)(p->seed >> 32),
-                       p->request_id, p->pose_offset, set_pt, set_link, ws.pose_valid, verdict, tstar);
+    const int64_t row = (int64_t)H.F * NW;
+    for (int64_t g0 = 0; g0 < n_poses; g0 += kMaxGridPoses) {
+        const int64_t s0 = g0 * p->draws;
+        hipLaunchKernelGGL(k_draw, dim3((unsigned)std::min<int64_t>(n_poses - g0, kMaxGridPoses)), dim3(kDrawThreads),
+                           lds, s, H, pts, nrm, n_points, poses + 12 * g0, dom_bits + row * g0, dom_count + H.F * g0,
+                           palm ? palm + g0 : nullptr, p->draws, p->k, (uint32_t)p->seed, (uint32_t)(p->seed >> 32),
+                           p->request_id, p->pose_offset + g0, set_pt + s0 * p->k, set_link + s0 * p->k,
+                           ws.pose_valid + g0, verdict + s0, tstar + s0);
+    }
     LG_HIP(hipGetLastError());
     // list of poses with at least k non-empty domains (ordered)
     lg_status st = compact(ws.pose_valid, n_poses, ws.pchunk_count, ws.pchunk_off, ws.valid_poses, ws.n_valid_poses, s);
@@ -2500,10 +2506,12 @@ lg_status lg_search_extend(const lg_field *field, const float *pts, const float 
     if (lds > 48 * 1024) return fail(LG_EUNSUPPORTED, "too many points for the draw rank structure");
     hipStream_t s = as_stream(stream);
     const SearchWs ws = search_ws(workspace, n_points, n_poses, p->draws, false);
-    hipLaunchKernelGGL(k_extend, dim3(n_poses), dim3(kDrawThreads), lds, s, H, pts, nrm, n_points,
-                       poses, dom_bits, dom_count, p->draws, k1, ep->k_add, set_pt1, set_link1, verdict1, ep->list,
-                       ep->list_n, ep->list_ok, (uint32_t)p->seed, (uint32_t)(p->seed >> 32), ep->request_id,
-                       p->pose_offset, set_pt2, set_link2, ws.pose_valid, verdict2, tstar2);
+    for (int64_t g0 = 0; g0 < n_poses; g0 += kMaxGridPoses)
+        hipLaunchKernelGGL(k_extend, dim3((unsigned)std::min<int64_t>(n_poses - g0, kMaxGridPoses)), dim3(kDrawThreads),
+                           lds, s, H, pts, nrm, n_points, (int)g0, poses, dom_bits, dom_count, p->draws, k1, ep->k_add,
+                           set_pt1, set_link1, verdict1, ep->list, ep->list_n, ep->list_ok, (uint32_t)p->seed,
+                           (uint32_t)(p->seed >> 32), ep->request_id, p->pose_offset, set_pt2, set_link2,
+                           ws.pose_valid, verdict2, tstar2);
     LG_HIP(hipGetLastError());
     const lg_status st =
         compact(ws.pose_valid, n_poses, ws.pchunk_count, ws.pchunk_off, ws.valid_poses, ws.n_valid_poses, s);

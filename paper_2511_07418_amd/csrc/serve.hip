@@ -164,16 +164,25 @@ struct ReqLayout {
     uint64_t total;
 };
 
+constexpr int kMaxBatch = 64;  // members of a batch
+
 static bool batched_request(const lg_server_params &sp, const lg_request &r)
 {
     return sp.batched && r.search.opt_outer == 0;
+}
+
+// Poses of a request's chunks.  A batched launch has a block per pose of all its members
+// (kMaxBatch), which must stay within kMaxGridPoses.
+static int64_t chunk_of(const lg_server_params &sp, const lg_request &r)
+{
+    return batched_request(sp, r) ? std::min<int64_t>(sp.chunk_poses, kMaxGridPoses / kMaxBatch) : sp.chunk_poses;
 }
 
 static ReqLayout layout_of(const lg_server_params &sp, const lg_request &r)
 {
     const lg_field *f = r.field;
     const int F = f->dh.F, J = f->dh.J, k = r.search.k, D = r.search.draws;
-    const int64_t N = r.n_points, chunk = std::min<int64_t>(sp.chunk_poses, r.n_poses);
+    const int64_t N = r.n_points, chunk = std::min<int64_t>(chunk_of(sp, r), r.n_poses);
     const int64_t NW = (N + 31) / 32, sets = chunk * D;
     ReqLayout L;
     uint64_t off = 0;
@@ -237,8 +246,6 @@ struct Req {
 // Batched launches: one descriptor table per batch slot, staged in pinned
 // host memory and copied to the device ahead of the batch's kernels.  A table
 // holds kMaxBatch chunk descriptors and up to kMaxLaunch member lists.
-constexpr int kMaxBatch = 64;
-
 // Template buckets of the batched kernels (fingers, contacts, joints per finger, 1..8
 // each): members of different buckets go into launches, and member lists, of their own.
 constexpr int fm_bucket(int F) { return F <= 3 ? 3 : F <= 4 ? 4 : F <= 5 ? 5 : 8; }
@@ -334,7 +341,7 @@ static lg_status launch_chunk(lg_server *S, Req *q)
     char *base = S->slab.base + q->off;
     const ReqLayout &L = q->L;
     const int64_t g0 = q->next_pose;
-    const int32_t P = (int32_t)std::min<int64_t>(S->p.chunk_poses, r.n_poses - g0);
+    const int32_t P = (int32_t)std::min<int64_t>(chunk_of(S->p, r), r.n_poses - g0);
     const float *pts = reinterpret_cast<const float *>(base + L.pts);
     const float *nrm = reinterpret_cast<const float *>(base + L.nrm);
     const float *poses = reinterpret_cast<const float *>(base + L.poses) + 12 * g0;
@@ -405,7 +412,7 @@ struct TableWriter {
             t += nb[j];
             first[j + 1] = (uint32_t)t;
         }
-        if (t > 0x7fffffffull) return fail(LG_EINVAL, "batched launch above 2^31 - 1 blocks");
+        if (t > 2ull * kMaxGridPoses - 1) return fail(LG_EINVAL, "batched launch above 2^24 - 1 blocks of 256 threads");
         out.d = reinterpret_cast<const ChunkDesc *>(dev);
         out.idx = reinterpret_cast<const uint16_t *>(dev + off);
         out.first = reinterpret_cast<const uint32_t *>(dev + foff);
@@ -502,7 +509,7 @@ static lg_status launch_batch(lg_server *S, BatchSlot &B)
     std::vector<int> all(n);
     for (int j = 0; j < n; ++j) {
         Req *q = B.members[j];
-        const int32_t P = (int32_t)std::min<int64_t>(S->p.chunk_poses, q->r.n_poses - q->next_pose);
+        const int32_t P = (int32_t)std::min<int64_t>(chunk_of(S->p, q->r), q->r.n_poses - q->next_pose);
         const int buf = __builtin_ctz(~q->buf_busy);  // a free working-buffer copy (inflight < nbuf)
         fill_desc(S, q, P, buf, cd[j]);
         B.bufs[j] = buf;
@@ -749,7 +756,7 @@ static void worker_loop(lg_server *S)
             // batches as there are free slots, of about equal size: small
             // chunks share a batch instead of waiting behind large ones.
             auto work = [&](const Req *q) {
-                return (double)std::min<int64_t>(S->p.chunk_poses, q->r.n_poses - q->next_pose) * q->r.n_points;
+                return (double)std::min<int64_t>(chunk_of(S->p, q->r), q->r.n_poses - q->next_pose) * q->r.n_points;
             };
             std::stable_sort(idle.begin(), idle.end(), [&](const Req *x, const Req *y) { return work(x) < work(y); });
             double total = 0;
