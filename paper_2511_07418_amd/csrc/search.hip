@@ -2208,8 +2208,6 @@ static SearchWs search_ws(void *base, int64_t n_points, int64_t n_poses, int64_t
             w.split.sB = reinterpret_cast<int32_t *>(take((size_t)n_sets * 28));
             w.split.cJ = reinterpret_cast<double *>(take(nc_ * 8));
             w.split.cB = reinterpret_cast<int32_t *>(take(nc_ * 28));
-            take(nc_ * 4);  // not used: the size asked for (40 B per candidate) is part of the interface
-            take((size_t)std::max<int64_t>(k, 1) * 4);
         }
     }
     w.bytes = off + 256;
