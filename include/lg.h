@@ -183,9 +183,9 @@ lg_status lg_query_domains_cone(const lg_field *field, const float *pts, const f
  * float (centre of the chunk's box, radius padded by 1e-5 relative + 1e-7 m),
  * 16-byte aligned.  pts DEVICE SoA [3][N].  Compute once per object.
  * lg_query_domains_bounded -- lg_query_domains with those bounds: a (chunk,
- * finger) pair whose sphere (plus 1e-3 voxel) misses the finger's window is
- * skipped (its domain bits are 0, as the lookups would give), and a chunk
- * missing every window is not read.  Outputs are identical to
+ * finger) pair whose sphere (plus 1e-3 voxel) misses the finger's window, or
+ * every voxel of it that holds a bin, is skipped (its domain bits are 0, as the
+ * lookups would give), and a chunk that no finger keeps is not read.  Outputs are identical to
  * lg_query_domains'; the saving depends on spatially compact chunks, e.g.
  * points in the order of lg_morton_order.  LG_EINVAL on null or misaligned
  * bounds, plus lg_query_domains' errors.
@@ -276,8 +276,8 @@ lg_status lg_search(const lg_field *field, const float *pts, const float *nrm, i
  * as lg_search, minus workspace/workspace_bytes: the workspace is a static
  * device array of lg_search_noalloc_max_bytes() bytes (8 MiB) per GPU, held
  * until the process ends; its device address is looked up once per device on
- * the first call there.  The per-candidate arrays of Alg. 2's gathered slow
- * LPs are used only when they fit; calls whose least workspace (see
+ * the first call there.  The per-candidate arrays of Alg. 2's criteria
+ * are used only when they fit; calls whose least workspace (see
  * lg_search_workspace_bytes) exceeds that size fail with LG_EINVAL before
  * anything is enqueued.  No call allocates:
  * no hipMalloc, hipFree or allocating library routine, and no memset node

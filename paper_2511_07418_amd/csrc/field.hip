@@ -645,7 +645,7 @@ lg_status lg_build_field(const lg_hand_desc *hand, const lg_field_params *params
     if (st != LG_OK) return st;
     hipStream_t s = as_stream(stream);
     const DevHand &H = f->dh;
-    // scratch: the dropped count and, with a witness, the table of the rounds before
+    // scratch: the dropped count and, for more than one round, the table of the rounds before
     unsigned long long *d_drop = nullptr;
     uint32_t *done = nullptr;
     hipError_t e = hipMalloc(&d_drop, sizeof(unsigned long long));

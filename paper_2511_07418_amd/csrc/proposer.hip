@@ -248,7 +248,8 @@ __device__ inline void fold_rows(f32x16_t a, int row0, int end, int half, float 
 // point; one lane-half swap per dword turns them into the layer-2 A operand
 // (8 consecutive channels of one point) without going through LDS.
 // Registers, not LDS, set the occupancy: the H1 of two row blocks, two
-// accumulators and the running pairs take 174 VGPRs, two waves per SIMD.
+// accumulators and the running pairs take 158 VGPRs, three waves per SIMD, so a
+// CU holds one workgroup of 8 waves.
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))) void
 k_encode(const float *__restrict__ x, int Np, int steps, const uint16_t *__restrict__ T, const float *__restrict__ P,
          unsigned long long *__restrict__ keys)
@@ -917,9 +918,11 @@ lg_status forward(lg_prop *p, const float *x, int B, int Np, hipStream_t s, floa
         hipLaunchKernelGGL(k_fill_u64, dim3(blocks((int64_t)p->max_batch * kH2, 256)), dim3(256), 0, s, p->keys,
                            (int64_t)p->max_batch * kH2);
     p->keys_dirty = true;
-    // Steps per wave: as many as keep two workgroups (the LDS of W2 allows two)
-    // on each of 256 CUs; fewer objects take shorter workgroups, each of which
-    // stages W2 again (32 objects of 2,048 points: 4 steps 34 us, 1 step 14 us).
+    // Steps per wave: as many as leave 512 workgroups, two rounds of the 256 CUs; each
+    // stages W2 again, so no more than that (32 objects of 2,048 points: 4 steps 34 us,
+    // 1 step 14 us).  With the line at 256, where the last round may be nearly empty,
+    // 192 and 384 objects take 48 and 77 us instead of 43 and 66 (128 and 256 objects 4 %
+    // less); at 1,024, 256 and 512 objects take 6 and 4 % more.
     int steps = kEncMaxSteps;
     while (steps > 1 && (int64_t)B * blocks(Np, kEncStep * steps) < 512) steps >>= 1;
     hipLaunchKernelGGL(k_encode, dim3(blocks(Np, kEncStep * steps), B), dim3(kEncThreads), 0, s, x, Np, steps, p->T,

@@ -23,13 +23,15 @@
 // zero without a lookup, and a chunk that no finger keeps is not loaded at all.
 //
 // What bounds it: VALU issue, with the L1's line rate close behind (65,536 poses x
-// 65,536 points, 22 joints: 5.3 G wave instructions and 3.6 G line accesses, 94 % and
-// 70 % of what 8.6 ms allow; 7 waves per SIMD 2 % slower than 8).  8.0 G instructions
-// in 12.0 ms before the culling by voxels, the bin index in float arithmetic, the
+// 65,536 points, 22 joints: 6.0 G wave instructions and 3.8 G line accesses in 9.1 ms,
+// the latter two thirds of one per CU and cycle; 7 waves per SIMD are 2 % slower than 8,
+// and forms with a few more instructions per kept chunk 1 to 2 %).  8.3 G instructions
+// in 13.0 ms before the culling by voxels, the bin index in float arithmetic, the
 // in-brick word by three multiply-adds, the scalar chunk bookkeeping and two
 // candidate bins instead of four; the last 0.5 ms were registers kept in scratch
-// memory across the units.  About 105 instructions per kept chunk: 9 for the
-// direction, 40 for its bin, 30 for the cell and word, 9 per kept finger.
+// memory across the units (up to five fingers none; the kernel for eight spills 5).
+// About 105 instructions per kept chunk: 9 for the direction, 40 for its bin, 30 for
+// the cell and word, 9 per kept finger.
 #include <math.h>
 
 #include <algorithm>
@@ -371,8 +373,9 @@ k_query_batch(const ChunkDesc *__restrict__ d, const uint16_t *__restrict__ idx,
 // a bin mask over the bins of its polar band that some finger's entry holds;
 // each finger's test is then one AND with its entry.  What bounds it: VALU issue;
 // with 32 bins the masks are 32 bits wide (16,384 poses x 37,176 points without
-// bounds 2.35 ms, 2.55 with 64-bit ones); with 64 bins and bounds 8,191 poses x
-// 30,011 points take 1.6 ms (2.05 before the culling by voxels).
+// bounds 2.25 ms, 2.44 with 64-bit ones); with 64 bins and bounds 8,191 poses x
+// 30,011 points take 1.6 ms (2.1 before the culling by voxels).  A pose has 256
+// threads also where there are few (more were not tried here).
 template <int W, int FM>
 __global__ void __launch_bounds__(kQueryThreads)
 k_query_cone(DevHand H, const uint32_t *__restrict__ merged, const float *__restrict__ pts,

@@ -512,7 +512,7 @@ __device__ inline void wave_fence()
 // are 1 mm apart on one axis, so their corner reads fall in few cache lines.  With
 // a lane per finger, 64 lanes read 64 unrelated cells each time: 2.6 ms at six waves
 // per SIMD, 1.7 ms at two inside the step kernel (fewer lines evicted between a
-// lane's samples); 470,724 sets of 22 joints now take 1.3 ms, bound by the lines the
+// lane's samples); 470,724 sets of 22 joints now take 1.2 ms, bound by the lines the
 // corner reads touch (28 per read, one a cycle) and by VALU issue.
 // SC: the hand's self-collision too, a set's pairs of links over the same lanes (a
 // finger's lane for its links took 448 pairs one after another at 8 fingers of 8

@@ -1918,8 +1918,10 @@ __device__ inline void flags_write(const uint4 &v, int64_t i, int32_t *__restric
 // Up to kCompactOneMax flags: one block of 1,024 threads, a run of flags each (a
 // multiple of 16), counts scanned over lanes and waves, then each thread writes
 // its run's indices.  A few thousand flags take 3-4 us in one launch (18 us in the
-// three of count, scan and scatter); beyond the limit one CU's reads and writes
-// cost more than they save (65,536 flags 21 us, 262,144 47 us; two launches 10 us).
+// three of count, scan and scatter) on an idle chip; among other streams' work the
+// block waits for a CU with 16 free waves (20 us on average under a busy server).
+// Beyond the limit one CU's reads and writes cost more than they save (65,536 flags
+// 21 us, 262,144 47 us; two launches 10 us).
 constexpr int kCompactOneThreads = 1024;
 constexpr int64_t kCompactOneMax = 32768;
 constexpr int64_t kSelfScanMax = 2048;  // chunks whose counts every scatter block adds up itself (4 us less)
@@ -2354,7 +2356,7 @@ static lg_status search_impl(const lg_field *field, const float *pts, const floa
     LG_HIP(hipGetDevice(&dev));
     LG_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     const dim3 lgrid(verdict_blocks(n_sets, n_cu));
-    // the common 8-edge cone gets kernels with the edge loop unrolled
+    // the common 8-edge cone gets kernels that price a contact's best edge in closed form
     const bool m8 = p->m_edges == 8;
 #define LG_VERDICT_M(KM, MC)                                                                                    \
     hipLaunchKernelGGL((k_verdict_lane<KM, MC>), lgrid, dim3(256), 0, s, pts, nrm, n_points, set_pt, palm,       \
