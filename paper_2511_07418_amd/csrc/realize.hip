@@ -478,8 +478,8 @@ __device__ inline void grid_part(const float *yA, const float *yB, float gm, flo
 
 // Sets whose samples a wave takes side by side when it has kManySets or more: a
 // hand's few samples in the grid then fill the lanes, and their reads overlap (65,536
-// sets of 12 links 209 -> 171 us with the joint steps, 262,144 of 22 links 1,103 ->
-// 1,047).  With fewer sets per wave one set after another over all lanes is the
+// sets of 12 links in two fingers 209 -> 171 us with the joint steps, 262,144 of 22
+// links 1,103 -> 1,047).  With fewer sets per wave one set after another over all lanes is the
 // faster one (300 sets of 22 links 73 us, 96 with four side by side).
 constexpr int kManySets = 8, kSideBySide = 4;
 
@@ -490,11 +490,23 @@ struct __attribute__((aligned(16))) LinkSeg {
     int pre, first;
 };
 
+// Sets per wave of the penetration test: a lane per finger, and no more than leave
+// room for four blocks' segments in a CU's 160 KB, which is the launch's size and what
+// the registers allow (1 finger of 8 links: 64 sets per wave leave room for two blocks,
+// 8 x 8 links two, 2 x 6 three).  With the joint steps, 65,536 sets: 2 x 6 links 172 ->
+// 136 us, 1 x 8 157 -> 127, 6 x 7 882 -> 714, 8 x 8 1,077 -> 922.
+__host__ __device__ inline int penetrate_sets_per_wave(int F, int J)
+{
+    const int room = (40960 - J * (int)sizeof(float2)) / (kRealizeThreads / 64 * J * (int)sizeof(LinkSeg));
+    return room < 64 / F ? room : 64 / F;  // J <= 64: room >= 4
+}
+
 // LDS of a block: a LinkSeg per (set, link) of each wave, and per link the
 // sample spacing 1 / (M - 1) and the radius
 __host__ __device__ inline size_t penetrate_lds(int F, int J)
 {
-    return (size_t)(kRealizeThreads / 64) * (64 / F) * J * sizeof(LinkSeg) + (size_t)J * sizeof(float2);
+    return (size_t)(kRealizeThreads / 64) * penetrate_sets_per_wave(F, J) * J * sizeof(LinkSeg) +
+           (size_t)J * sizeof(float2);
 }
 
 __device__ inline void wave_fence()
@@ -524,7 +536,7 @@ __device__ __forceinline__ void penetrate_sets(
     const IkDev &ik, const float *__restrict__ q_in, const float *__restrict__ cerr, const float *__restrict__ cang,
     float *__restrict__ depth_out, uint8_t *__restrict__ valid_out)
 {
-    const int J = H.J, F = H.F, spw = 64 / F;
+    const int J = H.J, F = H.F, spw = penetrate_sets_per_wave(F, J);
     const int tid = threadIdx.x, lane = tid & 63, slot = lane / F, f = lane - slot * F;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     LinkSeg *segs = reinterpret_cast<LinkSeg *>(lds) + (size_t)wave * spw * J;  // [set][link]
@@ -535,7 +547,7 @@ __device__ __forceinline__ void penetrate_sets(
     const int64_t nacc = min((int64_t)*n_acc_dev, (int64_t)max_acc);
     const int first = H.finger_first[f], d = H.finger_dof[f];
     const float gm = (float)(S.G - 1);
-    // few sets: fewer than 64 / F per wave, so that every wave has some
+    // few sets: fewer than spw per wave, so that every wave has some
     const int64_t waves = nb * (kRealizeThreads / 64);
     const int per = (int)max((int64_t)1, min((int64_t)spw, (nacc + waves - 1) / waves));
     for (int64_t a0 = (bid * (kRealizeThreads / 64) + wave) * per; a0 < nacc; a0 += waves * per) {
